@@ -290,30 +290,6 @@ __device__ __forceinline__ void rescale_block16(uint32_t (&w)[8], float f)
     for (int i = 0; i < 8; ++i) w[i] = pack_bf16x2(bf16lo_to_f32(w[i]) * f, bf16hi_to_f32(w[i]) * f);
 }
 
-// ---- straight-line forms for kernels that hold many blocks per lane -------------------------------
-// The functions above take one block from start to end.  The forms below run two independent chains of
-// work through one stretch of code -- two blocks for the plain rule, the two candidates of one block for
-// the scale search -- so that the latency of one chain's dependent instructions (a conversion writes one
-// byte of its destination, so the four that fill a code word wait on one another) hides behind the other.
-// The results are the exact ones: the common case is decided by fp32 arithmetic alone, and the rare
-// near-tie drops into the same exact resolution the functions above use.
-
-// Block scale byte for quotient q = bmax * inv_msg in the normal E4M3 range, by integer arithmetic on
-// the bits of q.  "unsure" is raised when q lies within 24 ulps of a rounding tie (the true quotient lies
-// within 16 ulps of q), below the normal range (subnormal scales, zero blocks), or is not an ordinary
-// number; the caller then calls block_scale_exact.
-__device__ __forceinline__ uint32_t block_scale_fast(float q, bool &unsure)
-{
-    q = fminf(q, kFp8Max);
-    const uint32_t u = __float_as_uint(q);
-    const uint32_t b = ((u + 0x7FFFFu + ((u >> 20) & 1u)) >> 20) - 960u;
-    unsure = ((u & 0xFFFFFu) - (0x80000u - 24u) <= 48u) | !(q >= 0.015625f * 1.0001f);
-    return b;
-}
-
-// E4M3 byte (normal range, as block_scale_fast returns it) -> f32, one instruction
-__device__ __forceinline__ float e4m3_normal_to_f32(uint32_t b) { return __uint_as_float((b << 20) + (120u << 23)); }
-
 // largest magnitude of 16 bf16 values as a float (exact: a maximum of exact values)
 __device__ __forceinline__ float block_absmax_f32(const uint32_t (&w)[8])
 {
@@ -341,6 +317,153 @@ __device__ __forceinline__ void unpack16(const uint32_t (&w)[8], float (&f)[16])
     }
 }
 
+// ---- one-sided encoder ------------------------------------------------------------------------------
+// Every rounding decision of the plain rule compares a short number with a multiple of the tensor scale: an element
+// |x| with c s_g, c = T s_b (T a midpoint between two E2M1 magnitudes, s_b an E4M3 value), or a block maximum with
+// c s_g, c = M q (q a midpoint between two E4M3 values, M the target magnitude 6 or 4).  Up to powers of two |x| is an
+// integer below 2^8 and c is one of the odd numbers below 2^7 that tie_candidate() lists, so two different quotients
+// |x| / c differ by more than 2^-15 of their value and at most ONE of them lies near s_g.  A quotient within 2^-17 of
+// s_g is therefore always the same one for the whole tensor: all the near-ties of a tensor lie on the same side of
+// their midpoints, the side on which s_g lies of that quotient.  So instead of converting both ends of a bracket and
+// settling the codes on which they differ, the tensor scale that the quotients are formed with is moved by 2^-18 away
+// from it, once per tensor: a near-tie then lands on its own side (2^-18 is eight times what the fp32 evaluation can
+// be off by), anything else is further than 2^-17 from a midpoint and does not cross it.  Where s_g equals the
+// quotient exactly (an eighth of the bf16 maxima) the near-ties are ties, and the quotients are rounded to 17
+// significant bits, which puts them exactly on the midpoint; the conversions then round to the even code.
+// Bound by VALU issue: about 75 instruction slots per block against 190 for the bracket (16 unpack, 8 maximum, about
+// 10 scale, 16 multiplies, 8 conversions of up to three slots), and no data-dependent loop.
+struct TensorScale {
+    float sg;          // the tensor scale, shifted into the fp32-safe range
+    float nudged;      // sg (1 -+ 2^-18), what quotients are formed with
+    float inv6;        // 1 / (6 nudged)
+    float shift;       // range_shift of the tensor scale: the tensor is multiplied by it before it is encoded
+    bool snap;         // sg is a tie itself: round the quotients to 17 bits
+};
+
+// the odd parts of all c: {1,3,5,7} x {1..15} (elements; subnormal block scales' midpoints; 4-bit scale midpoints
+// with M = 6), 3 x {17..31} and {17..31} (block scales with M = 6 and M = 4)
+__device__ __forceinline__ uint32_t tie_candidate(uint32_t lane)
+{
+    if (lane < 32u) return (2u * (lane & 3u) + 1u) * (2u * (lane >> 2) + 1u);
+    return (lane < 40u ? 3u : 1u) * (17u + 2u * (lane & 7u));
+}
+
+// Every lane of the wave calls this (lane l tests candidate l); the result is the same for all of them.
+__device__ __forceinline__ TensorScale tensor_scale(float sg_given)
+{
+    TensorScale t;
+    const float g = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sg_given)));
+    t.shift = g < 0x1p-100f ? 0x1p96f : (g > 0x1p100f ? 0x1p-96f : 1.0f);
+    t.sg = g * t.shift;
+    const float c = (float)tie_candidate(threadIdx.x & 63u), m = c * t.sg;
+    const float x = bf16lo_to_f32(pack_bf16x2(m, 0.0f));                   // the nearest 8-bit number
+    const float d = __builtin_fmaf(c, t.sg, -x);                           // exact where it is small
+    const bool near = fabsf(d) <= 0x1p-17f * m;
+    const bool below = __ballot(near & (d > 0.0f)) != 0ull;                // quotients lie below their midpoints
+    const bool above = __ballot(near & (d < 0.0f)) != 0ull;
+    t.snap = __ballot(near & (d == 0.0f)) != 0ull;
+    const float f = below ? 1.0f + 0x1p-18f : (above ? 1.0f - 0x1p-18f : 1.0f);
+    t.nudged = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(t.sg * f)));
+    t.inv6 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(1.0f / (6.0f * t.nudged))));
+    return t;
+}
+
+// nearest number of 17 significant bits (either sign; ties away from zero, which no quotient meets)
+__device__ __forceinline__ float snap17(float y) { return __uint_as_float((__float_as_uint(y) + 0x40u) & 0xFFFFFF80u); }
+
+// E4M3 byte nearest to q >= 0 (ties to even, gradual underflow, at most 448) and its value, by the hardware conversions:
+// the same as e4m3_rne_from_f32 for every float from 0 to 512
+__device__ __forceinline__ uint32_t e4m3_byte(float q)
+{
+    const float s = fminf(q, kFp8Max);
+    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(s, s, 0, false) & 0xFFu;
+}
+__device__ __forceinline__ float e4m3_value(uint32_t b) { return __builtin_amdgcn_cvt_f32_fp8((int)b, 0); }
+
+// scale byte of a block from its largest magnitude (target 6), and the factor that turns its elements into quotients
+__device__ __forceinline__ void block_scale(float bmax, const TensorScale &t, uint32_t &sbyte, float &inv)
+{
+    float q = bmax * t.inv6;
+    if (t.snap) q = snap17(q);
+    sbyte = e4m3_byte(q);
+    const float r = __builtin_amdgcn_rcpf(e4m3_value(sbyte) * t.nudged);
+    inv = sbyte == 0u ? 0.0f : r;
+}
+
+// sixteen values -> sixteen codes, N blocks side by side (a conversion writes one byte of its destination, so the four
+// that fill a code word wait on one another: a second block hides that)
+template <bool SNAP, int N>
+__device__ __forceinline__ void convert_codes(const float (&f)[N][16], const float (&inv)[N], uint32_t (&c)[N][2])
+{
+    auto q = [&](int n, int i) {
+        const float y = f[n][i] * inv[n];
+        return SNAP ? snap17(y) : y;
+    };
+#pragma unroll
+    for (int n = 0; n < N; ++n) c[n][0] = c[n][1] = 0u;
+#define NVFP4_STEP(SEL)                                                                                              \
+    _Pragma("unroll") for (int h = 0; h < 2; ++h) _Pragma("unroll") for (int n = 0; n < N; ++n)                     \
+        c[n][h] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c[n][h], q(n, 8 * h + 2 * SEL), q(n, 8 * h + 2 * SEL + 1), 1.0f, SEL);
+    NVFP4_STEP(0) NVFP4_STEP(1) NVFP4_STEP(2) NVFP4_STEP(3)
+#undef NVFP4_STEP
+}
+template <int N>
+__device__ __forceinline__ void encode_values(const float (&f)[N][16], const float (&inv)[N], bool snap, uint32_t (&c)[N][2])
+{
+    if (__builtin_expect(snap, 0)) convert_codes<true, N>(f, inv, c);      // (the same for every lane)
+    else convert_codes<false, N>(f, inv, c);
+}
+
+// Plain rule (Eq. 1: block maximum -> 6) on one block of eight packed pairs, already inside the fp32-safe range
+__device__ __forceinline__ void quantize_block16(const uint32_t (&w)[8], const TensorScale &t, uint32_t &sbyte, uint32_t &c0, uint32_t &c1)
+{
+    float f[1][16], inv[1];
+    uint32_t c[1][2];
+    unpack16(w, f[0]);
+    block_scale(absmax16_tree(f[0]), t, sbyte, inv[0]);
+    encode_values<1>(f, inv, t.snap, c);
+    c0 = c[0][0];
+    c1 = c[0][1];
+}
+// ... and on two blocks side by side
+__device__ __forceinline__ void quantize_pair16(const uint32_t (&wa)[8], const uint32_t (&wb)[8], const TensorScale &t,
+                                                uint32_t &sa, uint32_t &a0, uint32_t &a1, uint32_t &sb, uint32_t &b0, uint32_t &b1)
+{
+    float f[2][16], inv[2];
+    uint32_t c[2][2];
+    unpack16(wa, f[0]);
+    unpack16(wb, f[1]);
+    block_scale(absmax16_tree(f[0]), t, sa, inv[0]);
+    block_scale(absmax16_tree(f[1]), t, sb, inv[1]);
+    encode_values<2>(f, inv, t.snap, c);
+    a0 = c[0][0]; a1 = c[0][1];
+    b0 = c[1][0]; b1 = c[1][1];
+}
+
+// ---- straight-line forms for kernels that hold many blocks per lane -------------------------------
+// The functions above take one block from start to end.  The forms below run two independent chains of
+// work through one stretch of code -- two blocks for the plain rule, the two candidates of one block for
+// the scale search -- so that the latency of one chain's dependent instructions (a conversion writes one
+// byte of its destination, so the four that fill a code word wait on one another) hides behind the other.
+// The results are the exact ones: the common case is decided by fp32 arithmetic alone, and the rare
+// near-tie drops into the same exact resolution the functions above use.
+
+// Block scale byte for quotient q = bmax * inv_msg in the normal E4M3 range, by integer arithmetic on
+// the bits of q.  "unsure" is raised when q lies within 24 ulps of a rounding tie (the true quotient lies
+// within 16 ulps of q), below the normal range (subnormal scales, zero blocks), or is not an ordinary
+// number; the caller then calls block_scale_exact.
+__device__ __forceinline__ uint32_t block_scale_fast(float q, bool &unsure)
+{
+    q = fminf(q, kFp8Max);
+    const uint32_t u = __float_as_uint(q);
+    const uint32_t b = ((u + 0x7FFFFu + ((u >> 20) & 1u)) >> 20) - 960u;
+    unsure = ((u & 0xFFFFFu) - (0x80000u - 24u) <= 48u) | !(q >= 0.015625f * 1.0001f);
+    return b;
+}
+
+// E4M3 byte (normal range, as block_scale_fast returns it) -> f32, one instruction
+__device__ __forceinline__ float e4m3_normal_to_f32(uint32_t b) { return __uint_as_float((b << 20) + (120u << 23)); }
+
 // Scale byte, its value and the reciprocal of s_b s_g for one block (target magnitude M = 6 or 4).
 __device__ __forceinline__ void block_scale_inline(float bmax, float sg, float inv_msg, double target, uint32_t &sbyte,
                                                    float &sb, float &inv)
@@ -354,37 +477,6 @@ __device__ __forceinline__ void block_scale_inline(float bmax, float sg, float i
         sb = e4m3_to_f32(sbyte);
         inv = (sb == 0.0f) ? 0.0f : __builtin_amdgcn_rcpf(sb * sg);
     }
-}
-
-// one step of four conversions: pair K of the block(s) into byte K % 4 of code word K / 4, for four chains
-#define NVFP4_CVT4(K, SEL, A, FA, MA, B, FB, MB, C, FC, MC, D, FD, MD)                                              \
-    A[K >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(A[K >> 2], FA[2 * K] * MA, FA[2 * K + 1] * MA, 1.0f, SEL);  \
-    B[K >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(B[K >> 2], FB[2 * K] * MB, FB[2 * K + 1] * MB, 1.0f, SEL);  \
-    C[K >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(C[K >> 2], FC[2 * K] * MC, FC[2 * K + 1] * MC, 1.0f, SEL);  \
-    D[K >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(D[K >> 2], FD[2 * K] * MD, FD[2 * K + 1] * MD, 1.0f, SEL);
-
-// Plain rule (Eq. 1: block maximum -> 6) on two blocks side by side; the results of quantize_block16_exact
-// for tensor scales inside the fp32-safe range.
-__device__ __forceinline__ void quantize_pair16(const uint32_t (&wa)[8], const uint32_t (&wb)[8], float sg, float inv_6sg,
-                                                uint32_t &sa, uint32_t &a0, uint32_t &a1,
-                                                uint32_t &sb, uint32_t &b0, uint32_t &b1)
-{
-    float fa[16], fb[16];
-    unpack16(wa, fa);
-    unpack16(wb, fb);
-    float sva, svb, inva, invb;
-    block_scale_inline(absmax16_tree(fa), sg, inv_6sg, 6.0, sa, sva, inva);
-    block_scale_inline(absmax16_tree(fb), sg, inv_6sg, 6.0, sb, svb, invb);
-    const float ila = inva * kBracketLo, iha = inva * kBracketHi, ilb = invb * kBracketLo, ihb = invb * kBracketHi;
-    uint32_t la[2] = {0, 0}, ha[2] = {0, 0}, lb[2] = {0, 0}, hb[2] = {0, 0};
-#define NVFP4_STEP(K, SEL) NVFP4_CVT4(K, SEL, la, fa, ila, ha, fa, iha, lb, fb, ilb, hb, fb, ihb)
-    NVFP4_STEP(0, 0) NVFP4_STEP(1, 1) NVFP4_STEP(2, 2) NVFP4_STEP(3, 3)
-    NVFP4_STEP(4, 0) NVFP4_STEP(5, 1) NVFP4_STEP(6, 2) NVFP4_STEP(7, 3)
-#undef NVFP4_STEP
-    resolve_codes(wa, sva, sg, la[0], la[1], ha[0], ha[1]);
-    resolve_codes(wb, svb, sg, lb[0], lb[1], hb[0], hb[1]);
-    a0 = la[0]; a1 = la[1];
-    b0 = lb[0]; b1 = lb[1];
 }
 
 // Scale search (Eq. 12-13) on one block, the two candidates side by side; the results of
@@ -462,17 +554,8 @@ __device__ __forceinline__ void quantize_block16_4over6_inline(const uint32_t (&
     upper_end(pick4 ? ih4 : ih6, hw);
     resolve_codes(w, pick4 ? sb4 : sb6, sg, c0, c1, hw[0], hw[1]);   // (settled codes pass through unchanged)
 }
-#undef NVFP4_CVT4
 
 // the one-block-at-a-time counterparts, for any tensor scale (sgq, inv_6sgq, inv_4sgq: the scale after range_shift)
-__device__ __forceinline__ void quantize_block16_exact(uint32_t (&w)[8], float shift, float sgq, float inv_6sgq, uint32_t &sbyte,
-                                                       uint32_t &c0, uint32_t &c1)
-{
-    if (__builtin_expect(shift != 1.0f, 0)) rescale_block16(w, shift);
-    sbyte = block_scale_exact(block_absmax_f32(w), sgq, inv_6sgq);
-    encode_block16(w, e4m3_to_f32(sbyte), sgq, c0, c1);
-}
-
 __device__ __forceinline__ void quantize_block16_4over6_exact(uint32_t (&w)[8], float shift, float sgq, float inv_6sgq,
                                                               float inv_4sgq, uint32_t &sbyte, uint32_t &c0, uint32_t &c1)
 {

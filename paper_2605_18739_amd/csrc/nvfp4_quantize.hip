@@ -204,9 +204,9 @@ void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
     if constexpr (!SEARCH) fetch(first);
     const float sg = resolve_global_scale(gs_in, partial, n_partial, gs_out, lds4);
     if constexpr (SEARCH) fetch(first);
-    const float shift = range_shift(sg), sgq = sg * shift;      // (1 and s_g unless the tensor scale is out of the fp32-safe range)
-    const float inv_6sg = 1.0f / (6.0f * sgq);
-    const float inv_4sg = 1.0f / (4.0f * sgq);
+    const TensorScale ts = tensor_scale(sg);
+    const float inv_6sg = 1.0f / (6.0f * ts.sg);
+    const float inv_4sg = 1.0f / (4.0f * ts.sg);
     for (int64_t g0 = first; g0 < nblk; g0 += stride * U) {
         if (g0 != first) fetch(g0);
 #pragma unroll
@@ -216,22 +216,15 @@ void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
                 uint32_t w[8] = {v0[u].x, v0[u].y, v0[u].z, v0[u].w, v1[u].x, v1[u].y, v1[u].z, v1[u].w};
                 // SMOOTH: C / 16 = 1 << row_shift blocks per row
                 if constexpr (SMOOTH) smooth_block16(w, __uint_as_float((uint32_t)row_mean[g >> row_shift] << 16));
-                if (__builtin_expect(shift != 1.0f, 0)) rescale_block16(w, shift);
+                if (__builtin_expect(ts.shift != 1.0f, 0)) rescale_block16(w, ts.shift);
                 uint32_t sbyte, c0, c1;
-                if (SEARCH && __builtin_expect(shift == 1.0f, 1)) {
+                if constexpr (!SEARCH) {
+                    quantize_block16(w, ts, sbyte, c0, c1);
+                } else if (__builtin_expect(ts.shift == 1.0f, 1)) {
                     // the straight-line form: the candidates compared on one bracket end, the winner settled
-                    quantize_block16_4over6_inline(w, sgq, inv_6sg, inv_4sg, sbyte, c0, c1);
+                    quantize_block16_4over6_inline(w, ts.sg, inv_6sg, inv_4sg, sbyte, c0, c1);
                 } else {
-                    uint32_t acc = 0;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) acc = pk_absmax_u16(acc, w[i]);
-                    const float bmax = __uint_as_float(pk_hmax_u16(acc) << 16);
-                    if constexpr (SEARCH) {
-                        encode_block16_4over6(w, bmax, sgq, inv_6sg, inv_4sg, sbyte, c0, c1);
-                    } else {
-                        sbyte = block_scale_exact(bmax, sgq, inv_6sg);
-                        encode_block16(w, e4m3_to_f32(sbyte), sgq, c0, c1);
-                    }
+                    encode_block16_4over6(w, block_absmax_f32(w), ts.sg, inv_6sg, inv_4sg, sbyte, c0, c1);
                 }
                 uint2v cc = {c0, c1};
                 int64_t go = g;                       // output block index
@@ -434,25 +427,13 @@ __global__ __launch_bounds__(256, 3) void quantize_cols_kernel(const uint16_t *_
             v[i] = __builtin_nontemporal_load((const uint4v *)(x + (r + i) * ld + c));
     }
     const float sg = resolve_global_scale(gs_in, partial, n_partial, gs_out, lds4);
-    const float shift = range_shift(sg), sgq = sg * shift;      // (1 and s_g unless the tensor scale is out of the fp32-safe range)
-    const float inv_6sg = 1.0f / (6.0f * sgq);
-    auto group_max = [](const uint32_t (&w)[8]) {
-        uint32_t acc = 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc = pk_absmax_u16(acc, w[i]);
-        return __uint_as_float(pk_hmax_u16(acc) << 16);
-    };
-    // (transformed) group and its largest magnitude -> codes and scale of column c0 + col
-    auto encode_group = [&](uint32_t (&w)[8], float bmax, int col, int rbx) {
-        if (__builtin_expect(shift != 1.0f, 0)) {
-            rescale_block16(w, shift);
-            bmax = group_max(w);
-        }
-        uint32_t sbyte = block_scale_exact(bmax, sgq, inv_6sg);
-        uint32_t k0, k1;
-        encode_block16(w, e4m3_to_f32(sbyte), sgq, k0, k1);
-        uint2v cc = {k0, k1};
-        lds_codes[col][rbx] = cc;
+    const TensorScale ts = tensor_scale(sg);
+    // (transformed) group -> codes and scale of column c0 + col
+    auto encode_group = [&](uint32_t (&w)[8], int col, int rbx) {
+        if (__builtin_expect(ts.shift != 1.0f, 0)) rescale_block16(w, ts.shift);
+        uint32_t sbyte, k0, k1;
+        quantize_block16(w, ts, sbyte, k0, k1);
+        lds_codes[col][rbx] = uint2v{k0, k1};
         lds_scales[col][rbx] = (uint8_t)sbyte;
     };
     if constexpr (RHT) {
@@ -474,23 +455,22 @@ __global__ __launch_bounds__(256, 3) void quantize_cols_kernel(const uint16_t *_
             float y[16];
             rht_block16_mfma(raw, h, y);
             pack16(y, w);
-            // (rounding to bf16 is monotone: the largest of the rounded values is the rounded largest value.  A group
-            //  that is listed is encoded here all the same, and again, into the same place, after the sweep.)
-            encode_group(w, __uint_as_float(pack_bf16x2(absmax16_tree(y), 0.0f) << 16), cg * 8 + j, rb);
+            // (a group that is listed is encoded here all the same, and again, into the same place, after the sweep)
+            encode_group(w, cg * 8 + j, rb);
             if (__builtin_expect(!exact, 0))
                 if (!rht_list(list, raw, place + (uint32_t)j)) noted |= 1u << j;
         }
         rht_work_off(list, noted, place, h, sign_mask, x, r, c, ld, [&](uint32_t (&w)[8], uint32_t where) {
-            encode_group(w, group_max(w), (int)(where & 0xFFFFu), (int)(where >> 16));
+            encode_group(w, (int)(where & 0xFFFFu), (int)(where >> 16));
         });
     } else if (live) {
-        if (__builtin_expect(shift == 1.0f, 1)) {          // two columns side by side (see quantize_pair16)
+        if (__builtin_expect(ts.shift == 1.0f, 1)) {       // two columns side by side (see quantize_pair16)
 #pragma unroll
             for (int j = 0; j < 8; j += 2) {               // columns c + j, c + j + 1: elements j, j + 1 of every loaded vector
                 uint32_t wa[8], wb[8], sa, a0, a1, sb, b0, b1;
                 column_of(v, j, wa);
                 column_of(v, j + 1, wb);
-                quantize_pair16(wa, wb, sg, inv_6sg, sa, a0, a1, sb, b0, b1);
+                quantize_pair16(wa, wb, ts, sa, a0, a1, sb, b0, b1);
                 lds_codes[cg * 8 + j][rb] = uint2v{a0, a1};
                 lds_scales[cg * 8 + j][rb] = (uint8_t)sa;
                 lds_codes[cg * 8 + j + 1][rb] = uint2v{b0, b1};
@@ -501,7 +481,7 @@ __global__ __launch_bounds__(256, 3) void quantize_cols_kernel(const uint16_t *_
             for (int j = 0; j < 8; ++j) {
                 uint32_t w[8];
                 column_of(v, j, w);
-                encode_group(w, group_max(w), cg * 8 + j, rb);
+                encode_group(w, cg * 8 + j, rb);
             }
         }
     }
@@ -555,24 +535,28 @@ __global__ __launch_bounds__(256) void quantize_tiles_kernel(const uint16_t *__r
     }
     const float sg = resolve_global_scale(gs_in, partial, n_partial, gs_out, lds4);
     if (gs_out_t && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *gs_out_t = sg;
-    const float shift = range_shift(sg), sgq = sg * shift;      // (1 and s_g unless the tensor scale is out of the fp32-safe range)
-    const float inv_6sg = 1.0f / (6.0f * sgq);
+    const TensorScale ts = tensor_scale(sg);
     if (!live) return;
-    if (__builtin_expect(shift != 1.0f, 0)) {
+    if (__builtin_expect(ts.shift != 1.0f, 0)) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) rescale_block16(w[i], shift);
+        for (int i = 0; i < 16; ++i) rescale_block16(w[i], ts.shift);
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i)
 #pragma unroll
         for (int k = 0; k < 8; ++k) acc = pk_absmax_u16(acc, w[i][k]);
-    const float bmax = __uint_as_float(pk_hmax_u16(acc) << 16);
-    const uint32_t sbyte = block_scale_exact(bmax, sgq, inv_6sg);
-    const float sb = e4m3_to_f32(sbyte);
+    uint32_t sbyte;
+    float inv[1];
+    block_scale(__uint_as_float(pk_hmax_u16(acc) << 16), ts, sbyte, inv[0]);
     uint32_t c0[16], c1[16];                       // row i of the tile: codes of columns 0-7, 8-15
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        encode_block16(w[i], sb, sgq, c0[i], c1[i]);
+        float f[1][16];
+        uint32_t c[1][2];
+        unpack16(w[i], f[0]);
+        encode_values<1>(f, inv, ts.snap, c);
+        c0[i] = c[0][0];
+        c1[i] = c[0][1];
         const int64_t row = 16 * I + i;
         *(uint2v *)(codes + row * (C >> 1) + 8 * J) = uint2v{c0[i], c1[i]};
         scales[row * tc + J] = (uint8_t)sbyte;

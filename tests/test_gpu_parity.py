@@ -84,6 +84,31 @@ def test_quantize_given_scale_and_stride(oracle):
         assert_q_equal(nv.nvfp4_quantize(view, global_scale_in=gsd), oq, f"given scale {gs}")
 
 
+@pytest.mark.parametrize("offset", [0.0, 2.0 ** -23, -2.0 ** -23, 2.0 ** -19, -2.0 ** -19, -2.0 ** -17, 2.0 ** -16])
+def test_quantize_tensor_scales_on_and_beside_ties(oracle, offset):
+    """Given scales (bf16 number) / (odd number below 128), and the same a little off: elements and block maxima of
+    bf16 numbers next to the midpoints, through the row, column, tile and scale-search encoders."""
+    g = np.random.default_rng(97)
+    T = np.array([0.25, 0.75, 1.25, 1.75, 2.5, 3.5, 5.0])
+    for c in (1, 3, 5, 7, 21, 35, 49, 91, 105, 51, 93, 17, 31):
+        gs = np.float32(float(g.integers(128, 256)) / c * (1.0 + offset) * 2.0 ** -9)
+        say(f"[near ties] scale {gs!r}")
+        sb = wl.bf16_bits_to_f32(wl.to_bf16_bits(g.integers(8, 16, (128, 16)) * 2.0 ** g.integers(-13, 4, (128, 16)).astype(np.float32)))
+        x = T[g.integers(0, 7, (128, 16, 16))] * sb[:, :, None] * gs * g.choice([-1.0, 1.0], (128, 16, 16))
+        top = np.where(g.random((128, 16)) < 0.5, 6.0, 6.0 * (1.0 + 1.0 / 16))          # maxima on a block scale / on a midpoint
+        x[:, :, 3] = top * sb * gs
+        xb = wl.to_bf16_bits(x.reshape(128, 256).astype(np.float32))
+        gsd = torch.tensor([gs], dtype=torch.float32, device="cuda")
+        xd = dev_bf16(xb)
+        assert_q_equal(nv.nvfp4_quantize(xd, global_scale_in=gsd), oracle.quantize(xb, global_scale_in=gs), f"rows {gs!r}")
+        assert_q_equal(nv.nvfp4_quantize_4over6(xd, global_scale_in=gsd), oracle.quantize(xb, global_scale_in=gs, four_over_six=True), f"search {gs!r}")
+        xt = np.ascontiguousarray(xb.T)
+        assert_q_equal(nv.nvfp4_quantize(dev_bf16(xt), block_axis=1, global_scale_in=gsd), oracle.quantize(xt, block_axis=1, global_scale_in=gs), f"columns {gs!r}")
+        got, want = nv.nvfp4_quantize_2d(xd, global_scale_in=gsd), oracle.quantize_2d(xb, global_scale_in=gs)
+        assert_q_equal(got[0], want[0], f"tiles {gs!r}")
+        assert_q_equal(got[1], want[1], f"tiles transposed {gs!r}")
+
+
 @pytest.mark.parametrize("R,C", [(16, 8), (48, 24), (128, 256), (400, 520), (1024, 3072)])
 def test_quantize_transposed(oracle, R, C):
     g = np.random.default_rng(R + C)

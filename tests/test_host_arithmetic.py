@@ -187,3 +187,57 @@ def test_near_tie_difference_is_an_exact_fp32_number():
                     checked += 1
                     zero += d == 0
     assert checked > 10_000 and 0 < zero < checked // 4                        # exact ties occur, most cases are not
+
+
+def _tie_candidates():
+    """Odd parts of (midpoint between two codes) x (4-bit block scale) and of M x (midpoint between two block scales)."""
+    c = [(2 * (l & 3) + 1) * (2 * (l >> 2) + 1) for l in range(32)]
+    return sorted(set(c + [3 * (17 + 2 * l) for l in range(8)] + [17 + 2 * l for l in range(8)]))
+
+
+def test_one_nudge_of_the_tensor_scale_settles_every_near_tie():
+    """The quantizer forms its quotients with a tensor scale that is moved by 2^-18 away from the one quotient
+    (bf16 number) / (odd candidate) that can lie within 2^-17 of it, and rounds them to 17 bits where it IS that quotient.
+    For tensor scales on, beside and around every such quotient: every element and block maximum next to a midpoint
+    ends on the side the exact comparison says (on the midpoint for ties), whatever the last bit of the reciprocal."""
+    f32, cand = np.float32, np.array(_tie_candidates(), np.float64)
+    x0 = np.arange(128, 256, dtype=np.float64)
+    base = (x0[:, None] / cand[None, :]).ravel()
+    base = base / 2.0 ** np.floor(np.log2(base))                       # significands in [1, 2)
+    sg = np.concatenate([(base * (1.0 + o)).astype(f32) for o in
+                         (0.0, 2.0 ** -23, -2.0 ** -23, 2.0 ** -20, -2.0 ** -19, 2.0 ** -17 * 0.99, -2.0 ** -17 * 1.01, 2.0 ** -16, -2.0 ** -15)])
+    sg = np.unique(sg)
+    # the nudge, as the kernels take it: fp32 products, the nearest bf16 number, one fused difference (exact here)
+    m = (cand[None, :].astype(f32) * sg[:, None]).astype(f32)
+    near_x = _bf16_to_f32(_rne_f32_to_bf16(m.ravel())).reshape(m.shape).astype(np.float64)
+    d = cand[None, :] * sg[:, None].astype(np.float64) - near_x
+    near = np.abs(d) <= 2.0 ** -17 * m
+    below, above, tie = (near & (d > 0)).any(1), (near & (d < 0)).any(1), (near & (d == 0)).any(1)
+    assert (below.astype(int) + above + tie <= 1).all() and below.any() and above.any() and tie.any()
+    nudged = (sg * np.where(below, f32(1 + 2.0 ** -18), np.where(above, f32(1 - 2.0 ** -18), f32(1)))).astype(f32)
+
+    def snap17(y):
+        return ((y.view(np.uint32) + np.uint32(0x40)) & np.uint32(0xFFFFFF80)).view(np.float32)
+
+    checked = 0
+    # (factor of the scale in the divisor, midpoint that the quotient is compared with)
+    pairs = [(f32(s / 8.0), f32(t)) for s in range(8, 16) for t in (1.0, 1.25, 1.5, 1.75)]          # codes: 1,3,5,7 x 2^k
+    pairs += [(f32(mt), f32((2 * q + 1) / 16.0)) for mt in (4.0, 6.0) for q in range(8, 16)]        # block scales
+    pairs += [(f32(6.0), f32(o)) for o in (1, 3, 5, 7, 9, 11, 13, 15)]                              # subnormal block scales
+    for s, t in pairs:
+        c = float(s) * float(t)
+        target = c * sg.astype(np.float64)                                                          # exact
+        e = np.floor(np.log2(target))
+        sig = np.floor(target / 2.0 ** (e - 7))
+        for step in (-1, 0, 1, 2):                                                                  # bf16 neighbours of the midpoint
+            x = (sig + step) * 2.0 ** (e - 7)
+            exact = np.sign(x - target)
+            for ulp in (-1, 0, 1):                                                                  # reciprocal off by one ulp
+                den = (s * nudged).astype(f32)
+                rcp = (f32(1.0) / den).astype(f32)
+                rcp = (rcp.view(np.int32) + ulp).view(f32)
+                y = (x.astype(f32) * rcp).astype(f32)
+                y = np.where(tie, snap17(y), y)
+                assert (np.sign(y.astype(np.float64) - float(t)) == exact).all(), (s, t, step, ulp)
+                checked += y.size
+    assert checked > 5_000_000
