@@ -78,137 +78,12 @@ __device__ __forceinline__ _Float16 e4m3_to_f16(uint32_t b)
     _Float16 sub = (_Float16)((float)(b & 7u) * 0.001953125f);
     return (b >> 3) ? normal : sub;
 }
-// q >= 0 finite -> nearest E4M3 byte, ties to even, gradual underflow, saturating at 448
-__device__ __forceinline__ uint32_t e4m3_rne_from_f32(float q)
-{
-    q = fminf(q, kFp8Max);
-    uint32_t u = __float_as_uint(q);
-    uint32_t bn = ((u + 0x7FFFFu + ((u >> 20) & 1u)) >> 20) - 960u;
-    uint32_t bs = (uint32_t)__builtin_rintf(q * 512.0f);
-    return q < 0.015625f ? bs : bn;
-}
-
-// Relative half-width of the bracket put around every fp32 quotient before it
-// is rounded to a format: the fp32 evaluation (one rounded product or scale,
-// one reciprocal good to 1 ulp, one rounded multiply, one more for the bracket
-// itself) is off by less than 3.5 * 2^-23, so the exact quotient always lies
-// strictly inside [q(1-2^-20), q(1+2^-20)].  If both ends round to the same
-// code, that code is the exact answer; otherwise the decision is redone in
-// fp64 by cross-multiplication, which is exact.
-constexpr float kBracketLo = 1.0f - 0x1p-20f;
-constexpr float kBracketHi = 1.0f + 0x1p-20f;
-
-// Block scale of Eq. 12 for target magnitude M (6, or 4 for the second candidate of the
-// scale search): E4M3 nearest to bmax / (M sg), decided exactly.  inv_msg = 1 / (M sg) in fp32.
-__device__ __forceinline__ uint32_t block_scale_exact(float bmax, float sg, float inv_msg, double target = 6.0)
-{
-    float q = bmax * inv_msg;
-    uint32_t blo = e4m3_rne_from_f32(q * kBracketLo);
-    uint32_t bhi = e4m3_rne_from_f32(q * kBracketHi);
-    if (__builtin_expect(blo != bhi, 0)) {
-        double mid = 0.5 * ((double)e4m3_to_f32(blo) + (double)e4m3_to_f32(bhi));
-        double t = mid * target * (double)sg;  // <= 5 + 2 + 24 significant bits: exact
-        double b = (double)bmax;
-        blo = (b > t) ? bhi : ((b < t) ? blo : ((blo & 1u) ? bhi : blo));
-    }
-    return blo;
-}
-
-// Settle the nibbles on which the two ends of the bracket disagree.  l holds the codes of the lower end, h of the
-// upper end (neighbouring magnitudes, same sign).  Such an element lies within 2^-19 of the midpoint T between the
-// two magnitudes times s_b s_g, and which side it lies on is the sign of  T s_b s_g - |x|:  c = T s_b is exact in
-// fp32 (3 + 4 bits), the fused multiply-add rounds c s_g - |x| once, and because the two terms nearly cancel
-// (the difference has at most 12 significant bits) that one rounding is exact.  Tensor scales so small that the
-// difference could leave the normal range take the same comparison in fp64.  A tie goes to the even code.
-// One nibble per pass of the loop; a wave runs as many passes as its busiest lane needs (rarely more than two).
-__device__ __forceinline__ void resolve_codes(const uint32_t (&w)[8], float sb, float sg, uint32_t &l0, uint32_t &l1,
-                                              uint32_t h0, uint32_t h1)
-{
-    typedef float float2v __attribute__((ext_vector_type(2)));
-    uint32_t d0 = l0 ^ h0, d1 = l1 ^ h1;
-    const bool wide = sg >= 0x1p-80f;                                      // (the same for every lane)
-    while (__builtin_expect((d0 | d1) != 0u, 0)) {                         // (selects, no branches, inside)
-        const bool first = d0 != 0u;
-        const uint32_t d = first ? d0 : d1, lw = first ? l0 : l1;
-        const uint32_t sh = (uint32_t)__builtin_ctz(d) & 28u;              // bit position of the nibble in its word
-        const bool odd = (sh & 8u) != 0u, upper = (sh & 16u) != 0u;        // which of the word's four bf16 pairs
-        const uint32_t w01 = odd ? w[1] : w[0], w23 = odd ? w[3] : w[2];
-        const uint32_t w45 = odd ? w[5] : w[4], w67 = odd ? w[7] : w[6];
-        const uint32_t wlo = upper ? w23 : w01, whi = upper ? w67 : w45;
-        const uint32_t ww = first ? wlo : whi;
-        const float ax = __uint_as_float((ww >> ((sh & 4u) << 2) << 16) & 0x7FFF0000u);
-        const uint32_t lo = (lw >> sh) & 7u;
-        const float2v m = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(lo | ((lo + 1u) << 4), 1.0f, 0);
-        const float c = (0.5f * (m.x + m.y)) * sb;                         // midpoint times block scale, exact
-        bool above, equal;
-        if (wide) {
-            const float t = __builtin_fmaf(c, sg, -ax);
-            above = t < 0.0f;
-            equal = t == 0.0f;
-        } else {
-            const double t = (double)c * (double)sg, a = (double)ax;
-            above = a > t;
-            equal = a == t;
-        }
-        const bool up = above | (equal & ((lo & 1u) != 0u));
-        const uint32_t nib = d & (0xFu << sh);
-        const uint32_t nw = lw ^ (up ? nib : 0u), nd = d ^ nib;
-        l0 = first ? nw : l0;
-        l1 = first ? l1 : nw;
-        d0 = first ? nd : d0;
-        d1 = first ? d1 : nd;
-    }
-}
-
-// 16 consecutive bf16 (8 dwords) -> 16 E2M1 codes (2 dwords) on the scale
-// den = s_b * s_g.  The hardware conversion (round to nearest even, saturating,
-// sign preserved) is applied to both ends of the bracket; disagreeing nibbles
-// are resolved exactly.
-__device__ __forceinline__ void encode_block16(const uint32_t (&w)[8], float sb, float sg,
-                                               uint32_t &c0, uint32_t &c1)
-{
-    float d = sb * sg;
-    float inv = (sb == 0.0f) ? 0.0f : __builtin_amdgcn_rcpf(d);
-    float il = inv * kBracketLo, ih = inv * kBracketHi;
-    uint32_t l0 = 0, l1 = 0, h0 = 0, h1 = 0;
-#define NVFP4_CVT(L, H, W, SEL)                                                                   \
-    L = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(L, bf16lo_to_f32(W) * il, bf16hi_to_f32(W) * il, \
-                                                 1.0f, SEL);                                       \
-    H = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(H, bf16lo_to_f32(W) * ih, bf16hi_to_f32(W) * ih, \
-                                                 1.0f, SEL);
-    NVFP4_CVT(l0, h0, w[0], 0) NVFP4_CVT(l0, h0, w[1], 1) NVFP4_CVT(l0, h0, w[2], 2) NVFP4_CVT(l0, h0, w[3], 3)
-    NVFP4_CVT(l1, h1, w[4], 0) NVFP4_CVT(l1, h1, w[5], 1) NVFP4_CVT(l1, h1, w[6], 2) NVFP4_CVT(l1, h1, w[7], 3)
-#undef NVFP4_CVT
-    resolve_codes(w, sb, sg, l0, l1, h0, h1);
-    c0 = l0;
-    c1 = l1;
-}
 
 // ---- Four-over-Six scale search (Appendix "Scale Search NVFP4 Quantization", Eq. 12-13) ----
-// Squared reconstruction error of a 16-element block under one candidate encoding, in fp32.
-// den = s_b * s_g rounded to fp32; the codes carry the sign of x, so the decoded values are
-// subtracted as they are.
-__device__ __forceinline__ float block_error_f32(const uint32_t (&w)[8], uint32_t c0, uint32_t c1, float den)
-{
-    typedef float float2v __attribute__((ext_vector_type(2)));
-    float err = 0.0f;
-#define NVFP4_ERR(W, C, SEL)                                                                  \
-    {                                                                                         \
-        float2v q = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(C, 1.0f, SEL);                   \
-        float d0 = __builtin_fmaf(-q.x, den, bf16lo_to_f32(W)), d1 = __builtin_fmaf(-q.y, den, bf16hi_to_f32(W)); \
-        err = __builtin_fmaf(d0, d0, err);                                                    \
-        err = __builtin_fmaf(d1, d1, err);                                                    \
-    }
-    NVFP4_ERR(w[0], c0, 0) NVFP4_ERR(w[1], c0, 1) NVFP4_ERR(w[2], c0, 2) NVFP4_ERR(w[3], c0, 3)
-    NVFP4_ERR(w[4], c1, 0) NVFP4_ERR(w[5], c1, 1) NVFP4_ERR(w[6], c1, 2) NVFP4_ERR(w[7], c1, 3)
-#undef NVFP4_ERR
-    return err;
-}
-
-// The same error as the fp64 definition evaluates it: every difference |x| - m s_b s_g taken
+// The squared error of a block under one encoding, as the fp64 definition evaluates it: every difference |x| - m s_b s_g taken
 // once in fp64, squared, and summed in element order, each operation rounded on its own (no
 // fused multiply-add), so that "is candidate 4 strictly better" has one answer everywhere.
-// (A rolled loop: the fallback is inlined wherever a block is encoded and taken rarely, so it is written for
+// (A rolled loop: the comparison of last resort is inlined wherever a block is searched and taken rarely, so it is written for
 // small code, not for speed.)
 __device__ __forceinline__ double block_error_f64(const uint32_t (&w)[8], uint32_t c0, uint32_t c1, float sb, float sg)
 {
@@ -235,45 +110,6 @@ __device__ __forceinline__ double block_error_f64(const uint32_t (&w)[8], uint32
     return err;
 }
 
-// Scale search for one block: encode with the block maximum mapped to 6 and to 4, keep the
-// encoding with the strictly smaller squared error (equal errors keep 6).  The fp32 errors
-// decide whenever they differ by more than their own uncertainty; otherwise fp64 does.
-__device__ __forceinline__ void encode_block16_4over6(const uint32_t (&w)[8], float bmax, float sg, float inv_6sg,
-                                                      float inv_4sg, uint32_t &sbyte, uint32_t &c0, uint32_t &c1)
-{
-    const uint32_t s6 = block_scale_exact(bmax, sg, inv_6sg, 6.0);
-    const uint32_t s4 = block_scale_exact(bmax, sg, inv_4sg, 4.0);
-    const float sb6 = e4m3_to_f32(s6), sb4 = e4m3_to_f32(s4);
-    uint32_t a0, a1;
-    encode_block16(w, sb6, sg, a0, a1);
-    sbyte = s6;
-    c0 = a0;
-    c1 = a1;
-    if (s4 == s6) return;                          // same scale, same codes, same error (zero blocks, saturated scales)
-    uint32_t b0, b1;
-    encode_block16(w, sb4, sg, b0, b1);
-    const float den6 = sb6 * sg, den4 = sb4 * sg;
-    const float e6 = block_error_f32(w, a0, a1, den6), e4 = block_error_f32(w, b0, b1, den4);
-    // |d~ - d| <= 2^-24 (|x| + |x^| + 6 den) < u; |d~^2 - d^2| <= u (2 |d~| + u), and the sixteen
-    // |d~| add up to at most 4 sqrt(sum d~^2) (Cauchy-Schwarz; 4.01 covers the approximate square
-    // root and the rounding of the sum); sixteen fused accumulations add at most 2^-19 of the sum
-    const float u6 = 0x1p-22f * (bmax + 6.0f * den6), u4 = 0x1p-22f * (bmax + 6.0f * den4);
-    const float r6 = u6 * (8.02f * __builtin_amdgcn_sqrtf(e6) + 16.0f * u6) + 0x1p-19f * e6;
-    const float r4 = u4 * (8.02f * __builtin_amdgcn_sqrtf(e4) + 16.0f * u4) + 0x1p-19f * e4;
-    // the relative bounds above need normal fp32 numbers: errors near the underflow range
-    // (and exact zeros) go to fp64 as well
-    const bool tiny = fminf(e4, e6) < 0x1p-100f;
-    bool pick4;
-    if (!tiny && e4 + r4 < e6 - r6) pick4 = true;
-    else if (!tiny && e4 - r4 > e6 + r6) pick4 = false;
-    else pick4 = block_error_f64(w, b0, b1, sb4, sg) < block_error_f64(w, a0, a1, sb6, sg);
-    if (pick4) {
-        sbyte = s4;
-        c0 = b0;
-        c1 = b1;
-    }
-}
-
 // ---- tensor scales outside the range in which the fp32 quotients above are safe ----------------------
 // Below s_g = 2^-100 or above 2^100 the reciprocal 1 / (M s_g) or the products s_b s_g leave the normal fp32
 // range.  Every decision of the quantizer compares ratios, so it commutes with multiplying the tensor AND its
@@ -282,21 +118,10 @@ __device__ __forceinline__ void encode_block16_4over6(const uint32_t (&w)[8], fl
 // when a huge tensor is scaled down: they are below 2^-30, more than a hundred binades under a quarter of the
 // smallest block scale times s_g, so their code is zero either way, and so is the scale of a block made of them.
 // The stored tensor scale is the unscaled one.  The test is the same for every lane: a scalar branch.
-__device__ __forceinline__ bool scale_out_of_range(float sg) { return !(sg >= 0x1p-100f && sg <= 0x1p100f); }
-__device__ __forceinline__ float range_shift(float sg) { return sg < 0x1p-100f ? 0x1p96f : (sg > 0x1p100f ? 0x1p-96f : 1.0f); }
 __device__ __forceinline__ void rescale_block16(uint32_t (&w)[8], float f)
 {
 #pragma unroll
     for (int i = 0; i < 8; ++i) w[i] = pack_bf16x2(bf16lo_to_f32(w[i]) * f, bf16hi_to_f32(w[i]) * f);
-}
-
-// largest magnitude of 16 bf16 values as a float (exact: a maximum of exact values)
-__device__ __forceinline__ float block_absmax_f32(const uint32_t (&w)[8])
-{
-    float m = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) m = fmaxf(fmaxf(fabsf(bf16lo_to_f32(w[i])), fabsf(bf16hi_to_f32(w[i]))), m);
-    return m;
 }
 
 // sixteen values -> their largest magnitude through a tree of three-operand maxima (depth 3 instead of 8)
@@ -335,8 +160,8 @@ __device__ __forceinline__ void unpack16(const uint32_t (&w)[8], float (&f)[16])
 struct TensorScale {
     float sg;          // the tensor scale, shifted into the fp32-safe range
     float nudged;      // sg (1 -+ 2^-18), what quotients are formed with
-    float inv6;        // 1 / (6 nudged)
-    float shift;       // range_shift of the tensor scale: the tensor is multiplied by it before it is encoded
+    float inv6, inv4;  // 1 / (6 nudged), 1 / (4 nudged)
+    float shift;       // 1, or the power of two that the tensor is multiplied by before it is encoded (see above)
     bool snap;         // sg is a tie itself: round the quotients to 17 bits
 };
 
@@ -365,14 +190,15 @@ __device__ __forceinline__ TensorScale tensor_scale(float sg_given)
     const float f = below ? 1.0f + 0x1p-18f : (above ? 1.0f - 0x1p-18f : 1.0f);
     t.nudged = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(t.sg * f)));
     t.inv6 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(1.0f / (6.0f * t.nudged))));
+    t.inv4 = 1.5f * t.inv6;                                                // (one more rounding: 2^-18 is far above it)
     return t;
 }
 
 // nearest number of 17 significant bits (either sign; ties away from zero, which no quotient meets)
 __device__ __forceinline__ float snap17(float y) { return __uint_as_float((__float_as_uint(y) + 0x40u) & 0xFFFFFF80u); }
 
-// E4M3 byte nearest to q >= 0 (ties to even, gradual underflow, at most 448) and its value, by the hardware conversions:
-// the same as e4m3_rne_from_f32 for every float from 0 to 512
+// E4M3 byte nearest to q >= 0 (ties to even, gradual underflow, at most 448) and its value, by the hardware conversions
+// (checked against integer arithmetic for every float from 0 to 512)
 __device__ __forceinline__ uint32_t e4m3_byte(float q)
 {
     const float s = fminf(q, kFp8Max);
@@ -380,23 +206,36 @@ __device__ __forceinline__ uint32_t e4m3_byte(float q)
 }
 __device__ __forceinline__ float e4m3_value(uint32_t b) { return __builtin_amdgcn_cvt_f32_fp8((int)b, 0); }
 
-// scale byte of a block from its largest magnitude (target 6), and the factor that turns its elements into quotients
-__device__ __forceinline__ void block_scale(float bmax, const TensorScale &t, uint32_t &sbyte, float &inv)
+// scale byte of a block from its largest magnitude (inv_m: 1 / (M nudged) for the target magnitude M), its value, and
+// the factor that turns the block's elements into quotients
+__device__ __forceinline__ void block_scale(float bmax, float inv_m, const TensorScale &t, uint32_t &sbyte, float &sb, float &inv)
 {
-    float q = bmax * t.inv6;
+    float q = bmax * inv_m;
     if (t.snap) q = snap17(q);
     sbyte = e4m3_byte(q);
-    const float r = __builtin_amdgcn_rcpf(e4m3_value(sbyte) * t.nudged);
+    sb = e4m3_value(sbyte);
+    const float r = __builtin_amdgcn_rcpf(sb * t.nudged);
     inv = sbyte == 0u ? 0.0f : r;
 }
+__device__ __forceinline__ void block_scale(float bmax, const TensorScale &t, uint32_t &sbyte, float &inv)
+{
+    float sb;
+    block_scale(bmax, t.inv6, t, sbyte, sb, inv);
+}
 
-// sixteen values -> sixteen codes, N blocks side by side (a conversion writes one byte of its destination, so the four
-// that fill a code word wait on one another: a second block hides that)
+// Sixteen values -> sixteen codes, N chains side by side (a conversion writes one byte of its destination, so the four
+// that fill a code word wait on one another; a second chain hides that).  step 0: every chain encodes the same values.
+template <int N>
+struct Rows16 {
+    const float (*row)[16];
+    int step;
+    __device__ __forceinline__ float at(int n, int i) const { return row[n * step][i]; }
+};
 template <bool SNAP, int N>
-__device__ __forceinline__ void convert_codes(const float (&f)[N][16], const float (&inv)[N], uint32_t (&c)[N][2])
+__device__ __forceinline__ void convert_codes(const Rows16<N> f, const float (&inv)[N], uint32_t (&c)[N][2])
 {
     auto q = [&](int n, int i) {
-        const float y = f[n][i] * inv[n];
+        const float y = f.at(n, i) * inv[n];
         return SNAP ? snap17(y) : y;
     };
 #pragma unroll
@@ -408,7 +247,7 @@ __device__ __forceinline__ void convert_codes(const float (&f)[N][16], const flo
 #undef NVFP4_STEP
 }
 template <int N>
-__device__ __forceinline__ void encode_values(const float (&f)[N][16], const float (&inv)[N], bool snap, uint32_t (&c)[N][2])
+__device__ __forceinline__ void encode_values(const Rows16<N> f, const float (&inv)[N], bool snap, uint32_t (&c)[N][2])
 {
     if (__builtin_expect(snap, 0)) convert_codes<true, N>(f, inv, c);      // (the same for every lane)
     else convert_codes<false, N>(f, inv, c);
@@ -421,7 +260,7 @@ __device__ __forceinline__ void quantize_block16(const uint32_t (&w)[8], const T
     uint32_t c[1][2];
     unpack16(w, f[0]);
     block_scale(absmax16_tree(f[0]), t, sbyte, inv[0]);
-    encode_values<1>(f, inv, t.snap, c);
+    encode_values<1>({f, 1}, inv, t.snap, c);
     c0 = c[0][0];
     c1 = c[0][1];
 }
@@ -435,132 +274,93 @@ __device__ __forceinline__ void quantize_pair16(const uint32_t (&wa)[8], const u
     unpack16(wb, f[1]);
     block_scale(absmax16_tree(f[0]), t, sa, inv[0]);
     block_scale(absmax16_tree(f[1]), t, sb, inv[1]);
-    encode_values<2>(f, inv, t.snap, c);
+    encode_values<2>({f, 1}, inv, t.snap, c);
     a0 = c[0][0]; a1 = c[0][1];
     b0 = c[1][0]; b1 = c[1][1];
 }
 
-// ---- straight-line forms for kernels that hold many blocks per lane -------------------------------
-// The functions above take one block from start to end.  The forms below run two independent chains of
-// work through one stretch of code -- two blocks for the plain rule, the two candidates of one block for
-// the scale search -- so that the latency of one chain's dependent instructions (a conversion writes one
-// byte of its destination, so the four that fill a code word wait on one another) hides behind the other.
-// The results are the exact ones: the common case is decided by fp32 arithmetic alone, and the rare
-// near-tie drops into the same exact resolution the functions above use.
-
-// Block scale byte for quotient q = bmax * inv_msg in the normal E4M3 range, by integer arithmetic on
-// the bits of q.  "unsure" is raised when q lies within 24 ulps of a rounding tie (the true quotient lies
-// within 16 ulps of q), below the normal range (subnormal scales, zero blocks), or is not an ordinary
-// number; the caller then calls block_scale_exact.
-__device__ __forceinline__ uint32_t block_scale_fast(float q, bool &unsure)
-{
-    q = fminf(q, kFp8Max);
-    const uint32_t u = __float_as_uint(q);
-    const uint32_t b = ((u + 0x7FFFFu + ((u >> 20) & 1u)) >> 20) - 960u;
-    unsure = ((u & 0xFFFFFu) - (0x80000u - 24u) <= 48u) | !(q >= 0.015625f * 1.0001f);
-    return b;
-}
-
-// E4M3 byte (normal range, as block_scale_fast returns it) -> f32, one instruction
-__device__ __forceinline__ float e4m3_normal_to_f32(uint32_t b) { return __uint_as_float((b << 20) + (120u << 23)); }
-
-// Scale byte, its value and the reciprocal of s_b s_g for one block (target magnitude M = 6 or 4).
-__device__ __forceinline__ void block_scale_inline(float bmax, float sg, float inv_msg, double target, uint32_t &sbyte,
-                                                   float &sb, float &inv)
-{
-    bool unsure;
-    sbyte = block_scale_fast(bmax * inv_msg, unsure);
-    sb = e4m3_normal_to_f32(sbyte);
-    inv = __builtin_amdgcn_rcpf(sb * sg);
-    if (__builtin_expect(unsure, 0)) {
-        sbyte = block_scale_exact(bmax, sg, inv_msg, target);
-        sb = e4m3_to_f32(sbyte);
-        inv = (sb == 0.0f) ? 0.0f : __builtin_amdgcn_rcpf(sb * sg);
-    }
-}
-
-// Scale search (Eq. 12-13) on one block, the two candidates side by side; the results of
-// quantize_block16_4over6_exact for tensor scales inside the fp32-safe range.  The fp32 squared errors
-// are summed in four partial sums (the bound r of encode_block16_4over6 holds for any order of summation).
-__device__ __forceinline__ void quantize_block16_4over6_inline(const uint32_t (&w)[8], float sg, float inv_6sg, float inv_4sg,
-                                                               uint32_t &sbyte, uint32_t &c0, uint32_t &c1)
+// Scale search (Eq. 12-13) on one block: the block maximum mapped to 6 and to 4, both encodings settled as above, the
+// one with the strictly smaller squared error kept (equal errors keep 6).  Which error is smaller is decided by the
+// cheapest evaluation that is sure of it:
+//  1. with m the decoded magnitudes (signed like x) and den = s_b s_g, the error is sum x^2 - den (2 S - den Q),
+//     S = sum x m, Q = sum m^2, so the candidate with the larger gain den (2 S - den Q) wins.  S and Q are two-element
+//     dot products on the packed bf16 pairs themselves.  Q is exact (quarter integers up to 576); all terms of S are
+//     non-negative, a dot product step is off by less than 2^-22 of its sum (two fp32 roundings: 2^-23 measured), so
+//     S is off by less than 2^-20.8 of itself over chains of two steps and the additions behind them, and the gain by
+//     less than 2^-19.5 den S.  About one block in a thousand of Gaussian data is closer than the 2^-19 den S taken here;
+//  2. the errors themselves in fp32.  |d~ - d| <= 2^-24 (|x| + |x^| + 6 den) < u; |d~^2 - d^2| <= u (2 |d~| + u), and
+//     the sixteen |d~| add up to at most 4 sqrt(sum d~^2) (Cauchy-Schwarz; 4.01 covers the approximate square root
+//     and the rounding of the sum); sixteen fused accumulations add at most 2^-19 of the sum.  One block in 10^4 to
+//     10^5 is still open;
+//  3. the fp64 definition.
+// Gains and errors below 2^-100, where fp32 may lose its relative accuracy, or that are no finite numbers are never sure.
+// Bound by VALU issue: about 230 slots per block (the bracketed search took about 450): 16 unpack, 8 maximum, 20 scales,
+// 32 multiplies, 32 conversions of up to three slots, 32 dot products.
+__device__ __forceinline__ float block_error_f32(const float (&f)[16], const uint32_t (&c)[2], float den)
 {
     typedef float float2v __attribute__((ext_vector_type(2)));
-    float f[16];
-    unpack16(w, f);
-    const float bmax = absmax16_tree(f);
-    uint32_t s6, s4;
-    float sb6, sb4, inv6, inv4;
-    block_scale_inline(bmax, sg, inv_6sg, 6.0, s6, sb6, inv6);
-    block_scale_inline(bmax, sg, inv_4sg, 4.0, s4, sb4, inv4);
-    const float il6 = inv6 * kBracketLo, ih6 = inv6 * kBracketHi, il4 = inv4 * kBracketLo, ih4 = inv4 * kBracketHi;
-    // The candidates are compared on the codes of the LOWER bracket end alone; the upper end is converted for the
-    // winner only, whose near-ties are then settled.  A nibble on which the two ends would disagree lies within
-    // 2^-19 of a midpoint T between magnitudes T -+ h, so its squared error changes by the factor
-    // 1 +- 4 (T / h) 2^-19 at most when the nibble flips, and T / h <= 7: the settled codes' error lies within
-    // 2^-14 (e + r) of the error e that is computed here, which the uncertainty r below takes in.
-    uint32_t l6[2] = {0, 0}, l4[2] = {0, 0};
-#define NVFP4_STEP(K, SEL)                                                                                              \
-    l6[K >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(l6[K >> 2], f[2 * K] * il6, f[2 * K + 1] * il6, 1.0f, SEL);   \
-    l4[K >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(l4[K >> 2], f[2 * K] * il4, f[2 * K + 1] * il4, 1.0f, SEL);
+    float err = 0.0f;
+#define NVFP4_STEP(K, SEL)                                                                 \
+    {                                                                                      \
+        const float2v q = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c[K >> 2], 1.0f, SEL);  \
+        const float d0 = __builtin_fmaf(-q.x, den, f[2 * K]), d1 = __builtin_fmaf(-q.y, den, f[2 * K + 1]); \
+        err = __builtin_fmaf(d0, d0, err);                                                 \
+        err = __builtin_fmaf(d1, d1, err);                                                 \
+    }
     NVFP4_STEP(0, 0) NVFP4_STEP(1, 1) NVFP4_STEP(2, 2) NVFP4_STEP(3, 3)
     NVFP4_STEP(4, 0) NVFP4_STEP(5, 1) NVFP4_STEP(6, 2) NVFP4_STEP(7, 3)
 #undef NVFP4_STEP
-    const float den6 = sb6 * sg, den4 = sb4 * sg;
-    float e6a = 0.0f, e6b = 0.0f, e4a = 0.0f, e4b = 0.0f;
+    return err;
+}
+// S and Q of one candidate
+__device__ __forceinline__ void block_products(const uint32_t (&w)[8], const uint32_t (&c)[2], float &S, float &Q)
+{
+    typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f}, q[2] = {0.0f, 0.0f};
 #define NVFP4_STEP(K, SEL)                                                                                        \
     {                                                                                                             \
-        const float2v q6 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(l6[K >> 2], 1.0f, SEL);                       \
-        const float2v q4 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(l4[K >> 2], 1.0f, SEL);                       \
-        const float d60 = __builtin_fmaf(-q6.x, den6, f[2 * K]), d61 = __builtin_fmaf(-q6.y, den6, f[2 * K + 1]); \
-        const float d40 = __builtin_fmaf(-q4.x, den4, f[2 * K]), d41 = __builtin_fmaf(-q4.y, den4, f[2 * K + 1]); \
-        e6a = __builtin_fmaf(d60, d60, e6a);                                                                      \
-        e6b = __builtin_fmaf(d61, d61, e6b);                                                                      \
-        e4a = __builtin_fmaf(d40, d40, e4a);                                                                      \
-        e4b = __builtin_fmaf(d41, d41, e4b);                                                                      \
+        const bf16x2v m = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c[K >> 2], 1.0f, SEL);                        \
+        s[K & 3] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v, w[K]), m, s[K & 3], false);        \
+        q[K & 1] = __builtin_amdgcn_fdot2_f32_bf16(m, m, q[K & 1], false);                                        \
     }
     NVFP4_STEP(0, 0) NVFP4_STEP(1, 1) NVFP4_STEP(2, 2) NVFP4_STEP(3, 3)
     NVFP4_STEP(4, 0) NVFP4_STEP(5, 1) NVFP4_STEP(6, 2) NVFP4_STEP(7, 3)
 #undef NVFP4_STEP
-    const float e6 = e6a + e6b, e4 = e4a + e4b;
-    const float u6 = 0x1p-22f * (bmax + 6.0f * den6), u4 = 0x1p-22f * (bmax + 6.0f * den4);
-    float r6 = u6 * (8.02f * __builtin_amdgcn_sqrtf(e6) + 16.0f * u6) + 0x1p-19f * e6;   // (eight fused steps and one
-    float r4 = u4 * (8.02f * __builtin_amdgcn_sqrtf(e4) + 16.0f * u4) + 0x1p-19f * e4;   //  addition: below 2^-19 as well)
-    r6 = __builtin_fmaf(0x1p-14f, e6, 1.0001f * r6);
-    r4 = __builtin_fmaf(0x1p-14f, e4, 1.0001f * r4);
-    const bool tiny = fminf(e4, e6) < 0x1p-100f;
-    const bool same = s4 == s6;                    // (saturated scales, zero blocks: same codes, same error, 6 is kept)
-    bool pick4 = e4 + r4 < e6 - r6;
-    auto upper_end = [&](float ih, uint32_t (&h)[2]) {
-        h[0] = h[1] = 0u;
-#define NVFP4_STEP(K, SEL) h[K >> 2] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(h[K >> 2], f[2 * K] * ih, f[2 * K + 1] * ih, 1.0f, SEL);
-        NVFP4_STEP(0, 0) NVFP4_STEP(4, 0) NVFP4_STEP(1, 1) NVFP4_STEP(5, 1)
-        NVFP4_STEP(2, 2) NVFP4_STEP(6, 2) NVFP4_STEP(3, 3) NVFP4_STEP(7, 3)
-#undef NVFP4_STEP
-    };
-    if (__builtin_expect(!same & (tiny | !(pick4 | (e4 - r4 > e6 + r6))), 0)) {     // too close in fp32: settle both, compare in fp64
-        uint32_t h6[2], h4[2];
-        upper_end(ih6, h6);
-        upper_end(ih4, h4);
-        resolve_codes(w, sb6, sg, l6[0], l6[1], h6[0], h6[1]);
-        resolve_codes(w, sb4, sg, l4[0], l4[1], h4[0], h4[1]);
-        pick4 = block_error_f64(w, l4[0], l4[1], sb4, sg) < block_error_f64(w, l6[0], l6[1], sb6, sg);
+    S = (s[0] + s[1]) + (s[2] + s[3]);
+    Q = q[0] + q[1];
+}
+__device__ __forceinline__ void quantize_block16_4over6(const uint32_t (&w)[8], const TensorScale &t, uint32_t &sbyte, uint32_t &c0, uint32_t &c1)
+{
+    float f[16], sb[2], inv[2];
+    uint32_t s[2], c[2][2];                                    // [0]: maximum -> 6, [1]: maximum -> 4
+    unpack16(w, f);
+    const float bmax = absmax16_tree(f);
+    block_scale(bmax, t.inv6, t, s[0], sb[0], inv[0]);
+    block_scale(bmax, t.inv4, t, s[1], sb[1], inv[1]);
+    encode_values<2>({&f, 0}, inv, t.snap, c);                 // both candidates of the one block
+    const float den6 = sb[0] * t.sg, den4 = sb[1] * t.sg;
+    float S6, Q6, S4, Q4;
+    block_products(w, c[0], S6, Q6);
+    block_products(w, c[1], S4, Q4);
+    const float g6 = den6 * __builtin_fmaf(-den6, Q6, 2.0f * S6), g4 = den4 * __builtin_fmaf(-den4, Q4, 2.0f * S4);
+    const float r = 0x1p-19f * __builtin_fmaf(den6, S6, den4 * S4), diff = g4 - g6;
+    bool pick4 = diff > r;
+    const bool same = s[0] == s[1];                            // (saturated scales, zero blocks: same codes, same error, 6 is kept)
+    const bool sure = (fabsf(diff) > r) & (fminf(g6, g4) > 0x1p-100f) & (fmaxf(g6, g4) < 0x1p120f);
+    if (__builtin_expect(!(sure | same), 0)) {
+        const float e6 = block_error_f32(f, c[0], den6), e4 = block_error_f32(f, c[1], den4);
+        const float u6 = 0x1p-22f * (bmax + 6.0f * den6), u4 = 0x1p-22f * (bmax + 6.0f * den4);
+        const float r6 = u6 * (8.02f * __builtin_amdgcn_sqrtf(e6) + 16.0f * u6) + 0x1p-19f * e6;
+        const float r4 = u4 * (8.02f * __builtin_amdgcn_sqrtf(e4) + 16.0f * u4) + 0x1p-19f * e4;
+        pick4 = e4 + r4 < e6 - r6;
+        const bool settled = !(fminf(e4, e6) < 0x1p-100f) & (pick4 | (e4 - r4 > e6 + r6));
+        if (__builtin_expect(!settled, 0))
+            pick4 = block_error_f64(w, c[1][0], c[1][1], sb[1], t.sg) < block_error_f64(w, c[0][0], c[0][1], sb[0], t.sg);
     }
     pick4 &= !same;
-    sbyte = pick4 ? s4 : s6;
-    c0 = pick4 ? l4[0] : l6[0];
-    c1 = pick4 ? l4[1] : l6[1];
-    uint32_t hw[2];
-    upper_end(pick4 ? ih4 : ih6, hw);
-    resolve_codes(w, pick4 ? sb4 : sb6, sg, c0, c1, hw[0], hw[1]);   // (settled codes pass through unchanged)
-}
-
-// the one-block-at-a-time counterparts, for any tensor scale (sgq, inv_6sgq, inv_4sgq: the scale after range_shift)
-__device__ __forceinline__ void quantize_block16_4over6_exact(uint32_t (&w)[8], float shift, float sgq, float inv_6sgq,
-                                                              float inv_4sgq, uint32_t &sbyte, uint32_t &c0, uint32_t &c1)
-{
-    if (__builtin_expect(shift != 1.0f, 0)) rescale_block16(w, shift);
-    encode_block16_4over6(w, block_absmax_f32(w), sgq, inv_6sgq, inv_4sgq, sbyte, c0, c1);
+    sbyte = pick4 ? s[1] : s[0];
+    c0 = pick4 ? c[1][0] : c[0][0];
+    c1 = pick4 ? c[1][1] : c[0][1];
 }
 
 // Round a non-negative exact product held in a double to bf16 once (nearest

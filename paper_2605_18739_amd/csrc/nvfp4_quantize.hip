@@ -205,8 +205,6 @@ void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
     const float sg = resolve_global_scale(gs_in, partial, n_partial, gs_out, lds4);
     if constexpr (SEARCH) fetch(first);
     const TensorScale ts = tensor_scale(sg);
-    const float inv_6sg = 1.0f / (6.0f * ts.sg);
-    const float inv_4sg = 1.0f / (4.0f * ts.sg);
     for (int64_t g0 = first; g0 < nblk; g0 += stride * U) {
         if (g0 != first) fetch(g0);
 #pragma unroll
@@ -218,14 +216,8 @@ void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
                 if constexpr (SMOOTH) smooth_block16(w, __uint_as_float((uint32_t)row_mean[g >> row_shift] << 16));
                 if (__builtin_expect(ts.shift != 1.0f, 0)) rescale_block16(w, ts.shift);
                 uint32_t sbyte, c0, c1;
-                if constexpr (!SEARCH) {
-                    quantize_block16(w, ts, sbyte, c0, c1);
-                } else if (__builtin_expect(ts.shift == 1.0f, 1)) {
-                    // the straight-line form: the candidates compared on one bracket end, the winner settled
-                    quantize_block16_4over6_inline(w, ts.sg, inv_6sg, inv_4sg, sbyte, c0, c1);
-                } else {
-                    encode_block16_4over6(w, block_absmax_f32(w), ts.sg, inv_6sg, inv_4sg, sbyte, c0, c1);
-                }
+                if constexpr (SEARCH) quantize_block16_4over6(w, ts, sbyte, c0, c1);
+                else quantize_block16(w, ts, sbyte, c0, c1);
                 uint2v cc = {c0, c1};
                 int64_t go = g;                       // output block index
                 if (slab_heads > 0) {
@@ -554,7 +546,7 @@ __global__ __launch_bounds__(256) void quantize_tiles_kernel(const uint16_t *__r
         float f[1][16];
         uint32_t c[1][2];
         unpack16(w[i], f[0]);
-        encode_values<1>(f, inv, ts.snap, c);
+        encode_values<1>({f, 1}, inv, ts.snap, c);
         c0[i] = c[0][0];
         c1[i] = c[0][1];
         const int64_t row = 16 * I + i;

@@ -118,12 +118,12 @@ struct Pass2Out {
 // hardware drops, so no branch surrounds the stores and the compiler can schedule across them.
 template <bool SEARCH>
 __device__ __forceinline__ void pair_pass2(const uint32_t (&wa)[8], const uint32_t (&wb)[8], int64_t ga, int64_t gb, int64_t nblk,
-                                           const TensorScale &ts, float inv_6sg, float inv_4sg, const Pass2Out &out, const ResidentArgs &a)
+                                           const TensorScale &ts, const Pass2Out &out, const ResidentArgs &a)
 {
     uint32_t sa, a0, a1, sb, b0, b1;
     if constexpr (SEARCH) {
-        quantize_block16_4over6_inline(wa, ts.sg, inv_6sg, inv_4sg, sa, a0, a1);
-        quantize_block16_4over6_inline(wb, ts.sg, inv_6sg, inv_4sg, sb, b0, b1);
+        quantize_block16_4over6(wa, ts, sa, a0, a1);
+        quantize_block16_4over6(wb, ts, sb, b0, b1);
     } else {
         quantize_pair16(wa, wb, ts, sa, a0, a1, sb, b0, b1);
     }
@@ -283,7 +283,6 @@ __global__ __launch_bounds__(kResThreads) void quantize_rows_resident_kernel(Res
     const float sg = global_scale_from_amax_bits(tmax);
     if (blockIdx.x == 0 && tid == 0) *a.gs_out = sg;
     const TensorScale ts = tensor_scale(sg);
-    const float inv_6sg = 1.0f / (6.0f * ts.sg), inv_4sg = 1.0f / (4.0f * ts.sg);
     if (__builtin_expect(ts.shift != 1.0f, 0)) {
         // A tensor scale outside the range in which fp32 quotients are safe: every block one at a time with the
         // tensor and its scale shifted back into range, from
@@ -302,12 +301,9 @@ __global__ __launch_bounds__(kResThreads) void quantize_rows_resident_kernel(Res
             uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
             if constexpr (SMOOTH) smooth_block16(w, __uint_as_float((uint32_t)a.mean_out[g >> a.row_shift] << 16));
             uint32_t sbyte, c0, c1;
-            if constexpr (SEARCH) {
-                quantize_block16_4over6_exact(w, ts.shift, ts.sg, inv_6sg, inv_4sg, sbyte, c0, c1);
-            } else {
-                rescale_block16(w, ts.shift);
-                quantize_block16(w, ts, sbyte, c0, c1);
-            }
+            rescale_block16(w, ts.shift);
+            if constexpr (SEARCH) quantize_block16_4over6(w, ts, sbyte, c0, c1);
+            else quantize_block16(w, ts, sbyte, c0, c1);
             const int64_t go = output_block((uint32_t)g, a);
             *(uint2v *)(a.codes + (go << 3)) = uint2v{c0, c1};
             a.scales[go] = (uint8_t)sbyte;
@@ -321,7 +317,7 @@ __global__ __launch_bounds__(kResThreads) void quantize_rows_resident_kernel(Res
             const uint32_t wa[8] = {r0[i].x, r0[i].y, r0[i].z, r0[i].w, r1[i].x, r1[i].y, r1[i].z, r1[i].w};
             const uint32_t wb[8] = {r0[i + 1].x, r0[i + 1].y, r0[i + 1].z, r0[i + 1].w, r1[i + 1].x, r1[i + 1].y, r1[i + 1].z, r1[i + 1].w};
             // (slot i + 1 beyond the slots in use holds zeros and lies past the end of the tensor)
-            pair_pass2<SEARCH>(wa, wb, block_of(i), i + 1 < nr ? block_of(i + 1) : a.nblk, a.nblk, ts, inv_6sg, inv_4sg, out, a);
+            pair_pass2<SEARCH>(wa, wb, block_of(i), i + 1 < nr ? block_of(i + 1) : a.nblk, a.nblk, ts, out, a);
         }
     });
     // The blocks in LDS belong to no wave in particular, so they are handed out from a queue: 64 lanes x 2 slots per
@@ -341,7 +337,7 @@ __global__ __launch_bounds__(kResThreads) void quantize_rows_resident_kernel(Res
         const uint32_t wa[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
         const uint32_t wb[8] = {v2.x, v2.y, v2.z, v2.w, v3.x, v3.y, v3.z, v3.w};
         const int64_t ga = wg_first + (int64_t)(kResRegSlots + s) * kResThreads + t;
-        pair_pass2<SEARCH>(wa, wb, ga, two ? ga + kResThreads : a.nblk, a.nblk, ts, inv_6sg, inv_4sg, out, a);
+        pair_pass2<SEARCH>(wa, wb, ga, two ? ga + kResThreads : a.nblk, a.nblk, ts, out, a);
     }
 }
 
