@@ -1,18 +1,24 @@
-"""ctypes binding of the NVFP4 HIP library: argument marshalling only.
+"""Binding of the NVFP4 HIP library: argument marshalling only.
 
 Function names mirror the C ABI in include/nvfp4.h.  torch supplies device
 memory and the current stream; every step of the path runs in the library's
-kernels.  There is no CPU fallback: if the shared library is missing, importing
-this module's entry points raises.
+kernels.  The calls that launch work take their pointers and allocate what the
+caller does not pass in native code (csrc/nvfp4_host.cpp); lib() is the C ABI
+itself, through ctypes.  There is no CPU fallback: if a shared library is
+missing, importing this module's entry points raises.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libnvfp4_hip.so")
+_HOST_PATH = os.path.join(_HERE, "_host.so")
 _lib = None
+_host_module = None
 
 OUT_F32, OUT_BF16 = 0, 1
 ACT_NONE, ACT_GELU_TANH = 0, 1
@@ -110,9 +116,25 @@ def _check(rc):
         raise NVFP4Error(f"nvfp4 status {rc}: {lib().nvfp4_status_string(rc).decode()}")
 
 
+def _host():
+    global _host_module
+    if _host_module is None:
+        lib()
+        if not os.path.exists(_HOST_PATH):
+            raise NVFP4Error(f"{_HOST_PATH} is missing: build it with `python -m paper_2605_18739_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("_host", _HOST_PATH)
+        _host_module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_host", loader))
+        loader.exec_module(_host_module)
+    return _host_module
+
+
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    """The hipStream_t of `stream`, or of torch's current stream on the current device."""
+    if stream is not None:
+        return stream.cuda_stream
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 class NVFP4Tensor:
@@ -120,6 +142,9 @@ class NVFP4Tensor:
 
     def __init__(self, rows, K, device="cuda", codes=None, scales=None, global_scale=None):
         self.rows, self.K = int(rows), int(K)
+        if codes is None and scales is None and global_scale is None and isinstance(device, torch.device):
+            self.codes, self.scales, self.global_scale = _host().buffers(self.rows, self.K, device)
+            return
         self.codes = codes if codes is not None else torch.empty((rows, K // 2), dtype=torch.uint8, device=device)
         self.scales = scales if scales is not None else torch.empty((rows, K // 16), dtype=torch.uint8, device=device)
         self.global_scale = (global_scale if global_scale is not None
@@ -141,233 +166,146 @@ def nvfp4_workspace_bytes(op, a, b=0, c=0):
     return int(lib().nvfp4_workspace_bytes(op, a, b, c))
 
 
-def _workspace(nbytes, device):
-    return torch.empty(max(int(nbytes), 16), dtype=torch.uint8, device=device)
-
-
 def _ptr(t):
     return ctypes.c_void_p(t.data_ptr()) if t is not None else None
 
 
 def nvfp4_quantize(x, block_axis=0, global_scale_in=None, out=None, workspace=None, stream=None):
     """x: bf16 [R, C] device tensor with unit stride along C. Returns an NVFP4Tensor."""
-    assert x.dtype == torch.bfloat16 and x.dim() == 2 and x.stride(1) == 1
-    R, C = x.shape
-    ld = x.stride(0)
-    rows, K = (R, C) if block_axis == 0 else (C, R)
     if out is None:
-        out = NVFP4Tensor(rows, K, x.device)
-    if workspace is None:
-        workspace = _workspace(nvfp4_workspace_bytes(OP_QUANTIZE, R, C), x.device)
-    ct = out.c()
-    _check(lib().nvfp4_quantize(_ptr(x), R, C, ld, block_axis, _ptr(global_scale_in), ctypes.byref(ct),
-                                _ptr(workspace), workspace.numel(), _stream(stream)))
+        R, C = x.shape
+        out = NVFP4Tensor(R, C, x.device) if block_axis == 0 else NVFP4Tensor(C, R, x.device)
+    _check(_host().quantize(x, block_axis, global_scale_in, out, workspace, _stream(stream)))
     return out
 
 
 def nvfp4_gemm(A, W, out_dtype=OUT_F32, Y=None, stream=None):
-    M, N = A.rows, W.rows
     if Y is None:
-        Y = torch.empty((M, N), dtype=torch.float32 if out_dtype == OUT_F32 else torch.bfloat16,
-                        device=A.codes.device)
-    ca, cw = A.c(), W.c()
-    _check(lib().nvfp4_gemm(ctypes.byref(ca), ctypes.byref(cw), _ptr(Y), Y.stride(0), out_dtype,
-                            _stream(stream)))
+        Y = _host().output(A.codes, A.rows, W.rows, out_dtype != OUT_F32)
+    _check(_host().gemm(A, W, out_dtype, Y, _stream(stream)))
     return Y
 
 
 def nvfp4_gemm_scale_out(A, W, Y=None, scale_out=None, workspace=None, stream=None):
     """bf16 Y = A W^T together with the NVFP4 tensor scale of Y (one float on the device).  Returns (Y, scale_out)."""
-    M, N = A.rows, W.rows
     if Y is None:
-        Y = torch.empty((M, N), dtype=torch.bfloat16, device=A.codes.device)
+        Y = _host().output(A.codes, A.rows, W.rows, True)
     if scale_out is None:
         scale_out = torch.empty(1, dtype=torch.float32, device=A.codes.device)
-    if workspace is None:
-        workspace = _workspace(nvfp4_workspace_bytes(OP_GEMM_SCALE_OUT, M, N), A.codes.device)
-    ca, cw = A.c(), W.c()
-    _check(lib().nvfp4_gemm_scale_out(ctypes.byref(ca), ctypes.byref(cw), _ptr(Y), Y.stride(0), _ptr(scale_out),
-                                      _ptr(workspace), workspace.numel(), _stream(stream)))
+    _check(_host().gemm_scale_out(A, W, Y, scale_out, workspace, _stream(stream)))
     return Y, scale_out
 
 
 def nvfp4_lora_down(x, a, out=None, workspace=None, stream=None):
     """T = bf16(x a^T): x bf16 [M, K] (unit stride along K), a bf16 [128, K] contiguous."""
-    assert x.dtype == torch.bfloat16 and a.dtype == torch.bfloat16 and x.stride(1) == 1 and a.is_contiguous()
-    M, K = x.shape
-    assert a.shape == (LORA_RANK, K)
     if out is None:
-        out = torch.empty((M, LORA_RANK), dtype=torch.bfloat16, device=x.device)
-    if workspace is None:
-        workspace = _workspace(nvfp4_workspace_bytes(OP_LORA_DOWN, M, K), x.device)
-    _check(lib().nvfp4_lora_down(_ptr(x), M, K, x.stride(0), _ptr(a), _ptr(out), _ptr(workspace), workspace.numel(),
-                                 _stream(stream)))
+        out = _host().output(x, x.shape[0], LORA_RANK, True)
+    _check(_host().lora_down(x, a, out, workspace, _stream(stream)))
     return out
 
 
 def nvfp4_gemm_lora(A, W, t, b, lora_scale, out_dtype=OUT_F32, Y=None, stream=None):
     """nvfp4_gemm(A, W) + lora_scale * t b^T, fused; t bf16 [M, 128], b bf16 [N, 128], both contiguous."""
-    M, N = A.rows, W.rows
-    assert t.is_contiguous() and b.is_contiguous() and t.shape == (M, LORA_RANK) and b.shape == (N, LORA_RANK)
     if Y is None:
-        Y = torch.empty((M, N), dtype=torch.float32 if out_dtype == OUT_F32 else torch.bfloat16,
-                        device=A.codes.device)
-    ca, cw = A.c(), W.c()
-    _check(lib().nvfp4_gemm_lora(ctypes.byref(ca), ctypes.byref(cw), _ptr(t), _ptr(b), float(lora_scale), _ptr(Y),
-                                 Y.stride(0), out_dtype, _stream(stream)))
+        Y = _host().output(A.codes, A.rows, W.rows, out_dtype != OUT_F32)
+    _check(_host().gemm_lora(A, W, t, b, lora_scale, out_dtype, Y, _stream(stream)))
     return Y
 
 
 def nvfp4_gemm_act_quant(A, W, act=ACT_GELU_TANH, global_scale_in=None, out=None, h_bf16=None,
                          workspace=None, stream=None):
-    M, N = A.rows, W.rows
-    dev = A.codes.device
     if out is None:
-        out = NVFP4Tensor(M, N, dev)
-    if workspace is None:
-        flags = (1 if h_bf16 is not None else 0) | (2 if (global_scale_in is not None and A.K % 64 == 0) else 0)
-        workspace = _workspace(nvfp4_workspace_bytes(OP_GEMM_ACT_QUANT, M, N, flags), dev)
-    ca, cw, co = A.c(), W.c(), out.c()
-    _check(lib().nvfp4_gemm_act_quant(ctypes.byref(ca), ctypes.byref(cw), act, _ptr(global_scale_in),
-                                      ctypes.byref(co), _ptr(h_bf16), _ptr(workspace), workspace.numel(),
-                                      _stream(stream)))
+        out = NVFP4Tensor(A.rows, W.rows, A.codes.device)
+    _check(_host().gemm_act_quant(A, W, act, global_scale_in, out, h_bf16, workspace, _stream(stream)))
     return out
+
+
+def _heads_out(x):
+    T, H, d = x.shape
+    return NVFP4Tensor(T * H, d, x.device)
 
 
 def nvfp4_kv_quant(kv, out=None, workspace=None, stream=None):
     """kv: contiguous bf16 [T, H, d]."""
-    assert kv.dtype == torch.bfloat16 and kv.dim() == 3 and kv.is_contiguous()
-    T, H, d = kv.shape
     if out is None:
-        out = NVFP4Tensor(T * H, d, kv.device)
-    if workspace is None:
-        workspace = _workspace(nvfp4_workspace_bytes(OP_KV_QUANT, T, H, d), kv.device)
-    ct = out.c()
-    _check(lib().nvfp4_kv_quant(_ptr(kv), T, H, d, ctypes.byref(ct), _ptr(workspace), workspace.numel(),
-                                _stream(stream)))
+        out = _heads_out(kv)
+    _check(_host().kv_quant(kv, out, workspace, _stream(stream)))
     return out
 
 
 def nvfp4_kv_quant_noalloc(kv, out, stream=None):
     """kv: contiguous bf16 [T, H, d]; `out` must be given: this entry point (and this wrapper) allocates nothing."""
-    assert kv.dtype == torch.bfloat16 and kv.dim() == 3 and kv.is_contiguous()
-    T, H, d = kv.shape
-    ct = out.c()
-    _check(lib().nvfp4_kv_quant_noalloc(_ptr(kv), T, H, d, ctypes.byref(ct), _stream(stream)))
+    _check(_host().kv_quant_noalloc(kv, out, _stream(stream)))
     return out
 
 
 def nvfp4_quantize_4over6(x, global_scale_in=None, out=None, workspace=None, stream=None):
     """x: bf16 [R, C] device tensor with unit stride along C; blocks along C, scale search per block."""
-    assert x.dtype == torch.bfloat16 and x.dim() == 2 and x.stride(1) == 1
-    R, C = x.shape
     if out is None:
+        R, C = x.shape
         out = NVFP4Tensor(R, C, x.device)
-    if workspace is None:
-        workspace = _workspace(nvfp4_workspace_bytes(OP_QUANTIZE_4OVER6, R, C), x.device)
-    ct = out.c()
-    _check(lib().nvfp4_quantize_4over6(_ptr(x), R, C, x.stride(0), _ptr(global_scale_in), ctypes.byref(ct),
-                                       _ptr(workspace), workspace.numel(), _stream(stream)))
+    _check(_host().quantize_4over6(x, global_scale_in, out, workspace, _stream(stream)))
     return out
 
 
 def nvfp4_kv_quant_4over6(kv, out=None, workspace=None, stream=None):
     """kv: contiguous bf16 [T, H, d]; scale search per block."""
-    assert kv.dtype == torch.bfloat16 and kv.dim() == 3 and kv.is_contiguous()
-    T, H, d = kv.shape
     if out is None:
-        out = NVFP4Tensor(T * H, d, kv.device)
-    if workspace is None:
-        workspace = _workspace(nvfp4_workspace_bytes(OP_KV_QUANT_4OVER6, T, H, d), kv.device)
-    ct = out.c()
-    _check(lib().nvfp4_kv_quant_4over6(_ptr(kv), T, H, d, ctypes.byref(ct), _ptr(workspace), workspace.numel(),
-                                       _stream(stream)))
+        out = _heads_out(kv)
+    _check(_host().kv_quant_4over6(kv, out, workspace, _stream(stream)))
     return out
 
 
 def nvfp4_quantize_for_all_to_all(x, P, global_scale_in=None, out=None, workspace=None, stream=None):
     """x: contiguous bf16 [T, H, d]; NVFP4 along d, rows regrouped into P per-destination slabs of H/P heads."""
-    assert x.dtype == torch.bfloat16 and x.dim() == 3 and x.is_contiguous()
-    T, H, d = x.shape
     if out is None:
-        out = NVFP4Tensor(T * H, d, x.device)
-    if workspace is None:
-        workspace = _workspace(nvfp4_workspace_bytes(OP_QUANTIZE_A2A, T, H, d), x.device)
-    ct = out.c()
-    _check(lib().nvfp4_quantize_for_all_to_all(_ptr(x), T, H, d, P, _ptr(global_scale_in), ctypes.byref(ct),
-                                               _ptr(workspace), workspace.numel(), _stream(stream)))
+        out = _heads_out(x)
+    _check(_host().quantize_for_all_to_all(x, P, global_scale_in, out, workspace, _stream(stream)))
     return out
 
 
 def nvfp4_quantize_rht(x, sign_mask, global_scale_in=None, out=None, workspace=None, stream=None):
     """x: bf16 [R, C], contracted over R.  Random Hadamard transform along R (groups of 16) with the
     16-bit sign mask, then the transposed quantizer: returns NVFP4Tensor [C, R]."""
-    assert x.dtype == torch.bfloat16 and x.dim() == 2 and x.stride(1) == 1
-    R, C = x.shape
     if out is None:
+        R, C = x.shape
         out = NVFP4Tensor(C, R, x.device)
-    if workspace is None:
-        workspace = _workspace(nvfp4_workspace_bytes(OP_QUANTIZE_RHT, R, C), x.device)
-    ct = out.c()
-    _check(lib().nvfp4_quantize_rht(_ptr(x), R, C, x.stride(0), int(sign_mask), _ptr(global_scale_in),
-                                    ctypes.byref(ct), _ptr(workspace), workspace.numel(), _stream(stream)))
+    _check(_host().quantize_rht(x, int(sign_mask), global_scale_in, out, workspace, _stream(stream)))
     return out
 
 
 def nvfp4_quantize_2d(w, global_scale_in=None, transposed=True, workspace=None, stream=None):
     """w: bf16 [R, C] weights (R, C multiples of 16), one scale per 16x16 tile.
     Returns (NVFP4Tensor [R, C], NVFP4Tensor [C, R] or None)."""
-    assert w.dtype == torch.bfloat16 and w.dim() == 2 and w.stride(1) == 1
     R, C = w.shape
     out = NVFP4Tensor(R, C, w.device)
     out_t = NVFP4Tensor(C, R, w.device) if transposed else None
-    if workspace is None:
-        workspace = _workspace(nvfp4_workspace_bytes(OP_QUANTIZE_2D, R, C), w.device)
-    co = out.c()
-    ct = out_t.c() if transposed else None
-    _check(lib().nvfp4_quantize_2d(_ptr(w), R, C, w.stride(0), _ptr(global_scale_in), ctypes.byref(co),
-                                   ctypes.byref(ct) if transposed else None, _ptr(workspace), workspace.numel(),
-                                   _stream(stream)))
+    _check(_host().quantize_2d(w, global_scale_in, out, out_t, workspace, _stream(stream)))
     return out, out_t
 
 
 def nvfp4_kv_quant_k(k, out=None, row_mean=None, workspace=None, stream=None):
     """k: contiguous bf16 [T, H, d] keys; K-smoothing then scale search.  Returns (NVFP4Tensor, row means bf16 [T*H])."""
-    assert k.dtype == torch.bfloat16 and k.dim() == 3 and k.is_contiguous()
-    T, H, d = k.shape
     if out is None:
-        out = NVFP4Tensor(T * H, d, k.device)
+        out = _heads_out(k)
     if row_mean is None:
-        row_mean = torch.empty(T * H, dtype=torch.bfloat16, device=k.device)
-    if workspace is None:
-        workspace = _workspace(nvfp4_workspace_bytes(OP_KV_QUANT_K, T, H, d), k.device)
-    ct = out.c()
-    _check(lib().nvfp4_kv_quant_k(_ptr(k), T, H, d, ctypes.byref(ct), _ptr(row_mean), _ptr(workspace),
-                                  workspace.numel(), _stream(stream)))
+        row_mean = torch.empty(k.shape[0] * k.shape[1], dtype=torch.bfloat16, device=k.device)
+    _check(_host().kv_quant_k(k, out, row_mean, workspace, _stream(stream)))
     return out, row_mean
 
 
 def nvfp4_kv_dequant_gather(chunks, H, d, out=None, stream=None):
     """chunks: list of (NVFP4Tensor, row_mean or None, T).  Returns bf16 [sum T, H, d]."""
-    n = len(chunks)
-    arr = (_CKvChunk * n)()
-    total = 0
-    for i, (q, mean, T) in enumerate(chunks):
-        arr[i].q = q.c()
-        arr[i].row_mean_bf16 = mean.data_ptr() if mean is not None else None
-        arr[i].T = T
-        total += T
     if out is None:
-        out = torch.empty((total, H, d), dtype=torch.bfloat16, device=chunks[0][0].codes.device)
-    _check(lib().nvfp4_kv_dequant_gather(arr, n, _ptr(out), H, d, _stream(stream)))
+        out = torch.empty((sum(T for _, _, T in chunks), H, d), dtype=torch.bfloat16, device=chunks[0][0].codes.device)
+    _check(_host().kv_dequant_gather(chunks, H, d, out, _stream(stream)))
     return out
 
 
 def nvfp4_kv_dequant(q, T, H, d, out=None, stream=None):
     if out is None:
         out = torch.empty((T, H, d), dtype=torch.bfloat16, device=q.codes.device)
-    ct = q.c()
-    _check(lib().nvfp4_kv_dequant(ctypes.byref(ct), _ptr(out), T, H, d, _stream(stream)))
+    _check(_host().kv_dequant(q, T, H, d, out, _stream(stream)))
     return out
 
 

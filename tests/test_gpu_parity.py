@@ -291,6 +291,23 @@ def test_quantize_tensor_scales_outside_the_fp32_safe_range(oracle, magnitude):
     assert_q_equal(nv.nvfp4_quantize(dev_bf16(xb), block_axis=1), oracle.quantize(xb, block_axis=1), f"transposed {magnitude}")
 
 
+def test_binding_refuses_tensors_it_cannot_marshal():
+    x = torch.zeros((32, 64), dtype=torch.bfloat16, device="cuda")
+    for bad in (x.float(), x.t(), x[0], x[:, ::2]):
+        with pytest.raises(AssertionError):
+            nv.nvfp4_quantize(bad, out=nv.NVFP4Tensor(32, 64))
+    for bad in (x.view(2, 16, 64).float(), x.view(2, 16, 64)[:, :, :32], x):
+        with pytest.raises(AssertionError):
+            nv.nvfp4_kv_quant(bad, out=nv.NVFP4Tensor(32, 64))
+    q = nv.nvfp4_quantize(x)
+    with pytest.raises(TypeError):
+        nv.nvfp4_gemm(q, (q.codes, q.scales), Y=torch.empty((32, 32), device="cuda"))
+    with pytest.raises(nv.NVFP4Error):                                   # refused by the library, nothing launched
+        nv.nvfp4_gemm(q, nv.nvfp4_quantize(x[:, :32]), Y=torch.empty((32, 32), device="cuda"))
+    with pytest.raises(nv.NVFP4Error):
+        nv.nvfp4_quantize(x, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
+
+
 def test_quantize_is_deterministic():
     xb = wl.activation_with_outliers(512, 3072, 1, 0)
     x = dev_bf16(xb)
