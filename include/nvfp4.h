@@ -172,7 +172,7 @@ int nvfp4_quantize_2d(const void *w_bf16, int64_t R, int64_t C, int64_t ld,
  * operands produced by nvfp4_quantize with the matching block_axis.
  * K % 64 == 0 and N % 8 == 0 run on the tiled MFMA kernels at any M and N
  * (operands of 2 GiB and more are cut into row chunks, one set of launches per
- * chunk); other shapes (K % 16 == 0) run on a plain, much slower kernel.
+ * chunk); other shapes (K % 16 == 0) run on the 64x64 tile alone, at about half their rate.
  */
 int nvfp4_gemm(const nvfp4_tensor *A, const nvfp4_tensor *W, void *Y, int64_t ldy,
                int out_dtype, void *stream);
@@ -333,7 +333,7 @@ size_t nvfp4_workspace_bytes(int op, int64_t a, int64_t b, int64_t c);
 /* The kernel launches nvfp4_gemm (and the GEMM inside nvfp4_gemm_act_quant) issues
  * for an [M, K] x [N, K] problem, as text: one "BMxBN:workgroups" item per launch in
  * launch order, separated by spaces (tile shape and number of workgroups; "generic"
- * for shapes only the fallback kernel for odd shapes takes: about a third of the tiled rate).  The plan is this library's own
+ * for shapes that only the 64x64 tile takes: about half of the tiled rate).  The plan is this library's own
  * (a small cost model over its tile shapes and the 256 compute units): whole waves, or
  * whole tile rows, of large tiles, then the leftover rectangles on tiles that suit them.
  * Host pointers; nothing is launched.

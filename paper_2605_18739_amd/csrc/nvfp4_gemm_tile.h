@@ -8,13 +8,13 @@
 // per instruction) and one packed f16 multiply by the block scale
 // (v_cvt_scalef32_pk_f16_fp8 turns the E4M3 byte into f16).
 //
-// One tiled kernel, gemm_regdq_kernel, in four tile shapes (256x256 and 256x192 for the
-// bulk of a problem, 128x128 and 64x64 for small problems and the leftover rectangle of
-// a launch plan): the operands stay 4-bit through LDS (filled by buffer loads that write
-// LDS directly) and are expanded in registers in the shadow of the MFMAs that precede
-// their use.  gemm_edge_kernel (nvfp4_gemm.hip) takes the shapes the tiles cannot (K or N not a
-// multiple of 64 / 8).  plan_gemm picks tile shapes and splits a problem into whole waves
-// of large tiles plus the leftover on small ones.
+// One tiled kernel, gemm_regdq_kernel, in three tile shapes (256x256 and 256x192 for the
+// bulk of a problem, 128x128 for smaller ones and the leftover rectangle of a launch plan): the
+// operands stay 4-bit through LDS (filled by buffer loads that write LDS directly) and are
+// expanded in registers in the shadow of the MFMAs that precede their use.  The 64x64 tile, and
+// with it the shapes these cannot take (K or N not a multiple of 64 / 8), is gemm_split_kernel
+// (nvfp4_gemm_split.hip), whose waves cut K between them.  plan_gemm picks tile shapes and
+// splits a problem into whole waves of large tiles plus the leftover on small ones.
 //
 // Orientation: the MFMA's row operand is the W fragment and its column operand
 // the A fragment, so a lane ends up with ONE output row m and runs of four
@@ -670,7 +670,7 @@ static hipError_t launch_tile(int epi, const GemmArgs &g, int64_t tiles, hipStre
     }
 }
 
-// defined in nvfp4_gemm_tile_*.hip
+// defined in nvfp4_gemm_tile_*.hip and nvfp4_gemm_split.hip
 hipError_t launch_tile_256x256(int epi, const GemmArgs &g, int64_t tiles, hipStream_t s);
 hipError_t launch_tile_256x192(int epi, const GemmArgs &g, int64_t tiles, hipStream_t s);
 hipError_t launch_tile_128x128(int epi, const GemmArgs &g, int64_t tiles, hipStream_t s);

@@ -300,7 +300,7 @@ def test_binding_refuses_tensors_it_cannot_marshal():
         with pytest.raises(AssertionError):
             nv.nvfp4_kv_quant(bad, out=nv.NVFP4Tensor(32, 64))
     q = nv.nvfp4_quantize(x)
-    with pytest.raises(TypeError):
+    with pytest.raises((AttributeError, TypeError)):
         nv.nvfp4_gemm(q, (q.codes, q.scales), Y=torch.empty((32, 32), device="cuda"))
     with pytest.raises(nv.NVFP4Error):                                   # refused by the library, nothing launched
         nv.nvfp4_gemm(q, nv.nvfp4_quantize(x[:, :32]), Y=torch.empty((32, 32), device="cuda"))
@@ -392,6 +392,17 @@ def test_gemm_ragged_tiles(oracle, M, N, K):
     ab = wl.to_bf16_bits(g.standard_normal((M, K)).astype(np.float32))
     wb = wl.to_bf16_bits((g.standard_normal((N, K)) * 0.02).astype(np.float32))
     _gemm_case(oracle, ab, wb, f"ragged {M}x{N}x{K}")
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 8, 64), (63, 72, 128), (64, 64, 512), (65, 56, 576),       # whole units; 8 waves / 4 waves
+                                   (130, 136, 640), (70, 200, 1600),                                # 5 units; 12 and a half
+                                   (63, 68, 112), (33, 60, 144), (66, 132, 496), (40, 76, 1040)])   # scales off the dword grid, partial units
+def test_gemm_tile_that_cuts_k_between_its_waves(oracle, M, N, K):
+    g = np.random.default_rng(M * N + K)
+    assert nv.nvfp4_gemm_plan(M, N, K)[0][0] in ("64x64", "generic")
+    ab = wl.to_bf16_bits(g.standard_normal((M, K)).astype(np.float32))
+    wb = wl.to_bf16_bits((g.standard_normal((N, K)) * 0.02).astype(np.float32))
+    _gemm_case(oracle, ab, wb, f"K cut between waves {M}x{N}x{K}")
 
 
 def test_gemm_random_shapes(oracle):
