@@ -91,7 +91,7 @@ int quantize_impl(const void *x, int64_t R, int64_t C, int64_t ld, int block_axi
     uint32_t *partial = static_cast<uint32_t *>(ws);
     int n_partial = 0;
     if (!gs_in && block_axis == 0 && quantize_rows_resident_fits(R, C, ld, false) &&
-        quantize_rows_resident_pays(R * (C >> 4), scale_search)) {
+        quantize_rows_resident_pays(R * (C >> 4), scale_search, false)) {
         // the tensor fits on the chip (and is of a size at which that pays): one launch, one pass over the input
         hipError_t e = launch_quantize_rows_resident(xb, R, C, out->codes, out->scales, out->global_scale,
                                                      scale_search, nullptr, s);
@@ -207,7 +207,7 @@ int nvfp4_quantize_for_all_to_all(const void *x_bf16, int64_t T, int64_t H, int6
     const uint16_t *xb = static_cast<const uint16_t *>(x_bf16);
     uint32_t *partial = static_cast<uint32_t *>(workspace);
     int n_partial = 0;
-    if (!global_scale_in && quantize_rows_resident_fits(T * H, d, d, false) && quantize_rows_resident_pays(T * H * (d >> 4), false)) {
+    if (!global_scale_in && quantize_rows_resident_fits(T * H, d, d, false) && quantize_rows_resident_pays(T * H * (d >> 4), false, false)) {
         // small enough to stay on the chip between the maximum and the encoding: one launch
         hipError_t e1 = launch_quantize_rows_resident(xb, T * H, d, out->codes, out->scales, out->global_scale, false,
                                                       nullptr, s, (int)H, (int)(H / P));
@@ -295,7 +295,7 @@ int nvfp4_kv_quant_k(const void *k_bf16, int64_t T, int64_t H, int64_t d, nvfp4_
     uint16_t *mean = static_cast<uint16_t *>(row_mean_bf16_out);
     uint32_t *partial = static_cast<uint32_t *>(workspace);
     int n_partial = 0;
-    if (quantize_rows_resident_fits(T * H, d, d, true) && quantize_rows_resident_pays(T * H * (d >> 4), true)) {
+    if (quantize_rows_resident_fits(T * H, d, d, true) && quantize_rows_resident_pays(T * H * (d >> 4), true, true)) {
         hipError_t e = launch_quantize_rows_resident(x, T * H, d, out->codes, out->scales, out->global_scale, true,
                                                      mean, s);
         return e == hipSuccess ? NVFP4_OK : NVFP4_ERR_LAUNCH;

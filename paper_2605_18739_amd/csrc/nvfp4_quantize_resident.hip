@@ -363,20 +363,23 @@ bool quantize_rows_resident_fits(int64_t rows, int64_t C, int64_t ld, bool smoot
 }
 
 // Whether the one-launch form is taken for a tensor that fits.  It fetches the tensor once where the two passes
-// fetch it twice, but its encoding runs at two waves per SIMD where the streaming pass has six to eight, and
-// measured back to back on cache-like data: for the scale search and the smoothed keys, whose encoding is the
-// heavier, the two passes are faster at every size (by 7-14 % from 1 M blocks up to the largest tensor that
-// fits); for the plain rule they are faster by 5-11 % from about 0.5 M to 2.5 M blocks, below 0.4 M blocks the
-// one launch gains the second launch it does not make, and from 2.5 M blocks (80 MB) on the two forms take the
-// same time and the single fetch decides.  mode 1: whenever it fits; mode 2: never.
+// fetch it twice, but pays for the exchange across the grid, and its encoding runs at two waves per SIMD where the
+// streaming pass has six to eight.  Measured back to back (us, one launch / two passes, blocks of 16 elements):
+//   plain rule    1.5 k 5.3 / 6.1   19 k 6.6 / 6.2   192 k 9.6 / 6.6   676 k 13.2 / 12.6   887 k 14.2 / 14.7   1.7 M 21.3 / 23.0   3.5 M 34.6 / 42.7
+//   scale search                    19 k 9.1 / 8.1   192 k 13.1 / 9.2  676 k 22.1 / 18.6   1.7 M 34.1 / 32.0   2.6 M 41.6 / 43.7   3.5 M 54.5 / 56.7
+//   smoothed keys                   19 k 9.9 / 9.0   192 k 13.8 / 10.6 676 k 21.9 / 18.9   1.7 M 38.9 / 35.6   3.5 M 67.3 / 64.0
+// So: below 12 k blocks one launch where that saves the second launch, from there on two passes until the second
+// fetch costs more than the exchange, which is at 0.8 M blocks for the plain rule and 2.2 M with the search; smoothed
+// keys (whose first pass sums in fp64 either way) two passes throughout.  mode 1: whenever it fits; mode 2: never.
 static int g_one_launch_mode = 0;
 void set_one_launch_mode(int mode) { g_one_launch_mode = mode; }
-bool quantize_rows_resident_pays(int64_t nblk, bool search_or_smooth)
+bool quantize_rows_resident_pays(int64_t nblk, bool search, bool smooth)
 {
     if (g_one_launch_mode == 1) return true;
     if (g_one_launch_mode == 2) return false;
-    constexpr int64_t kSmall = 400000, kLarge = 2500000;
-    return !search_or_smooth && (nblk >= kLarge || nblk < kSmall);
+    constexpr int64_t kSmall = 12000, kLarge = 800000, kLargeSearch = 2200000;
+    if (smooth) return false;
+    return search ? nblk >= kLargeSearch : nblk < kSmall || nblk >= kLarge;
 }
 
 template <bool SEARCH, bool SMOOTH>
