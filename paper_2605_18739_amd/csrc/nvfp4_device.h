@@ -396,6 +396,48 @@ __device__ __forceinline__ void smooth_block16(uint32_t (&w)[8], float mu)
     for (int i = 0; i < 8; ++i) w[i] = pack_bf16x2(bf16lo_to_f32(w[i]) - mu, bf16hi_to_f32(w[i]) - mu);
 }
 
+// Mean of a row of d = 16 nb_row features (nb_row a power of two up to 64, one 16-element block per lane, the row's
+// lanes neighbours), rounded to bf16: RN_bf16(sum / d) of the exact sum.  Every lane of the wave calls this.
+// The sum is taken in fp32: 4 + log2(nb_row) <= 10 rounded levels, each off by at most 2^-24 of the sum of magnitudes, so
+// the mean lies within e = 10.1 * 2^-24 * (row maximum) of the exact one; where both ends of that interval round to the
+// same bf16 number, that is the mean.  Otherwise (one row in a few hundred, rows whose terms cancel, and rows that fp32
+// could overflow on) the wave takes the sum in fp64, which is exact for rows whose values span less than 2^40.
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v) { return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, true)); }
+__device__ __forceinline__ uint32_t row_mean_bits(const uint32_t (&w)[8], int nb_row)
+{
+    float f[16], s[16];
+    unpack16(w, f);
+    float mx = absmax16_tree(f);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = f[i];
+#pragma unroll
+    for (int h = 8; h > 0; h >>= 1)
+#pragma unroll
+        for (int i = 0; i < h; ++i) s[i] += s[i + h];
+    float sum = s[0];
+    // lane ^ 1, ^ 2 by quad permutations; ^ 4, ^ 8 by mirrors (the lanes of a half already agree); then shuffles
+    if (nb_row > 1) { sum += dpp_f32<0xB1>(sum); mx = fmaxf(mx, dpp_f32<0xB1>(mx)); }
+    if (nb_row > 2) { sum += dpp_f32<0x4E>(sum); mx = fmaxf(mx, dpp_f32<0x4E>(mx)); }
+    if (nb_row > 4) { sum += dpp_f32<0x141>(sum); mx = fmaxf(mx, dpp_f32<0x141>(mx)); }
+    if (nb_row > 8) { sum += dpp_f32<0x140>(sum); mx = fmaxf(mx, dpp_f32<0x140>(mx)); }
+    for (int m = 16; m < nb_row; m <<= 1) { sum += __shfl_xor(sum, m, 64); mx = fmaxf(mx, __shfl_xor(mx, m, 64)); }
+    const float mean = sum * (1.0f / (float)(16 * nb_row)) + 0.0f;           // (a power of two; a zero is +0)
+    const float e = 10.1f * 0x1p-24f * mx;
+    const uint32_t ends = pack_bf16x2(mean - e, mean + e);
+    uint32_t bits = ends & 0xFFFFu;
+    const bool sure = (bits == ends >> 16) & (mx < 0x1p110f);
+    if (__ballot(!sure) != 0ull) {
+        double d = 0.0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) d += (double)f[i];
+        for (int m = 1; m < nb_row; m <<= 1) d += __shfl_xor(d, m, 64);
+        const uint32_t exact = bf16_rne_signed_from_f64(d * (1.0 / (double)(16 * nb_row)));
+        bits = sure ? bits : exact;
+    }
+    return bits;
+}
+
 // Random Hadamard transform (Sec. 2.2, weight-gradient operands) of one group of 16 values
 // held as eight packed bf16 pairs: y = (1/4) H16 diag(s) v, H16[i][j] = (-1)^popcount(i & j),
 // s_j = -1 where bit j of sign_mask is set.  Fast Walsh-Hadamard butterflies in fp64 (exact

@@ -88,15 +88,7 @@ __device__ __forceinline__ uint32_t block_pass1(uint32_t (&w)[8], bool live, int
 {
     if constexpr (SMOOTH) {
         const int nb_row = 1 << a.row_shift;
-        double sum = 0.0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            sum += (double)bf16lo_to_f32(w[i]);
-            sum += (double)bf16hi_to_f32(w[i]);
-        }
-        for (int m = 1; m < nb_row; m <<= 1) sum += __shfl_xor(sum, m, 64);
-        const double inv_d = 1.0 / (double)(16 << a.row_shift);           // a power of two: the quotient is exact
-        const uint32_t mean_bits = bf16_rne_signed_from_f64(sum * inv_d);
+        const uint32_t mean_bits = row_mean_bits(w, nb_row);
         if (live) {
             if (WRITE_MEAN && (g & (nb_row - 1)) == 0) a.mean_out[g >> a.row_shift] = (uint16_t)mean_bits;
             smooth_block16(w, __uint_as_float(mean_bits << 16));
