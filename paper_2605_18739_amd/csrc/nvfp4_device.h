@@ -80,34 +80,44 @@ __device__ __forceinline__ _Float16 e4m3_to_f16(uint32_t b)
 }
 
 // ---- Four-over-Six scale search (Appendix "Scale Search NVFP4 Quantization", Eq. 12-13) ----
-// The squared error of a block under one encoding, as the fp64 definition evaluates it: every difference |x| - m s_b s_g taken
-// once in fp64, squared, and summed in element order, each operation rounded on its own (no
-// fused multiply-add), so that "is candidate 4 strictly better" has one answer everywhere.
-// (A rolled loop: the comparison of last resort is inlined wherever a block is searched and taken rarely, so it is written for
-// small code, not for speed.)
-__device__ __forceinline__ double block_error_f64(const uint32_t (&w)[8], uint32_t c0, uint32_t c1, float sb, float sg)
+// The squared errors of a block under two encodings, as the fp64 definition evaluates them: every difference x - m s_b s_g
+// (m signed like x) taken once in fp64, squared, and summed in element order, each operation rounded on its own (no fused
+// multiply-add), so that "is candidate 4 strictly better" has one answer everywhere.
+// Taken by a few blocks of every tensor (equal errors are common), and a launch ends with the slowest of its waves: the
+// two chains run side by side, unrolled (a rolled loop over the elements took 4 us, as long as the rest of a small call).
+__device__ __forceinline__ bool second_is_closer_f64(const uint32_t (&w)[8], const uint32_t (&ca)[2], const uint32_t (&cb)[2], float sba, float sbb, float sg)
 {
     // (under the default contraction mode the compiler fuses these into multiply-adds: one rounding where the
-    //  definition has two, and a different answer on blocks whose two errors are equal in exact arithmetic)
+    //  definition has two, and a different answer on blocks whose two errors are equal in exact arithmetic.  Plain
+    //  operators: contraction is switched off for this function; the rounding intrinsics are inlined with the
+    //  contraction mode of their own header and would be fused all the same)
 #pragma clang fp contract(off)
     typedef float float2v __attribute__((ext_vector_type(2)));
-    const double den = (double)sb * (double)sg;     // exact
-    double err = 0.0;
-#pragma unroll 1
-    for (uint32_t j = 0; j < 16; ++j) {
-        const bool odd = (j & 2u) != 0u, upper = (j & 4u) != 0u, second = (j & 8u) != 0u;
-        const uint32_t w01 = odd ? w[1] : w[0], w23 = odd ? w[3] : w[2], w45 = odd ? w[5] : w[4], w67 = odd ? w[7] : w[6];
-        const uint32_t wlo = upper ? w23 : w01, whi = upper ? w67 : w45;
-        const uint32_t ww = second ? whi : wlo;
-        const double a = (double)__uint_as_float((ww >> ((j & 1u) << 4) << 16) & 0x7FFF0000u);
-        const uint32_t idx = ((second ? c1 : c0) >> (4u * (j & 7u))) & 7u;
-        const float2v m = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(idx, 1.0f, 0);       // the code's magnitude, exact
-        const double prod = (double)m.x * den;            // (plain operators: contraction is switched off for this function;
-        const double d = a - prod;                         //  the rounding intrinsics are inlined with the contraction mode
-        const double sq = d * d;                           //  of their own header and would be fused all the same)
-        err = err + sq;
+    // (the codes are decoded anew: kept from the comparison before, the decoded values would cost the kernel 20 registers)
+    uint32_t a[2] = {ca[0], ca[1]}, b[2] = {cb[0], cb[1]};
+    asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(b[0]), "+v"(b[1]));
+    const double dena = (double)sba * (double)sg, denb = (double)sbb * (double)sg;      // exact
+    double ea = 0.0, eb = 0.0;
+    auto one = [&](float x, float ma, float mb) {
+#pragma clang fp contract(off)
+        const double pa = (double)ma * dena, pb = (double)mb * denb;
+        const double da = (double)x - pa, db = (double)x - pb;
+        const double qa = da * da, qb = db * db;
+        ea = ea + qa;
+        eb = eb + qb;
+    };
+#define NVFP4_STEP(K, SEL)                                                                       \
+    {                                                                                            \
+        const float2v ma = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(a[K >> 2], 1.0f, SEL);       \
+        const float2v mb = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(b[K >> 2], 1.0f, SEL);       \
+        one(bf16lo_to_f32(w[K]), ma.x, mb.x);                                                    \
+        one(bf16hi_to_f32(w[K]), ma.y, mb.y);                                                    \
+        __builtin_amdgcn_sched_barrier(0);      /* two elements at a time: more would cost waves their registers */ \
     }
-    return err;
+    NVFP4_STEP(0, 0) NVFP4_STEP(1, 1) NVFP4_STEP(2, 2) NVFP4_STEP(3, 3)
+    NVFP4_STEP(4, 0) NVFP4_STEP(5, 1) NVFP4_STEP(6, 2) NVFP4_STEP(7, 3)
+#undef NVFP4_STEP
+    return eb < ea;
 }
 
 // ---- tensor scales outside the range in which the fp32 quotients above are safe ----------------------
@@ -355,7 +365,7 @@ __device__ __forceinline__ void quantize_block16_4over6(const uint32_t (&w)[8], 
         pick4 = e4 + r4 < e6 - r6;
         const bool settled = !(fminf(e4, e6) < 0x1p-100f) & (pick4 | (e4 - r4 > e6 + r6));
         if (__builtin_expect(!settled, 0))
-            pick4 = block_error_f64(w, c[1][0], c[1][1], sb[1], t.sg) < block_error_f64(w, c[0][0], c[0][1], sb[0], t.sg);
+            pick4 = second_is_closer_f64(w, c[0], c[1], sb[0], sb[1], t.sg);
     }
     pick4 &= !same;
     sbyte = pick4 ? s[1] : s[0];

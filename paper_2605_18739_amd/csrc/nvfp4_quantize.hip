@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void scale_from_partials_kernel(const uint32_t
 // (what the pre-attention all-to-all of sequence-parallel inference sends to each peer).
 // --------------------------------------------------------------------------
 template <bool CONTIG, bool SEARCH = false, bool SMOOTH = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))   // at most 128 registers: four waves per SIMD
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SEARCH ? 8 : 4)))   // at most 64 / 128 registers
 void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
                                                             int64_t C, int64_t ld,
                                                             const float *__restrict__ gs_in,
