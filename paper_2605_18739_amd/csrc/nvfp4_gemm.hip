@@ -8,54 +8,54 @@ namespace nvfp4 {
 
 // ============================================================================
 // Down projection of the LoRA side branch: T [M, 128] = bf16(X A^T), X [M, K] and A [128, K]
-// bf16, fp32 accumulation on v_mfma_f32_32x32x16_bf16.  A skinny GEMM: with whole-K tiles
-// either few workgroups run or every one of them pulls all of A through its compute unit, and
-// a compute unit pulls only ~30-60 GB/s at the latency of one step in flight.  So K is cut:
-// workgroup (i, s) multiplies rows 128 i .. 128 i + 127 with K range s of `splits` (64-k steps
-// staged in LDS with full-line coalesced loads, one step ahead; 2 x 2 waves of 64 x 64), writes
-// an fp32 partial tile to the workspace, and a second small kernel adds the partial tiles in
-// split order and rounds to bf16.
+// bf16, fp32 accumulation on v_mfma_f32_32x32x16_bf16.  A skinny GEMM, bound by latency and by what a compute unit
+// pulls: with whole-K tiles either few workgroups run or every one of them pulls all of A.  So K is cut:
+// workgroup (i, s) multiplies rows 128 i .. 128 i + 127 with K range s of `splits` (2 x 2 waves of 64 x 64), writes
+// an fp32 partial tile to the workspace, and a second small kernel adds the partial tiles in split order and rounds to
+// bf16.  The 64-k steps of a range are copied straight into a ring of four LDS stages, so that most of a range (six steps
+// of the 3520x3072 projection) is under way at once: 17.7 us for that
+// projection, both kernels, with one step at a time through registers; 14.7 now (128x3072: 12.2 -> 7.7).
 // ============================================================================
 constexpr int kLdRows = 128;                                      // rows of X per workgroup
+constexpr int kLdStages = 4, kLdStageBytes = (kLdRows + kLoraRank) * ROW_BYTES;      // 32 KB
+static __device__ __align__(16) uint8_t g_zeros[16];              // what chunks past the end of K are copied from
 __global__ __launch_bounds__(256) void lora_down_partial_kernel(const uint16_t *__restrict__ x, int64_t M,
                                                                 int64_t K, int64_t ldx,
                                                                 const uint16_t *__restrict__ a, int steps_per_split,
                                                                 float *__restrict__ partial, int64_t m_pad)
 {
+#if defined(__HIP_DEVICE_COMPILE__)
     typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
+    typedef __attribute__((address_space(3))) void *lds_ptr_t;
+    typedef const __attribute__((address_space(1))) void *global_ptr_t;
     constexpr int ROWS = kLdRows + kLoraRank;                     // staged rows: X rows first, then A rows
-    constexpr int STAGE = ROWS * ROW_BYTES;                       // 32 KB
-    constexpr int CHUNKS = ROWS * 8 / 256;                        // 16-byte chunks per thread and step
+    constexpr int UPW = ROWS / 8 / 4;                             // copy instructions per wave and step: eight rows each
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const int lrow = lane & 31, lhalf = lane >> 5;
     const int64_t m0 = (int64_t)blockIdx.x * kLdRows;
     const int step0 = blockIdx.y * steps_per_split;
     const int ksteps_all = (int)((K + 63) >> 6);                  // the last step may be partly past K (K % 16 == 0)
     const int nsteps = min(steps_per_split, ksteps_all - step0);
-    // this thread's chunks: q = tid + 256 i -> staged row q / 8, chunk q % 8
-    const uint16_t *src[CHUNKS];
-    int dst[CHUNKS], kc[CHUNKS];
+    // lane l of unit u copies row 8 u + l / 8, the chunk whose slot (lds_chunk_off) is l % 8
+    const uint16_t *src[UPW];
+    int kc[UPW];
 #pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) {
-        const int q = tid + 256 * i, row = q >> 3, c = q & 7;
-        src[i] = row < kLdRows ? x + min(m0 + row, M - 1) * ldx + 8 * c     // rows past the end repeat the last one (never used)
-                               : a + (int64_t)(row - kLdRows) * K + 8 * c;
-        dst[i] = lds_chunk_off(row, c);
+    for (int i = 0; i < UPW; ++i) {
+        const int row = 8 * (wave + 4 * i) + (lane >> 3), c = (lane & 7) ^ swz_key(row);
+        src[i] = (row < kLdRows ? x + min(m0 + row, M - 1) * ldx              // rows past the end repeat the last one (never used)
+                                : a + (int64_t)(row - kLdRows) * K) + 8 * c;
         kc[i] = 8 * c;
     }
-    uint4v regs[CHUNKS];
-    auto fetch = [&](int step) {
+    auto copy = [&](int step) {
 #pragma unroll
-        for (int i = 0; i < CHUNKS; ++i) {
-            const int64_t k = (int64_t)step * 64 + kc[i];
-            regs[i] = k < K ? *(const uint4v *)(src[i] + (int64_t)step * 64) : uint4v{0u, 0u, 0u, 0u};
+        for (int i = 0; i < UPW; ++i) {
+            const int64_t k = (int64_t)(step0 + step) * 64;
+            const void *p = k + kc[i] < K ? (const void *)(src[i] + k) : (const void *)g_zeros;
+            __builtin_amdgcn_global_load_lds((global_ptr_t)p, (lds_ptr_t)(lds + (step & (kLdStages - 1)) * kLdStageBytes + (wave + 4 * i) * 1024), 16, 0, 0);
         }
-    };
-    auto stage = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < CHUNKS; ++i) *(uint4v *)(lds + buf * STAGE + dst[i]) = regs[i];
     };
     float16v acc[2][2];                                           // [column tile][row tile] of this wave's 64 x 64
 #pragma unroll
@@ -64,23 +64,25 @@ __global__ __launch_bounds__(256) void lora_down_partial_kernel(const uint16_t *
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[c][j][r] = 0.0f;
-    if (nsteps > 0) {
-        fetch(step0);
-        stage(0);
-    }
-    __syncthreads();
+    for (int st = 0; st < min(nsteps, kLdStages - 1); ++st) copy(st);
     for (int st = 0; st < nsteps; ++st) {
-        const int buf = st & 1;
-        if (st + 1 < nsteps) fetch(step0 + st + 1);
+        // this wave's copies of step st have landed when at most those of the steps behind it are outstanding
+        const int behind = min(nsteps - 1, st + kLdStages - 2) - st;
+        if (behind >= 2) wait_vmcnt_le<2 * UPW>();
+        else if (behind == 1) wait_vmcnt_le<UPW>();
+        else wait_vmcnt_le<0>();
+        NVFP4_COMPILER_FENCE();
+        __builtin_amdgcn_s_barrier();               // step st is in LDS, and every wave has read step st - 1
+        NVFP4_COMPILER_FENCE();
+        if (st + kLdStages - 1 < nsteps) copy(st + kLdStages - 1);
+        const uint8_t *stage = lds + (st & (kLdStages - 1)) * kLdStageBytes;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
             uint4v fx[2], fa[2];
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-                fx[j] = *(const uint4v *)(lds + buf * STAGE + lds_chunk_off(64 * wm + 32 * j + lrow, 2 * kk + lhalf));
+            for (int j = 0; j < 2; ++j) fx[j] = *(const uint4v *)(stage + lds_chunk_off(64 * wm + 32 * j + lrow, 2 * kk + lhalf));
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
-                fa[c] = *(const uint4v *)(lds + buf * STAGE + lds_chunk_off(kLdRows + 64 * wn + 32 * c + lrow, 2 * kk + lhalf));
+            for (int c = 0; c < 2; ++c) fa[c] = *(const uint4v *)(stage + lds_chunk_off(kLdRows + 64 * wn + 32 * c + lrow, 2 * kk + lhalf));
 #pragma unroll
             for (int c = 0; c < 2; ++c)
 #pragma unroll
@@ -88,21 +90,28 @@ __global__ __launch_bounds__(256) void lora_down_partial_kernel(const uint16_t *
                     acc[c][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8v, fa[c]),
                                                                         __builtin_bit_cast(bf16x8v, fx[j]), acc[c][j], 0, 0, 0);
         }
-        if (st + 1 < nsteps) stage(buf ^ 1);         // the other stage was last read before the previous barrier
-        __syncthreads();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // (this wave's reads of the stage, before the next barrier)
     }
-    // lane = output row, register r = column 8 (r / 4) + 4 lhalf + r % 4 of the 32-column tile
-    float *pp = partial + ((int64_t)blockIdx.y * m_pad + m0) * kLoraRank;
+    // lane = output row, register r = column 8 (r / 4) + 4 lhalf + r % 4 of the 32-column tile: transposed through LDS, so
+    // that a wave stores four whole 256-byte runs at a time and not thirty-two of 32 bytes
+    __syncthreads();
+    float4v *slab = (float4v *)(lds + wave * 16384);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int row = 64 * wm + 32 * j + lrow;
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                *(float4v *)(pp + (int64_t)row * kLoraRank + 64 * wn + 32 * c + 8 * q + 4 * lhalf) =
+                slab[(32 * j + lrow) * 16 + ((8 * c + 2 * q + lhalf) ^ (lrow & 15))] =
                     float4v{acc[c][j][4 * q], acc[c][j][4 * q + 1], acc[c][j][4 * q + 2], acc[c][j][4 * q + 3]};
+    NVFP4_COMPILER_FENCE();                       // (a wave reads its own slab)
+    float *pp = partial + ((int64_t)blockIdx.y * m_pad + m0 + 64 * wm) * kLoraRank + 64 * wn;
+#pragma unroll
+    for (int p = 0; p < 16; ++p) {
+        const int row = 4 * p + (lane >> 4), c4 = lane & 15;
+        *(float4v *)(pp + (int64_t)row * kLoraRank + 4 * c4) = slab[row * 16 + (c4 ^ (row & 15))];
     }
+#endif
 }
 
 // T = bf16(sum over the splits, in split order)
@@ -111,8 +120,15 @@ __global__ __launch_bounds__(256) void lora_down_reduce_kernel(const float *__re
 {
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;           // four consecutive columns of one row
     if (i >= M * kLoraRank) return;
-    float4v sum = *(const float4v *)(partial + i);
-    for (int s = 1; s < splits; ++s) sum += *(const float4v *)(partial + (int64_t)s * m_pad * kLoraRank + i);
+    constexpr int kMost = 16;                                                    // (lora_down_plan makes no more ranges)
+    float4v p[kMost];                                                           // all loads in flight together
+#pragma unroll
+    for (int s = 0; s < kMost; ++s)
+        if (s < splits) p[s] = *(const float4v *)(partial + (int64_t)s * m_pad * kLoraRank + i);
+    float4v sum = p[0];
+#pragma unroll
+    for (int s = 1; s < kMost; ++s)
+        if (s < splits) sum += p[s];
     *(uint2v *)(t + i) = uint2v{pack_bf16x2(sum.x, sum.y), pack_bf16x2(sum.z, sum.w)};
 }
 
@@ -175,6 +191,8 @@ hipError_t launch_gemm(const uint8_t *codesA, const uint8_t *scalesA, const floa
         const int kind = ep.out_dtype != 0 ? (kEpiBF16 | (ep.act == 1 ? kEpiGelu : 0)) : kEpiF32;
         return launch_tile_64x64(kind, g, ((M + 63) / 64) * ((N + 63) / 64), s);
     }
+    if (with_lora && lora_takes_64(M, N, K))
+        return launch_tile_64x64((ep.out_dtype != 0 ? kEpiBF16 : kEpiF32) | kEpiLora, g, ((M + 63) / 64) * ((N + 63) / 64), s);
     // (the tiled fp32 output never carries an activation: nvfp4_gemm has none and the fused call emits bf16)
     const int out_kind = ep.q_scale ? kEpiQuant : (ep.out_dtype != 0 ? kEpiBF16 : kEpiF32);
     const int epi = out_kind | ((ep.act == 1 && out_kind != kEpiF32) ? kEpiGelu : 0);
@@ -239,8 +257,17 @@ hipError_t launch_lora_down(const uint16_t *x, int64_t M, int64_t K, int64_t ldx
     int64_t m_pad;
     lora_down_plan(M, K, &splits, &sps, &m_pad);
     dim3 grid((unsigned)(m_pad / kLdRows), (unsigned)splits);
-    lora_down_partial_kernel<<<grid, 256, 2 * (kLdRows + kLoraRank) * ROW_BYTES, s>>>(x, M, K, ldx, a, sps, workspace, m_pad);
-    hipError_t e = hipGetLastError();
+    constexpr int smem = kLdStages * kLdStageBytes;
+    static uint64_t attr_set = 0;              // the dynamic LDS limit is raised once per device
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess && ((attr_set >> (dev & 63)) & 1u) == 0) {
+        e = hipFuncSetAttribute((const void *)lora_down_partial_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        if (e == hipSuccess) attr_set |= 1ull << (dev & 63);
+    }
+    if (e != hipSuccess) return e;
+    lora_down_partial_kernel<<<grid, 256, smem, s>>>(x, M, K, ldx, a, sps, workspace, m_pad);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     lora_down_reduce_kernel<<<(unsigned)((M * kLoraRank / 4 + 255) / 256), 256, 0, s>>>(workspace, splits, m_pad, M, t);
     return hipGetLastError();

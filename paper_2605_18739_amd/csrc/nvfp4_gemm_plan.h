@@ -49,7 +49,7 @@ static double small_cost(int64_t M, int64_t N, int64_t K, TileKind kind)
     return c.base + waves * (c.wave + steps * c.step) + (double)tiles / kCUs * (c.tile + steps * c.fill);
 }
 
-// big_only: only the 256-row tile shapes (the kernels that can carry the LoRA phase)
+// big_only: only the 256-row tile shapes (the planned kernels that can carry the LoRA phase)
 static TileKind choose_tile(int64_t M, int64_t N, int64_t K, double *cost = nullptr, bool big_only = false)
 {
     // order of preference on ties: the larger tile
@@ -66,6 +66,14 @@ static TileKind choose_tile(int64_t M, int64_t N, int64_t K, double *cost = null
     }
     if (cost) *cost = cbest;
     return best;
+}
+
+// A small problem with a LoRA phase: one launch of 64x64 tiles (the kernel that cuts K between its waves carries the phase
+// as well) where that is cheaper than 256-row tiles: 128x3072x3072 takes 12 us instead of 49, 400x1024x1024 8 instead of 23.
+static bool lora_takes_64(int64_t M, int64_t N, int64_t K)
+{
+    if (!small_problem(M, N)) return false;
+    return small_cost(M, N, K, kTile64) < std::min(small_cost(M, N, K, kTile256x256), small_cost(M, N, K, kTile256x192));
 }
 
 // A launch plan: the main launch runs whole waves of tiles (in row-major tile

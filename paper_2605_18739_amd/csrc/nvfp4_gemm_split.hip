@@ -27,7 +27,7 @@ template <int EPI_ACT, int NW, int STAGES, bool ODD>
 __global__ __launch_bounds__(NW * 64, 2) void gemm_split_kernel(GemmArgs g)
 {
     constexpr int EPI = EPI_ACT & 3;
-    constexpr bool GELU = (EPI_ACT & kEpiGelu) != 0;
+    constexpr bool GELU = (EPI_ACT & kEpiGelu) != 0, LORA = (EPI_ACT & kEpiLora) != 0;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -171,6 +171,35 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_split_kernel(GemmArgs g)
     static_for<0, STAGES>([&](auto st) {
         if (wave + decltype(st)::value * NW < full) copy(wave + decltype(st)::value * NW, st);
     });
+    if constexpr (LORA) {
+        // the low-rank update T B^T, on the wave whose turn the next unit would be, scaled so that the epilogue's one
+        // multiplication by alpha leaves lora_scale T B^T (rank 128: sixteen consecutive k per matrix instruction)
+        if (units % NW == wave) {
+            typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
+            const uint16_t *lp[4];
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+                lp[f] = (f < 2 ? g.lora_t + min(m0 + 32 * f + lrow, g.M - 1) * kLoraRank : g.lora_b + min(n0 + 32 * (f - 2) + lrow, g.N - 1) * kLoraRank) + 8 * lhalf;
+#pragma unroll
+            for (int k = 0; k < kLoraRank / 16; ++k) {
+                uint4v v[4];
+#pragma unroll
+                for (int f = 0; f < 4; ++f) v[f] = *(const uint4v *)(lp[f] + 16 * k);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8v, v[2 + i]), __builtin_bit_cast(bf16x8v, v[j]), acc[i][j], 0, 0, 0);
+            }
+            const float rescale = g.lora_scale / alpha;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[i][j][r] *= rescale;
+        }
+    }
     if (rest != 0 && full % NW == wave) {
         Unit x;
         load_rest(x);
@@ -197,7 +226,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_split_kernel(GemmArgs g)
     // in register 4 q + e, column 8 q + 4 lhalf + e of a W fragment: four consecutive columns per 16-byte granule.
     // Granule (row, c4 = column / 4) of wave w lies at  w * 16 KB + c4 * 1 KB + (row with its low bits XOR c4) * 16 B:
     // what a wave writes at a time (32 rows of one c4) and what sixteen lanes read at a time (one row) fall on distinct banks.
-    const int used = min(NW, units);
+    const int used = min(NW, units + (LORA ? 1 : 0));
     float4v *slab = (float4v *)lds;
     if (wave < used) {
 #pragma unroll
@@ -321,6 +350,9 @@ static hipError_t launch_split_epi(int epi, const GemmArgs &g, int64_t tiles, hi
     // (re-quantizing epilogues: planned problems only, K % 64 == 0)
     case kEpiQuant: return odd ? hipErrorInvalidValue : launch_split<kEpiQuant, NW, STAGES, false>(g, tiles, s);
     case kEpiQuant | kEpiGelu: return odd ? hipErrorInvalidValue : launch_split<kEpiQuant | kEpiGelu, NW, STAGES, false>(g, tiles, s);
+    // (planned problems only as well)
+    case kEpiF32 | kEpiLora: return odd ? hipErrorInvalidValue : launch_split<kEpiF32 | kEpiLora, NW, STAGES, false>(g, tiles, s);
+    case kEpiBF16 | kEpiLora: return odd ? hipErrorInvalidValue : launch_split<kEpiBF16 | kEpiLora, NW, STAGES, false>(g, tiles, s);
     default: return hipErrorInvalidValue;
     }
 }

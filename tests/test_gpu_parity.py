@@ -659,6 +659,12 @@ def test_gemm_lora_small_and_ragged(oracle):
     _lora_case(oracle, 520, 400, 320, 2.0, "256x192 tiles")
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 8, 64), (65, 72, 128), (40, 264, 448), (130, 200, 512),     # the phase on wave 1, 1, 4, 4 of eight
+                                   (63, 136, 576), (100, 80, 1024), (70, 64, 2112)])                # wave 1, 0, 1 of four; long K
+def test_gemm_lora_on_the_tile_that_cuts_k_between_its_waves(oracle, M, N, K):
+    _lora_case(oracle, M, N, K, 0.7, f"lora, K cut between waves {M}x{N}x{K}")
+
+
 def test_gemm_lora_projection_shape(oracle):
     """The DiT projection with its adapter (rank 128, alpha 128): sampled rows against the oracle."""
     M = wl.TOKENS_INFER
