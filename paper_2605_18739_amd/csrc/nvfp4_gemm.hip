@@ -222,7 +222,10 @@ hipError_t launch_gemm(const uint8_t *codesA, const uint8_t *scalesA, const floa
                 a.lora_t = lora.t + m_lo * kLoraRank;
                 a.lora_b = lora.b + n_lo * kLoraRank;
             }
-            err = launch_kind(p.kind, epi | (with_lora ? kEpiLora : 0), a, p.tiles, s);
+            // a leftover rectangle (every launch but the first tiles one completely) of a LoRA plan, which knows 256-row tiles
+            // only, takes 64x64 tiles where those are cheaper (3520x14336x3072: 312 -> 276 us)
+            if (with_lora && i > 0 && lora_takes_64(a.M, a.N, K)) err = launch_tile_64x64(epi | kEpiLora, a, ((a.M + 63) / 64) * ((a.N + 63) / 64), s);
+            else err = launch_kind(p.kind, epi | (with_lora ? kEpiLora : 0), a, p.tiles, s);
             wg_total += (int)p.tiles;
         }
     });
