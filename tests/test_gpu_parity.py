@@ -665,6 +665,13 @@ def test_gemm_lora_on_the_tile_that_cuts_k_between_its_waves(oracle, M, N, K):
     _lora_case(oracle, M, N, K, 0.7, f"lora, K cut between waves {M}x{N}x{K}")
 
 
+def test_gemm_lora_leftover_rectangle(oracle):
+    """18 x 17 tiles of 256x256: one whole wave, and a rectangle of leftover rows on 64x64 tiles; ragged both ways."""
+    M, N = 4500, 4104
+    rows = np.unique(np.concatenate([np.random.default_rng(3).integers(0, M, 60), [0, 3839, 3840, 4095, 4096, M - 1]])).astype(np.int64)
+    _lora_case(oracle, M, N, 64, 0.5, "lora leftover rectangle", rows=rows)
+
+
 def test_gemm_lora_projection_shape(oracle):
     """The DiT projection with its adapter (rank 128, alpha 128): sampled rows against the oracle."""
     M = wl.TOKENS_INFER
