@@ -132,7 +132,7 @@ def main():
     up_ms = sum(up_all) / max(len(up_all), 1)
     achieved = flops_gemm / (up_ms * 1e-3) / 1e12
     traffic, traffic_note = profile_traffic()
-    plan = " + ".join(f"gemm_regdq_kernel<{t},bf16+gelu> ({n} tiles)" for t, n in nv.nvfp4_gemm_plan(M, F, D))
+    plan = " + ".join(f"{'gemm_split_kernel' if t == '64x64' else 'gemm_regdq_kernel'}<{t},bf16+gelu> ({n} tiles)" for t, n in nv.nvfp4_gemm_plan(M, F, D))
     roofline = {"bound": "mfma", "kernel": f"up projection {M}x{F}x{D}, f16 MFMA: {plan}",
                 "achieved": round(achieved, 1), "peak": PEAK_MFMA_F16_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_MFMA_F16_TFLOPS, 4), "traffic": traffic, "traffic_source": traffic_note,
