@@ -665,6 +665,17 @@ def test_gemm_lora_on_the_tile_that_cuts_k_between_its_waves(oracle, M, N, K):
     _lora_case(oracle, M, N, K, 0.7, f"lora, K cut between waves {M}x{N}x{K}")
 
 
+@pytest.mark.parametrize("M,K", [(1, 16), (127, 48), (130, 208), (300, 272), (129, 1040)])     # ranges that end inside a 64-k step
+def test_lora_down_partial_steps(oracle, M, K):
+    xb, ab = wl.normal((M, K), 1.0, M, K), wl.normal((nv.LORA_RANK, K), 0.02, M, K + 1)
+    x = torch.full((M, K + 8), float("nan"), dtype=torch.bfloat16, device="cuda")             # what lies behind a row is not read as part of it
+    x[:, :K] = dev_bf16(xb)
+    tv = wl.bf16_bits_to_f32(nv.bits_from_bf16(nv.nvfp4_lora_down(x[:, :K], dev_bf16(ab)))).astype(np.float64)
+    wv = wl.bf16_bits_to_f32(oracle.lora_down(xb, ab)).astype(np.float64)
+    bound = np.abs(wl.bf16_bits_to_f32(xb)).astype(np.float64) @ np.abs(wl.bf16_bits_to_f32(ab)).astype(np.float64).T
+    assert (np.abs(tv - wv) <= 2.0 ** -7 * np.abs(wv) + 2.0 ** -15 * bound).all()              # one bf16 step and the fp32 sums
+
+
 def test_gemm_lora_leftover_rectangle(oracle):
     """18 x 17 tiles of 256x256: one whole wave, and a rectangle of leftover rows on 64x64 tiles; ragged both ways."""
     M, N = 4500, 4104
