@@ -382,7 +382,6 @@ int nvfp4_gemm_scale_out(const nvfp4_tensor *A, const nvfp4_tensor *W, void *Y_b
     if (int rc = check_gemm(A, W)) return rc;
     const int64_t M = A->rows, N = W->rows;
     if (ldy < N) return NVFP4_ERR_SHAPE;
-    const bool tiled = gemm_is_tiled(M, N, A->K);
     if (!aligned16(Y_bf16) || (ldy & 7) != 0 || (reinterpret_cast<uintptr_t>(y_global_scale_out) & 3u)) return NVFP4_ERR_ALIGN;
     if (!workspace || workspace_bytes < fused_partial_bytes(M, N)) return NVFP4_ERR_WORKSPACE;
     if (!aligned16(workspace)) return NVFP4_ERR_ALIGN;
@@ -395,16 +394,12 @@ int nvfp4_gemm_scale_out(const nvfp4_tensor *A, const nvfp4_tensor *W, void *Y_b
     ep.act = NVFP4_ACT_NONE;
     ep.Y = Y_bf16;
     ep.ldy = ldy;
-    ep.stream_out = tiled && streams_out(M, N, NVFP4_OUT_BF16);
-    ep.amax_partial = tiled ? partial : nullptr;        // the tiled kernels' epilogue leaves one maximum per workgroup
+    ep.stream_out = streams_out(M, N, NVFP4_OUT_BF16);
+    ep.amax_partial = partial;                          // the epilogue leaves one maximum per workgroup, whatever the shape
     int n_partial = 0;
     if (launch_gemm(A->codes, A->scales, A->global_scale, W->codes, W->scales, W->global_scale, M, N, A->K, ep,
                     &n_partial, s) != hipSuccess)
         return NVFP4_ERR_LAUNCH;
-    if (n_partial == 0) {                               // odd shape: the fallback kernel has no such epilogue, one pass over Y
-        if (launch_amax(static_cast<const uint16_t *>(Y_bf16), M, N, ldy, partial, &n_partial, s) != hipSuccess)
-            return NVFP4_ERR_LAUNCH;
-    }
     return launch_scale_from_partials(partial, n_partial, y_global_scale_out, s) == hipSuccess ? NVFP4_OK : NVFP4_ERR_LAUNCH;
 }
 
@@ -507,7 +502,7 @@ int nvfp4_gemm_act_quant(const nvfp4_tensor *A, const nvfp4_tensor *W, int act,
             return NVFP4_ERR_LAUNCH;
     }
     int n_partial = n_wg;
-    if (!global_scale_in && n_wg == 0) {   // shape went to the untiled kernel: ordinary amax pass over H
+    if (!global_scale_in && !tiled) {      // 64x64 tiles throughout: too many maxima for every workgroup to reduce, one pass over H (N % 16 == 0)
         if (launch_amax(H, M, N, N, partial, &n_partial, s) != hipSuccess) return NVFP4_ERR_LAUNCH;
     }
     hipError_t e = launch_quantize_rows(H, M, N, N, global_scale_in, partial, n_partial, out->codes,
@@ -537,8 +532,8 @@ size_t nvfp4_workspace_bytes(int op, int64_t a, int64_t b, int64_t c)
         // the GEMM tiles (hence the number of per-workgroup maxima) depend on K, which this query
         // does not know: reserve for the smallest tile everywhere
         size_t part = fused_partial_bytes(a, b);
-        // with a given scale the fused epilogue needs no staging of H -- unless the shape falls back
-        // to the untiled kernel (K % 64 != 0 or N % 8 != 0), which this query cannot see either:
+        // with a given scale the fused epilogue needs no staging of H -- unless the shape is one that only
+        // the 64x64 tile takes (K % 64 != 0 or N % 8 != 0), which this query cannot see either:
         // only skip the H area when N is a multiple of 16 and leave K to the caller's contract
         const bool need_h = !(c & 1) && !((c & 2) && (b & 15) == 0);
         return part + (need_h ? align_up((size_t)a * (size_t)b * 2, 256) : 0);

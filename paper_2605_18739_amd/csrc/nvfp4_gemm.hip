@@ -187,9 +187,10 @@ hipError_t launch_gemm(const uint8_t *codesA, const uint8_t *scalesA, const floa
     const bool with_lora = lora.t != nullptr;
     if (!tiled_ok(M, N, K)) {                            // an odd shape: 64x64 tiles throughout
         if (with_lora) return hipErrorInvalidValue;      // (no LoRA phase there; callers check gemm_is_tiled)
-        if (n_wg) *n_wg = 0;
+        const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
+        if (n_wg) *n_wg = (int)tiles;
         const int kind = ep.out_dtype != 0 ? (kEpiBF16 | (ep.act == 1 ? kEpiGelu : 0)) : kEpiF32;
-        return launch_tile_64x64(kind, g, ((M + 63) / 64) * ((N + 63) / 64), s);
+        return launch_tile_64x64(kind, g, tiles, s);
     }
     if (with_lora && lora_takes_64(M, N, K))
         return launch_tile_64x64((ep.out_dtype != 0 ? kEpiBF16 : kEpiF32) | kEpiLora, g, ((M + 63) / 64) * ((N + 63) / 64), s);

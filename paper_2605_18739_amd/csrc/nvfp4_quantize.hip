@@ -138,11 +138,12 @@ __device__ __forceinline__ float resolve_global_scale(const float *gs_in, const 
 
 // The tensor scale alone, from partial maxima that something else produced (a GEMM epilogue, an amax pass): one
 // workgroup, one float.  What a later quantizer call takes as its given scale.
-__global__ __launch_bounds__(256) void scale_from_partials_kernel(const uint32_t *__restrict__ partial, int n_partial,
-                                                                  float *__restrict__ gs_out)
+// (1024 threads: a GEMM that runs on 64x64 tiles alone leaves up to tens of thousands of maxima)
+__global__ __launch_bounds__(1024) void scale_from_partials_kernel(const uint32_t *__restrict__ partial, int n_partial,
+                                                                   float *__restrict__ gs_out)
 {
-    __shared__ uint32_t lds4[4];
-    (void)resolve_global_scale(nullptr, partial, n_partial, gs_out, lds4);
+    __shared__ uint32_t lds16[16];
+    (void)resolve_global_scale(nullptr, partial, n_partial, gs_out, lds16);
 }
 
 // --------------------------------------------------------------------------
@@ -806,7 +807,7 @@ hipError_t launch_amax(const uint16_t *x, int64_t R, int64_t C, int64_t ld, uint
 
 hipError_t launch_scale_from_partials(const uint32_t *partial, int n_partial, float *gs_out, hipStream_t s)
 {
-    scale_from_partials_kernel<<<1, 256, 0, s>>>(partial, n_partial, gs_out);
+    scale_from_partials_kernel<<<1, 1024, 0, s>>>(partial, n_partial, gs_out);
     return hipGetLastError();
 }
 

@@ -1075,6 +1075,26 @@ def test_gemm_scale_out_feeds_the_given_scale_quantizers(oracle, M, N, K):
                        oracle.quantize(yb[:Mt], block_axis=1, global_scale_in=float(want_gs)), "columns, given scale")
 
 
+@pytest.mark.parametrize("M,N,K", [(33, 4, 128), (100, 12, 64), (70, 3076, 96), (65, 67, 80), (1, 1, 16)])
+def test_gemm_scale_out_sees_the_columns_behind_the_last_whole_vector(oracle, M, N, K):
+    """Widths that are no multiple of 8 in a padded Y, the largest value in the last column: Y and its scale as always,
+    the padding left alone."""
+    g = np.random.default_rng(M + N + K)
+    w = g.standard_normal((N, K)) * 0.02
+    w[-1] *= 50.0
+    ga = nv.nvfp4_quantize(dev_bf16(wl.to_bf16_bits(g.standard_normal((M, K)).astype(np.float32))))
+    gw = nv.nvfp4_quantize(dev_bf16(wl.to_bf16_bits(w.astype(np.float32))))
+    y = torch.full((M, (N + 7) // 8 * 8 + 8), -7.0, dtype=torch.bfloat16, device="cuda")
+    _, scale = nv.nvfp4_gemm_scale_out(ga, gw, Y=y[:, :N])
+    ref = torch.full_like(y, -7.0)
+    nv.nvfp4_gemm(ga, gw, nv.OUT_BF16, Y=ref[:, :N])
+    yb = nv.bits_from_bf16(y)
+    assert (yb == nv.bits_from_bf16(ref)).all() and bool((y[:, N:] == -7.0).all())
+    assert int(y[:, :N].float().abs().max(0).values.argmax()) == N - 1
+    want = oracle.global_scale(np.ascontiguousarray(yb[:, :N]))
+    assert np.float32(scale.item()).view(np.uint32) == np.float32(want).view(np.uint32)
+
+
 # -------------------------------------------------------- full benchmark sizes
 
 def test_full_size_projection_config2(oracle):
