@@ -110,13 +110,20 @@ struct Workspace {
     size_t size() const { return (size_t)t.numel(); }
 };
 
+// the library may wait for a lock: not under the GIL, which is taken again however the call ends (what torch throws
+// while the arguments of the call are put together becomes a Python error)
+struct WithoutGil {
+    PyThreadState *saved = PyEval_SaveThread();
+    ~WithoutGil() { PyEval_RestoreThread(saved); }
+};
 template <class F>
-PyObject *status(F &&call)                                          // the library may wait for a lock: not under the GIL
+PyObject *status(F &&call)
 {
     int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = call();
-    Py_END_ALLOW_THREADS
+    {
+        WithoutGil released;
+        rc = call();
+    }
     return PyLong_FromLong(rc);
 }
 

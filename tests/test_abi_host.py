@@ -3,13 +3,16 @@ symbol the header declares, and rejects bad arguments before launching anything.
 import ctypes
 import os
 import re
+import types
 
 import numpy as np
 import pytest
+import torch
 
 import paper_2605_18739_amd as nv
 from paper_2605_18739_amd.binding import _CTensor
 
+NO_STREAM = types.SimpleNamespace(cuda_stream=0)      # host checks come before anything is launched
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -240,3 +243,12 @@ def test_binding_fails_loudly_without_the_library(monkeypatch):
     monkeypatch.setattr(binding, "_LIB_PATH", "/nonexistent/libnvfp4_hip.so")
     with pytest.raises(binding.NVFP4Error):
         binding.lib()
+
+
+def test_torch_errors_of_the_marshalling_reach_python():
+    """Y.stride(0) of a Y without dimensions throws inside the call, where the GIL is released."""
+    q = nv.NVFP4Tensor(16, 64, "cpu")
+    for call in (lambda Y: nv.nvfp4_gemm(q, q, Y=Y, stream=NO_STREAM),
+                 lambda Y: nv.nvfp4_gemm_scale_out(q, q, Y=Y, scale_out=q.global_scale, workspace=q.codes, stream=NO_STREAM)):
+        with pytest.raises(IndexError):
+            call(torch.zeros(()))
