@@ -61,7 +61,8 @@ PyObject *attribute(PyObject *o, PyObject *name)                    // (borrowed
     return a;
 }
 
-// An NVFP4Tensor; holds references, so the buffers live through the call whatever other threads do to the object
+// An NVFP4Tensor; holds references, so the buffers live through the call whatever other threads do to the object (what
+// stands in the argument list itself is held by the caller)
 struct Quantized {
     nvfp4_tensor t{};
     at::Tensor codes, scales, global_scale;
@@ -254,23 +255,29 @@ PyObject *kv_dequant(PyObject *const *a)                            // q, T, H, 
 }
 PyObject *kv_dequant_gather(PyObject *const *a)                     // [(q, row_mean or None, T), ...], H, d, out, stream
 {
-    PyObject *seq = PySequence_Fast(a[0], "chunks is a list of (NVFP4Tensor, row_mean or None, T)");
-    if (!seq) throw Fail();
-    struct Drop {
+    // tuples of our own: a list may change under the call (attributes are read on the way, and the GIL is released)
+    struct Owned {
         PyObject *o;
-        ~Drop() { Py_DECREF(o); }
-    } drop{seq};
-    const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
+        explicit Owned(PyObject *sequence) : o(PySequence_Tuple(sequence))
+        {
+            if (!o) throw Fail();
+        }
+        Owned(const Owned &) = delete;
+        ~Owned() { Py_DECREF(o); }
+    } seq(a[0]);
+    const Py_ssize_t n = PyTuple_GET_SIZE(seq.o);
     std::vector<nvfp4_kv_chunk> chunks((size_t)n);
     std::vector<Quantized> keep;
+    std::vector<at::Tensor> keep_means;
     keep.reserve((size_t)n);
+    keep_means.reserve((size_t)n);
     for (Py_ssize_t i = 0; i < n; ++i) {
-        PyObject *c = PySequence_Fast(PySequence_Fast_GET_ITEM(seq, i), "a chunk is (NVFP4Tensor, row_mean or None, T)");
-        if (!c) throw Fail();
-        Drop dc{c};
-        if (PySequence_Fast_GET_SIZE(c) != 3) fail(PyExc_ValueError, "a chunk is (NVFP4Tensor, row_mean or None, T)");
-        keep.emplace_back(PySequence_Fast_GET_ITEM(c, 0));
-        chunks[(size_t)i] = {keep.back().t, address(PySequence_Fast_GET_ITEM(c, 1)), number(PySequence_Fast_GET_ITEM(c, 2))};
+        const Owned c(PyTuple_GET_ITEM(seq.o, i));
+        if (PyTuple_GET_SIZE(c.o) != 3) fail(PyExc_ValueError, "a chunk is (NVFP4Tensor, row_mean or None, T)");
+        PyObject *mean = PyTuple_GET_ITEM(c.o, 1);
+        keep.emplace_back(PyTuple_GET_ITEM(c.o, 0));
+        if (mean != Py_None) keep_means.push_back(tensor(mean));
+        chunks[(size_t)i] = {keep.back().t, address(mean), number(PyTuple_GET_ITEM(c.o, 2))};
     }
     const int64_t H = number(a[1]), d = number(a[2]);
     void *out = address(a[3]), *s = stream_of(a[4]);

@@ -4,6 +4,7 @@ import ctypes
 import os
 import re
 import types
+import weakref
 
 import numpy as np
 import pytest
@@ -252,3 +253,29 @@ def test_torch_errors_of_the_marshalling_reach_python():
                  lambda Y: nv.nvfp4_gemm_scale_out(q, q, Y=Y, scale_out=q.global_scale, workspace=q.codes, stream=NO_STREAM)):
         with pytest.raises(IndexError):
             call(torch.zeros(()))
+
+
+def test_gather_holds_the_row_means_of_a_list_that_changes_during_the_call():
+    q = nv.NVFP4Tensor(16, 64, "cpu")
+    means = np.zeros(16, np.int16)
+    alive = weakref.ref(means)
+    chunks = [(q, torch.from_numpy(means).view(torch.bfloat16), 1)]
+    del means
+    seen = []
+
+    class Last(nv.NVFP4Tensor):                        # its K is read after the first chunk's pointers were taken
+        @property
+        def K(self):
+            chunks[0] = None
+            seen.append(alive() is not None)
+            return 64
+
+        @K.setter
+        def K(self, value):
+            pass
+
+    chunks.append((Last(16, 64, "cpu"), None, 1))
+    del seen[:]
+    with pytest.raises(nv.NVFP4Error):                 # (16 rows are not one token of 8 heads)
+        nv.nvfp4_kv_dequant_gather(chunks, 8, 64, out=torch.empty((2, 8, 64), dtype=torch.bfloat16), stream=NO_STREAM)
+    assert seen == [True]
