@@ -170,10 +170,16 @@ def _ptr(t):
     return ctypes.c_void_p(t.data_ptr()) if t is not None else None
 
 
+def _sizes(x, rank):
+    """The sizes that an output is allocated by; everything else about x is checked by the native call."""
+    assert x.dim() == rank, f"expected a tensor of {rank} dimensions, got {x.dim()}"
+    return x.shape
+
+
 def nvfp4_quantize(x, block_axis=0, global_scale_in=None, out=None, workspace=None, stream=None):
     """x: bf16 [R, C] device tensor with unit stride along C. Returns an NVFP4Tensor."""
     if out is None:
-        R, C = x.shape
+        R, C = _sizes(x, 2)
         out = NVFP4Tensor(R, C, x.device) if block_axis == 0 else NVFP4Tensor(C, R, x.device)
     _check(_host().quantize(x, block_axis, global_scale_in, out, workspace, _stream(stream)))
     return out
@@ -199,7 +205,7 @@ def nvfp4_gemm_scale_out(A, W, Y=None, scale_out=None, workspace=None, stream=No
 def nvfp4_lora_down(x, a, out=None, workspace=None, stream=None):
     """T = bf16(x a^T): x bf16 [M, K] (unit stride along K), a bf16 [128, K] contiguous."""
     if out is None:
-        out = _host().output(x, x.shape[0], LORA_RANK, True)
+        out = _host().output(x, _sizes(x, 2)[0], LORA_RANK, True)
     _check(_host().lora_down(x, a, out, workspace, _stream(stream)))
     return out
 
@@ -221,7 +227,7 @@ def nvfp4_gemm_act_quant(A, W, act=ACT_GELU_TANH, global_scale_in=None, out=None
 
 
 def _heads_out(x):
-    T, H, d = x.shape
+    T, H, d = _sizes(x, 3)
     return NVFP4Tensor(T * H, d, x.device)
 
 
@@ -242,7 +248,7 @@ def nvfp4_kv_quant_noalloc(kv, out, stream=None):
 def nvfp4_quantize_4over6(x, global_scale_in=None, out=None, workspace=None, stream=None):
     """x: bf16 [R, C] device tensor with unit stride along C; blocks along C, scale search per block."""
     if out is None:
-        R, C = x.shape
+        R, C = _sizes(x, 2)
         out = NVFP4Tensor(R, C, x.device)
     _check(_host().quantize_4over6(x, global_scale_in, out, workspace, _stream(stream)))
     return out
@@ -268,7 +274,7 @@ def nvfp4_quantize_rht(x, sign_mask, global_scale_in=None, out=None, workspace=N
     """x: bf16 [R, C], contracted over R.  Random Hadamard transform along R (groups of 16) with the
     16-bit sign mask, then the transposed quantizer: returns NVFP4Tensor [C, R]."""
     if out is None:
-        R, C = x.shape
+        R, C = _sizes(x, 2)
         out = NVFP4Tensor(C, R, x.device)
     _check(_host().quantize_rht(x, int(sign_mask), global_scale_in, out, workspace, _stream(stream)))
     return out
@@ -277,7 +283,7 @@ def nvfp4_quantize_rht(x, sign_mask, global_scale_in=None, out=None, workspace=N
 def nvfp4_quantize_2d(w, global_scale_in=None, transposed=True, workspace=None, stream=None):
     """w: bf16 [R, C] weights (R, C multiples of 16), one scale per 16x16 tile.
     Returns (NVFP4Tensor [R, C], NVFP4Tensor [C, R] or None)."""
-    R, C = w.shape
+    R, C = _sizes(w, 2)
     out = NVFP4Tensor(R, C, w.device)
     out_t = NVFP4Tensor(C, R, w.device) if transposed else None
     _check(_host().quantize_2d(w, global_scale_in, out, out_t, workspace, _stream(stream)))
@@ -289,7 +295,8 @@ def nvfp4_kv_quant_k(k, out=None, row_mean=None, workspace=None, stream=None):
     if out is None:
         out = _heads_out(k)
     if row_mean is None:
-        row_mean = torch.empty(k.shape[0] * k.shape[1], dtype=torch.bfloat16, device=k.device)
+        T, H, _ = _sizes(k, 3)
+        row_mean = torch.empty(T * H, dtype=torch.bfloat16, device=k.device)
     _check(_host().kv_quant_k(k, out, row_mean, workspace, _stream(stream)))
     return out, row_mean
 

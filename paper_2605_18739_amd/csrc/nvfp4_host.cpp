@@ -266,7 +266,7 @@ PyObject *kv_dequant_gather(PyObject *const *a)                     // [(q, row_
         ~Owned() { Py_DECREF(o); }
     } seq(a[0]);
     const Py_ssize_t n = PyTuple_GET_SIZE(seq.o);
-    std::vector<nvfp4_kv_chunk> chunks((size_t)n);
+    std::vector<nvfp4_kv_chunk> chunks((size_t)std::max<Py_ssize_t>(n, 1));     // (an empty list is refused for its size, not as a null pointer)
     std::vector<Quantized> keep;
     std::vector<at::Tensor> keep_means;
     keep.reserve((size_t)n);

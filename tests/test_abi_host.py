@@ -279,3 +279,21 @@ def test_gather_holds_the_row_means_of_a_list_that_changes_during_the_call():
     with pytest.raises(nv.NVFP4Error):                 # (16 rows are not one token of 8 heads)
         nv.nvfp4_kv_dequant_gather(chunks, 8, 64, out=torch.empty((2, 8, 64), dtype=torch.bfloat16), stream=NO_STREAM)
     assert seen == [True]
+
+
+@pytest.mark.parametrize("rank", [0, 1, 2, 3, 4])
+def test_tensors_of_the_wrong_rank_are_refused_before_an_output_is_allocated(rank):
+    x = torch.zeros((16,) * rank, dtype=torch.bfloat16)
+    calls = {2: [nv.nvfp4_quantize, nv.nvfp4_quantize_4over6, nv.nvfp4_quantize_2d, lambda x, **kw: nv.nvfp4_quantize_rht(x, 1, **kw),
+                 lambda x, **kw: nv.nvfp4_lora_down(x, torch.zeros((128, 16), dtype=torch.bfloat16), **kw)],
+             3: [nv.nvfp4_kv_quant, nv.nvfp4_kv_quant_4over6, nv.nvfp4_kv_quant_k, lambda x, **kw: nv.nvfp4_quantize_for_all_to_all(x, 2, **kw),
+                 lambda x, **kw: nv.nvfp4_kv_quant_k(x, out=nv.NVFP4Tensor(16, 16, "cpu"), **kw)]}
+    for wanted, entries in calls.items():
+        for entry in entries if wanted != rank else []:
+            with pytest.raises(AssertionError):
+                entry(x, stream=NO_STREAM)
+
+
+def test_gather_of_no_chunks_is_refused_for_its_size():
+    with pytest.raises(nv.NVFP4Error, match="status -2"):
+        nv.nvfp4_kv_dequant_gather([], 8, 64, out=torch.empty((1, 8, 64), dtype=torch.bfloat16), stream=NO_STREAM)
