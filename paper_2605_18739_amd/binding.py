@@ -137,6 +137,27 @@ def _stream(stream=None):
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
+def _elsewhere(stream):
+    """Whether `stream` is another one than torch's current stream."""
+    return stream.cuda_stream != (_stream() if torch.cuda.is_initialized() else 0)
+
+
+def _on(stream, call, *args):
+    """The call with `stream` as torch's current stream.  What it allocates comes from that stream's pool: a block of
+    the current stream's pool may still be in use by work queued there, and a workspace would go back to that pool while
+    `stream` still uses it.  New outputs are noted as used by the caller's stream too, which is where they are read."""
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream)
+    here = torch.cuda.current_stream(stream.device)
+    with torch.cuda.stream(stream):
+        result = call(*args)
+    for new in result if isinstance(result, tuple) else (result,):
+        if new is not None and not any(new is a for a in args):
+            for t in (new.codes, new.scales, new.global_scale) if isinstance(new, NVFP4Tensor) else (new,):
+                t.record_stream(here)
+    return result
+
+
 class NVFP4Tensor:
     """Device NVFP4 tensor: codes [rows, K/2] u8, scales [rows, K/16] u8, global_scale [1] f32."""
 
@@ -178,6 +199,8 @@ def _sizes(x, rank):
 
 def nvfp4_quantize(x, block_axis=0, global_scale_in=None, out=None, workspace=None, stream=None):
     """x: bf16 [R, C] device tensor with unit stride along C. Returns an NVFP4Tensor."""
+    if stream is not None and (out is None or workspace is None) and _elsewhere(stream):
+        return _on(stream, nvfp4_quantize, x, block_axis, global_scale_in, out, workspace)
     if out is None:
         R, C = _sizes(x, 2)
         out = NVFP4Tensor(R, C, x.device) if block_axis == 0 else NVFP4Tensor(C, R, x.device)
@@ -186,6 +209,8 @@ def nvfp4_quantize(x, block_axis=0, global_scale_in=None, out=None, workspace=No
 
 
 def nvfp4_gemm(A, W, out_dtype=OUT_F32, Y=None, stream=None):
+    if stream is not None and Y is None and _elsewhere(stream):
+        return _on(stream, nvfp4_gemm, A, W, out_dtype, Y)
     if Y is None:
         Y = _host().output(A.codes, A.rows, W.rows, out_dtype != OUT_F32)
     _check(_host().gemm(A, W, out_dtype, Y, _stream(stream)))
@@ -194,6 +219,8 @@ def nvfp4_gemm(A, W, out_dtype=OUT_F32, Y=None, stream=None):
 
 def nvfp4_gemm_scale_out(A, W, Y=None, scale_out=None, workspace=None, stream=None):
     """bf16 Y = A W^T together with the NVFP4 tensor scale of Y (one float on the device).  Returns (Y, scale_out)."""
+    if stream is not None and (Y is None or scale_out is None or workspace is None) and _elsewhere(stream):
+        return _on(stream, nvfp4_gemm_scale_out, A, W, Y, scale_out, workspace)
     if Y is None:
         Y = _host().output(A.codes, A.rows, W.rows, True)
     if scale_out is None:
@@ -204,6 +231,8 @@ def nvfp4_gemm_scale_out(A, W, Y=None, scale_out=None, workspace=None, stream=No
 
 def nvfp4_lora_down(x, a, out=None, workspace=None, stream=None):
     """T = bf16(x a^T): x bf16 [M, K] (unit stride along K), a bf16 [128, K] contiguous."""
+    if stream is not None and (out is None or workspace is None) and _elsewhere(stream):
+        return _on(stream, nvfp4_lora_down, x, a, out, workspace)
     if out is None:
         out = _host().output(x, _sizes(x, 2)[0], LORA_RANK, True)
     _check(_host().lora_down(x, a, out, workspace, _stream(stream)))
@@ -212,6 +241,8 @@ def nvfp4_lora_down(x, a, out=None, workspace=None, stream=None):
 
 def nvfp4_gemm_lora(A, W, t, b, lora_scale, out_dtype=OUT_F32, Y=None, stream=None):
     """nvfp4_gemm(A, W) + lora_scale * t b^T, fused; t bf16 [M, 128], b bf16 [N, 128], both contiguous."""
+    if stream is not None and Y is None and _elsewhere(stream):
+        return _on(stream, nvfp4_gemm_lora, A, W, t, b, lora_scale, out_dtype, Y)
     if Y is None:
         Y = _host().output(A.codes, A.rows, W.rows, out_dtype != OUT_F32)
     _check(_host().gemm_lora(A, W, t, b, lora_scale, out_dtype, Y, _stream(stream)))
@@ -220,6 +251,8 @@ def nvfp4_gemm_lora(A, W, t, b, lora_scale, out_dtype=OUT_F32, Y=None, stream=No
 
 def nvfp4_gemm_act_quant(A, W, act=ACT_GELU_TANH, global_scale_in=None, out=None, h_bf16=None,
                          workspace=None, stream=None):
+    if stream is not None and (out is None or workspace is None) and _elsewhere(stream):
+        return _on(stream, nvfp4_gemm_act_quant, A, W, act, global_scale_in, out, h_bf16, workspace)
     if out is None:
         out = NVFP4Tensor(A.rows, W.rows, A.codes.device)
     _check(_host().gemm_act_quant(A, W, act, global_scale_in, out, h_bf16, workspace, _stream(stream)))
@@ -233,6 +266,8 @@ def _heads_out(x):
 
 def nvfp4_kv_quant(kv, out=None, workspace=None, stream=None):
     """kv: contiguous bf16 [T, H, d]."""
+    if stream is not None and (out is None or workspace is None) and _elsewhere(stream):
+        return _on(stream, nvfp4_kv_quant, kv, out, workspace)
     if out is None:
         out = _heads_out(kv)
     _check(_host().kv_quant(kv, out, workspace, _stream(stream)))
@@ -247,6 +282,8 @@ def nvfp4_kv_quant_noalloc(kv, out, stream=None):
 
 def nvfp4_quantize_4over6(x, global_scale_in=None, out=None, workspace=None, stream=None):
     """x: bf16 [R, C] device tensor with unit stride along C; blocks along C, scale search per block."""
+    if stream is not None and (out is None or workspace is None) and _elsewhere(stream):
+        return _on(stream, nvfp4_quantize_4over6, x, global_scale_in, out, workspace)
     if out is None:
         R, C = _sizes(x, 2)
         out = NVFP4Tensor(R, C, x.device)
@@ -256,6 +293,8 @@ def nvfp4_quantize_4over6(x, global_scale_in=None, out=None, workspace=None, str
 
 def nvfp4_kv_quant_4over6(kv, out=None, workspace=None, stream=None):
     """kv: contiguous bf16 [T, H, d]; scale search per block."""
+    if stream is not None and (out is None or workspace is None) and _elsewhere(stream):
+        return _on(stream, nvfp4_kv_quant_4over6, kv, out, workspace)
     if out is None:
         out = _heads_out(kv)
     _check(_host().kv_quant_4over6(kv, out, workspace, _stream(stream)))
@@ -264,6 +303,8 @@ def nvfp4_kv_quant_4over6(kv, out=None, workspace=None, stream=None):
 
 def nvfp4_quantize_for_all_to_all(x, P, global_scale_in=None, out=None, workspace=None, stream=None):
     """x: contiguous bf16 [T, H, d]; NVFP4 along d, rows regrouped into P per-destination slabs of H/P heads."""
+    if stream is not None and (out is None or workspace is None) and _elsewhere(stream):
+        return _on(stream, nvfp4_quantize_for_all_to_all, x, P, global_scale_in, out, workspace)
     if out is None:
         out = _heads_out(x)
     _check(_host().quantize_for_all_to_all(x, P, global_scale_in, out, workspace, _stream(stream)))
@@ -273,6 +314,8 @@ def nvfp4_quantize_for_all_to_all(x, P, global_scale_in=None, out=None, workspac
 def nvfp4_quantize_rht(x, sign_mask, global_scale_in=None, out=None, workspace=None, stream=None):
     """x: bf16 [R, C], contracted over R.  Random Hadamard transform along R (groups of 16) with the
     16-bit sign mask, then the transposed quantizer: returns NVFP4Tensor [C, R]."""
+    if stream is not None and (out is None or workspace is None) and _elsewhere(stream):
+        return _on(stream, nvfp4_quantize_rht, x, sign_mask, global_scale_in, out, workspace)
     if out is None:
         R, C = _sizes(x, 2)
         out = NVFP4Tensor(C, R, x.device)
@@ -283,6 +326,8 @@ def nvfp4_quantize_rht(x, sign_mask, global_scale_in=None, out=None, workspace=N
 def nvfp4_quantize_2d(w, global_scale_in=None, transposed=True, workspace=None, stream=None):
     """w: bf16 [R, C] weights (R, C multiples of 16), one scale per 16x16 tile.
     Returns (NVFP4Tensor [R, C], NVFP4Tensor [C, R] or None)."""
+    if stream is not None and _elsewhere(stream):
+        return _on(stream, nvfp4_quantize_2d, w, global_scale_in, transposed, workspace)
     R, C = _sizes(w, 2)
     out = NVFP4Tensor(R, C, w.device)
     out_t = NVFP4Tensor(C, R, w.device) if transposed else None
@@ -292,6 +337,8 @@ def nvfp4_quantize_2d(w, global_scale_in=None, transposed=True, workspace=None, 
 
 def nvfp4_kv_quant_k(k, out=None, row_mean=None, workspace=None, stream=None):
     """k: contiguous bf16 [T, H, d] keys; K-smoothing then scale search.  Returns (NVFP4Tensor, row means bf16 [T*H])."""
+    if stream is not None and (out is None or row_mean is None or workspace is None) and _elsewhere(stream):
+        return _on(stream, nvfp4_kv_quant_k, k, out, row_mean, workspace)
     if out is None:
         out = _heads_out(k)
     if row_mean is None:
@@ -303,6 +350,8 @@ def nvfp4_kv_quant_k(k, out=None, row_mean=None, workspace=None, stream=None):
 
 def nvfp4_kv_dequant_gather(chunks, H, d, out=None, stream=None):
     """chunks: list of (NVFP4Tensor, row_mean or None, T).  Returns bf16 [sum T, H, d]."""
+    if stream is not None and out is None and _elsewhere(stream):
+        return _on(stream, nvfp4_kv_dequant_gather, chunks, H, d, out)
     if out is None:
         out = torch.empty((sum(T for _, _, T in chunks), H, d), dtype=torch.bfloat16, device=chunks[0][0].codes.device)
     _check(_host().kv_dequant_gather(chunks, H, d, out, _stream(stream)))
@@ -310,6 +359,8 @@ def nvfp4_kv_dequant_gather(chunks, H, d, out=None, stream=None):
 
 
 def nvfp4_kv_dequant(q, T, H, d, out=None, stream=None):
+    if stream is not None and out is None and _elsewhere(stream):
+        return _on(stream, nvfp4_kv_dequant, q, T, H, d, out)
     if out is None:
         out = torch.empty((T, H, d), dtype=torch.bfloat16, device=q.codes.device)
     _check(_host().kv_dequant(q, T, H, d, out, _stream(stream)))

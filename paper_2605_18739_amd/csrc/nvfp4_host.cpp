@@ -98,8 +98,8 @@ private:
 
 at::Tensor bytes_on(const at::Device &device, int64_t n) { return at::empty({n}, at::TensorOptions().device(device).dtype(at::kByte)); }
 
-// the caller's workspace, or one for this call: freed to torch's caching allocator when the call returns, behind the
-// launches on the current stream
+// the caller's workspace, or one for this call: from the current stream's pool, and back to it when the call returns,
+// behind the launches.  So the stream of a call without a workspace is torch's current one (binding.py sees to it).
 struct Workspace {
     at::Tensor t;
     Workspace(PyObject *given, const at::Device &device, int op, int64_t a, int64_t b, int64_t c = 0)

@@ -1,5 +1,7 @@
 """GPU parity: the HIP library (through its C ABI) against the CPU oracle, element by
 element, on seeded inputs that span several tiles and ragged tails."""
+import types
+
 import numpy as np
 import pytest
 import torch
@@ -306,6 +308,57 @@ def test_binding_refuses_tensors_it_cannot_marshal():
         nv.nvfp4_gemm(q, nv.nvfp4_quantize(x[:, :32]), Y=torch.empty((32, 32), device="cuda"))
     with pytest.raises(nv.NVFP4Error):
         nv.nvfp4_quantize(x, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
+
+
+def _pool_of(t):
+    """The stream whose pool a tensor's memory belongs to."""
+    return next(s["stream"] for s in torch.cuda.memory_snapshot() if s["address"] <= t.data_ptr() < s["address"] + s["total_size"])
+
+
+def test_calls_on_another_stream_allocate_from_its_pool():
+    """stream= another stream than the current one: outputs and workspaces come from that stream's pool (no block that
+    the current stream still uses, none that it is handed back too early), the results are the same, and the current
+    stream stays what it is.  With buffers given, or with the current stream itself, nothing changes pools."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    x = torch.randn((256, 512), generator=g, device="cuda").to(torch.bfloat16)
+    kv = x.view(256, 4, 128)
+    a, b = x[:128].contiguous(), torch.randn((256, 128), generator=g, device="cuda").to(torch.bfloat16)
+    q = nv.nvfp4_quantize(x)
+    t = nv.nvfp4_lora_down(x, a)
+    qk, mean = nv.nvfp4_kv_quant_k(kv)
+    calls = [lambda **kw: nv.nvfp4_quantize(x, **kw), lambda **kw: nv.nvfp4_quantize(x, block_axis=1, **kw), lambda **kw: nv.nvfp4_gemm(q, q, **kw),
+             lambda **kw: nv.nvfp4_gemm_scale_out(q, q, **kw), lambda **kw: nv.nvfp4_lora_down(x, a, **kw), lambda **kw: nv.nvfp4_gemm_lora(q, q, t, b, 0.5, **kw),
+             lambda **kw: nv.nvfp4_gemm_act_quant(q, q, **kw), lambda **kw: nv.nvfp4_kv_quant(kv, **kw), lambda **kw: nv.nvfp4_quantize_4over6(x, **kw),
+             lambda **kw: nv.nvfp4_kv_quant_4over6(kv, **kw), lambda **kw: nv.nvfp4_quantize_for_all_to_all(kv, 2, **kw),
+             lambda **kw: nv.nvfp4_quantize_rht(x, 0x5A3C, **kw), lambda **kw: nv.nvfp4_quantize_2d(x, **kw), lambda **kw: nv.nvfp4_kv_quant_k(kv, **kw),
+             lambda **kw: nv.nvfp4_kv_dequant_gather([(qk, mean, 256)], 4, 128, **kw), lambda **kw: nv.nvfp4_kv_dequant(q, 256, 1, 512, **kw)]
+
+    def tensors(result):
+        flat = result if isinstance(result, tuple) else (result,)
+        return [u for r in flat for u in ((r.codes, r.scales, r.global_scale) if isinstance(r, nv.NVFP4Tensor) else (r,))]
+
+    torch.cuda.synchronize()
+    here, side = torch.cuda.current_stream(), torch.cuda.Stream()
+    assert side.cuda_stream != here.cuda_stream
+    for call in calls:
+        want = tensors(call(stream=here))
+        got = tensors(call(stream=side))
+        raw = tensors(call(stream=types.SimpleNamespace(cuda_stream=side.cuda_stream)))     # anything that names a stream
+        assert torch.cuda.current_stream() == here
+        assert {_pool_of(u) for u in want} == {here.cuda_stream} and {_pool_of(u) for u in got + raw} == {side.cuda_stream}
+        torch.cuda.synchronize()
+        for u, v, w in zip(want, got, raw):
+            assert torch.equal(u.view(torch.uint8), v.view(torch.uint8)) and torch.equal(u.view(torch.uint8), w.view(torch.uint8))
+    # only the workspace is missing: it comes from the other stream's pool as well
+    out = nv.NVFP4Tensor(512, 256, "cuda")
+    size = nv.nvfp4_workspace_bytes(nv.OP_QUANTIZE, 256, 512)
+    fresh = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    assert nv.nvfp4_quantize(x, block_axis=1, out=out, stream=fresh) is out
+    assert sum(s["total_size"] for s in torch.cuda.memory_snapshot() if s["stream"] == fresh.cuda_stream) >= size
+    assert _pool_of(out.codes) == here.cuda_stream
+    torch.cuda.synchronize()
 
 
 def test_quantize_is_deterministic():
