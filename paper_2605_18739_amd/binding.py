@@ -4,19 +4,22 @@ Function names mirror the C ABI in include/nvfp4.h.  torch supplies device
 memory and the current stream; every step of the path runs in the library's
 kernels.  The calls that launch work take their pointers and allocate what the
 caller does not pass in native code (csrc/nvfp4_host.cpp); lib() is the C ABI
-itself, through ctypes.  There is no CPU fallback: if a shared library is
-missing, importing this module's entry points raises.
+itself, through ctypes, and needs neither this torch nor this Python.  There is
+no CPU fallback: if a shared library is missing, or the native code was built
+with another torch, the entry points raise.
 """
 import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import re
+import sysconfig
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libnvfp4_hip.so")
-_HOST_PATH = os.path.join(_HERE, "_host.so")
+_HOST_PATH = os.path.join(_HERE, "_host" + sysconfig.get_config_var("EXT_SUFFIX"))
 _lib = None
 _host_module = None
 
@@ -123,8 +126,16 @@ def _host():
         if not os.path.exists(_HOST_PATH):
             raise NVFP4Error(f"{_HOST_PATH} is missing: build it with `python -m paper_2605_18739_amd.build`")
         loader = importlib.machinery.ExtensionFileLoader("_host", _HOST_PATH)
-        _host_module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_host", loader))
-        loader.exec_module(_host_module)
+        try:
+            module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_host", loader))
+            loader.exec_module(module)
+        except ImportError as e:
+            raise NVFP4Error(f"{_HOST_PATH} does not load with torch {torch.__version__} ({e}): build it again") from e
+        # torch's C++ interface changes from release to release, and not every change shows when the symbols are bound
+        if module.torch_version != re.match(r"\d+(\.\d+)*", torch.__version__).group():
+            raise NVFP4Error(f"{_HOST_PATH} was built with torch {module.torch_version}, this is torch {torch.__version__}: "
+                             "build it again with `python -m paper_2605_18739_amd.build`")
+        _host_module = module
     return _host_module
 
 

@@ -2,7 +2,7 @@
 
 Every source is compiled to an object of its own, side by side (the GEMM tile shapes are separate
 translation units for this), and the objects are linked into libnvfp4_hip.so next to this file.
-The binding's host code (_host.so, against torch's headers) is compiled beside them and linked to it."""
+The binding's host code (_host.*.so, against torch's and Python's headers) is compiled beside them and linked to it."""
 import os
 import subprocess
 import sys
@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libnvfp4_hip.so")
-HOST = os.path.join(HERE, "_host.so")
+HOST = os.path.join(HERE, "_host" + sysconfig.get_config_var("EXT_SUFFIX"))       # (tied to this Python by its name, to this torch by a check)
 SOURCES = ["nvfp4_gemm_tile_256x256.hip", "nvfp4_gemm_tile_256x192.hip", "nvfp4_gemm_tile_128x128.hip",
            "nvfp4_gemm_split.hip", "nvfp4_quantize.hip", "nvfp4_quantize_resident.hip", "nvfp4_gemm.hip", "nvfp4_probe.hip", "nvfp4_api.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

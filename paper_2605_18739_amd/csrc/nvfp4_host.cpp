@@ -12,6 +12,7 @@
 #include <torch/csrc/Device.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <algorithm>
 #include <vector>
@@ -376,5 +377,10 @@ extern "C" PyObject *PyInit__host(void)
     s_global_scale = PyUnicode_InternFromString("global_scale");
     s_rows = PyUnicode_InternFromString("rows");
     s_K = PyUnicode_InternFromString("K");
-    return PyModule_Create(&module);
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
 }

@@ -13,9 +13,9 @@ def pytest_configure(config):
 
 
 def pytest_sessionstart(session):
-    """The tests load the library that is built in-tree; it is compiled here only when there is none."""
+    """The tests load the library that is built in-tree; it is compiled here only when something is missing."""
     from paper_2605_18739_amd import build as hip_build
-    if not os.path.exists(hip_build.LIB):
+    if not (os.path.exists(hip_build.LIB) and os.path.exists(hip_build.HOST)):
         hip_build.build(verbose=False)
 
 

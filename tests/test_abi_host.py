@@ -3,6 +3,7 @@ symbol the header declares, and rejects bad arguments before launching anything.
 import ctypes
 import os
 import re
+import sysconfig
 import types
 import weakref
 
@@ -11,6 +12,7 @@ import pytest
 import torch
 
 import paper_2605_18739_amd as nv
+from paper_2605_18739_amd import binding
 from paper_2605_18739_amd.binding import _CTensor
 
 NO_STREAM = types.SimpleNamespace(cuda_stream=0)      # host checks come before anything is launched
@@ -297,3 +299,13 @@ def test_tensors_of_the_wrong_rank_are_refused_before_an_output_is_allocated(ran
 def test_gather_of_no_chunks_is_refused_for_its_size():
     with pytest.raises(nv.NVFP4Error, match="status -2"):
         nv.nvfp4_kv_dequant_gather([], 8, 64, out=torch.empty((1, 8, 64), dtype=torch.bfloat16), stream=NO_STREAM)
+
+
+def test_native_code_built_with_another_torch_is_refused(monkeypatch):
+    assert torch.__version__.startswith(binding._host().torch_version)
+    assert os.path.basename(binding._HOST_PATH) == "_host" + sysconfig.get_config_var("EXT_SUFFIX")
+    monkeypatch.setattr(binding, "_host_module", None)
+    monkeypatch.setattr(torch, "__version__", "2.0.1+rocm7.0")
+    with pytest.raises(nv.NVFP4Error, match="built with torch"):
+        binding._host()
+    assert binding._host_module is None
