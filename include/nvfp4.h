@@ -173,6 +173,10 @@ int nvfp4_quantize_2d(const void *w_bf16, int64_t R, int64_t C, int64_t ld,
  * K % 64 == 0 and N % 8 == 0 run on the tiled MFMA kernels at any M and N
  * (operands of 2 GiB and more are cut into row chunks, one set of launches per
  * chunk); other shapes (K % 16 == 0) run on the 64x64 tile alone, at about half their rate.
+ * Last bits: the order in which a result's products are added is fixed for given M, N and K,
+ * and the same in every entry point and for both output types, but it depends on the tile that
+ * the launch plan gives the element (64x64 tiles add K in four or eight parts, the others in
+ * one), so a row of an fp32 result may differ in its last bits when M or N changes.
  */
 int nvfp4_gemm(const nvfp4_tensor *A, const nvfp4_tensor *W, void *Y, int64_t ldy,
                int out_dtype, void *stream);
@@ -191,8 +195,8 @@ int nvfp4_gemm(const nvfp4_tensor *A, const nvfp4_tensor *W, void *Y, int64_t ld
  * nvfp4_gemm_lora: Y = nvfp4_gemm(A, W) + lora_scale * T B^T in one kernel: the
  *   low-rank product (b_bf16 [N, NVFP4_LORA_RANK] bf16) is accumulated on the
  *   matrix cores into the accumulators of the FP4 product, in fp32.  Y, ldy,
- *   out_dtype as nvfp4_gemm; lora_scale = alpha_LoRA / r.  Needs K % 64 == 0
- *   and N % 8 == 0 (NVFP4_ERR_SHAPE otherwise).
+ *   out_dtype as nvfp4_gemm; lora_scale = alpha_LoRA / r.  With an adapter of zeros Y has
+ *   nvfp4_gemm's bits.  Needs K % 64 == 0 and N % 8 == 0 (NVFP4_ERR_SHAPE otherwise).
  */
 #define NVFP4_LORA_RANK 128
 int nvfp4_lora_down(const void *x_bf16, int64_t M, int64_t K, int64_t ldx, const void *a_bf16,

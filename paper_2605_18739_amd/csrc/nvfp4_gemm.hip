@@ -144,7 +144,7 @@ int gemm_plan_text(int64_t M, int64_t N, int64_t K, char *text, size_t text_byte
     size_t used = 0;
     int launches = 0;
     bool fits = true;
-    for_each_chunk(M, N, K, false, [&](int64_t, int64_t, int64_t, int64_t, const LaunchPlan &p) {
+    for_each_chunk(M, N, K, [&](int64_t, int64_t, int64_t, int64_t, const LaunchPlan &p) {
         for (int i = 0; i < p.n && fits; ++i) {
             const TileShape &t = kShapes[p.part[i].kind];
             const int w = snprintf(text + used, used < text_bytes ? text_bytes - used : 0, "%s%dx%d:%lld",
@@ -162,7 +162,7 @@ int gemm_plan_text(int64_t M, int64_t N, int64_t K, char *text, size_t text_byte
 int gemm_workgroups(int64_t M, int64_t N, int64_t K)
 {
     int64_t n = 0;
-    for_each_chunk(M, N, K, false, [&](int64_t, int64_t, int64_t, int64_t, const LaunchPlan &p) {
+    for_each_chunk(M, N, K, [&](int64_t, int64_t, int64_t, int64_t, const LaunchPlan &p) {
         for (int i = 0; i < p.n; ++i) n += p.part[i].tiles;
     });
     return (int)n;
@@ -173,7 +173,7 @@ static hipError_t launch_kind(TileKind kind, int epi, const GemmArgs &g, int64_t
     switch (kind) {
     case kTile256x256: return launch_tile_256x256(epi, g, tiles, s);
     case kTile256x192: return launch_tile_256x192(epi, g, tiles, s);
-    case kTile64: return launch_tile_64x64(epi, g, tiles, s);        // (LoRA is planned with the 256-row tiles only)
+    case kTile64: return launch_tile_64x64(epi, g, tiles, s);
     default: return launch_tile_128x128(epi, g, tiles, s);
     }
 }
@@ -192,8 +192,6 @@ hipError_t launch_gemm(const uint8_t *codesA, const uint8_t *scalesA, const floa
         const int kind = ep.out_dtype != 0 ? (kEpiBF16 | (ep.act == 1 ? kEpiGelu : 0)) : kEpiF32;
         return launch_tile_64x64(kind, g, tiles, s);
     }
-    if (with_lora && lora_takes_64(M, N, K))
-        return launch_tile_64x64((ep.out_dtype != 0 ? kEpiBF16 : kEpiF32) | kEpiLora, g, ((M + 63) / 64) * ((N + 63) / 64), s);
     // (the tiled fp32 output never carries an activation: nvfp4_gemm has none and the fused call emits bf16)
     const int out_kind = ep.q_scale ? kEpiQuant : (ep.out_dtype != 0 ? kEpiBF16 : kEpiF32);
     const int epi = out_kind | ((ep.act == 1 && out_kind != kEpiF32) ? kEpiGelu : 0);
@@ -201,7 +199,7 @@ hipError_t launch_gemm(const uint8_t *codesA, const uint8_t *scalesA, const floa
     const int64_t ysize = ep.out_dtype == 0 ? 4 : 2;
     int wg_total = 0;
     hipError_t err = hipSuccess;
-    for_each_chunk(M, N, K, with_lora, [&](int64_t cm, int64_t, int64_t cn, int64_t, const LaunchPlan &plan) {
+    for_each_chunk(M, N, K, [&](int64_t cm, int64_t, int64_t cn, int64_t, const LaunchPlan &plan) {
         for (int i = 0; i < plan.n && err == hipSuccess; ++i) {
             const SubLaunch &p = plan.part[i];
             const int64_t m_lo = cm + p.m_lo, n_lo = cn + p.n_lo;     // the sub-rectangle [m_lo, ..) x [n_lo, ..) as a problem of its own
@@ -223,10 +221,7 @@ hipError_t launch_gemm(const uint8_t *codesA, const uint8_t *scalesA, const floa
                 a.lora_t = lora.t + m_lo * kLoraRank;
                 a.lora_b = lora.b + n_lo * kLoraRank;
             }
-            // a leftover rectangle (every launch but the first tiles one completely) of a LoRA plan, which knows 256-row tiles
-            // only, takes 64x64 tiles where those are cheaper (3520x14336x3072: 312 -> 276 us)
-            if (with_lora && i > 0 && lora_takes_64(a.M, a.N, K)) err = launch_tile_64x64(epi | kEpiLora, a, ((a.M + 63) / 64) * ((a.N + 63) / 64), s);
-            else err = launch_kind(p.kind, epi | (with_lora ? kEpiLora : 0), a, p.tiles, s);
+            err = launch_kind(p.kind, epi | (with_lora ? kEpiLora : 0), a, p.tiles, s);
             wg_total += (int)p.tiles;
         }
     });

@@ -49,15 +49,14 @@ static double small_cost(int64_t M, int64_t N, int64_t K, TileKind kind)
     return c.base + waves * (c.wave + steps * c.step) + (double)tiles / kCUs * (c.tile + steps * c.fill);
 }
 
-// big_only: only the 256-row tile shapes (the planned kernels that can carry the LoRA phase)
-static TileKind choose_tile(int64_t M, int64_t N, int64_t K, double *cost = nullptr, bool big_only = false)
+static TileKind choose_tile(int64_t M, int64_t N, int64_t K, double *cost = nullptr)
 {
     // order of preference on ties: the larger tile
     static const TileKind order[4] = {kTile256x256, kTile256x192, kTile128, kTile64};
     const bool small = small_problem(M, N);
     TileKind best = kTile256x256;
     double cbest = 1e300;
-    for (int i = 0; i < (big_only ? 2 : 4); ++i) {
+    for (int i = 0; i < 4; ++i) {
         const double c = small ? small_cost(M, N, K, order[i]) / kUnitUs : tile_cost(M, N, K, kShapes[order[i]]);
         if (c < cbest) {
             cbest = c;
@@ -68,27 +67,21 @@ static TileKind choose_tile(int64_t M, int64_t N, int64_t K, double *cost = null
     return best;
 }
 
-// A small problem with a LoRA phase: one launch of 64x64 tiles (the kernel that cuts K between its waves carries the phase
-// as well) where that is cheaper than 256-row tiles: 128x3072x3072 takes 12 us instead of 49, 400x1024x1024 8 instead of 23.
-static bool lora_takes_64(int64_t M, int64_t N, int64_t K)
-{
-    if (!small_problem(M, N)) return false;
-    return small_cost(M, N, K, kTile64) < std::min(small_cost(M, N, K, kTile256x256), small_cost(M, N, K, kTile256x192));
-}
-
 // A launch plan: the main launch runs whole waves of tiles (in row-major tile
 // order) with one tile shape; what is left of the tile grid -- the tail of one row
 // of tiles and the rows below it -- goes to up to two more launches on the
 // corresponding sub-rectangles of the output, each with the tile shape that suits
 // it, when the cost model says that beats one more, mostly idle, wave.  (A small problem is one launch.)
+// A GEMM with a LoRA phase runs the plan of the plain one, so that an adapter of zeros leaves the plain GEMM's bits: the
+// 64x64 tile adds its K in another order than the larger ones.
 struct SubLaunch { int64_t m_lo, m_hi, n_lo, n_hi; TileKind kind; int64_t tiles; };   // tiles: how many of its grid to run (prefix)
 struct LaunchPlan { int n; SubLaunch part[3]; };
 
-static LaunchPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool big_only = false)
+static LaunchPlan plan_gemm(int64_t M, int64_t N, int64_t K)
 {
     LaunchPlan p{};
     double whole;
-    const TileKind kind = choose_tile(M, N, K, &whole, big_only);
+    const TileKind kind = choose_tile(M, N, K, &whole);
     const TileShape &t = kShapes[kind];
     const int64_t tm = (M + t.bm - 1) / t.bm, tn = (N + t.bn - 1) / t.bn, tiles = tm * tn;
     p.n = 1;
@@ -109,7 +102,7 @@ static LaunchPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool big_only = fal
     if (full_from < tm) extra[ne++] = {full_from * t.bm, M, 0, N, kTile128, 0};
     for (int i = 0; i < ne; ++i) {
         double ci;
-        extra[i].kind = choose_tile(extra[i].m_hi - extra[i].m_lo, extra[i].n_hi - extra[i].n_lo, K, &ci, big_only);
+        extra[i].kind = choose_tile(extra[i].m_hi - extra[i].m_lo, extra[i].n_hi - extra[i].n_lo, K, &ci);
         const TileShape &ts = kShapes[extra[i].kind];
         extra[i].tiles = ((extra[i].m_hi - extra[i].m_lo + ts.bm - 1) / ts.bm) * ((extra[i].n_hi - extra[i].n_lo + ts.bn - 1) / ts.bn);
         split += ci + kNextLaunch;
@@ -119,7 +112,7 @@ static LaunchPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool big_only = fal
     if (c != 0 && q > 0) {
         SubLaunch below = {q * t.bm, M, 0, N, kTile128, 0};
         double cb;
-        below.kind = choose_tile(M - below.m_lo, N, K, &cb, big_only);
+        below.kind = choose_tile(M - below.m_lo, N, K, &cb);
         const TileShape &ts = kShapes[below.kind];
         below.tiles = ((M - below.m_lo + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn);
         const int64_t rows_tiles = q * tn;
@@ -150,13 +143,13 @@ static bool tiled_ok(int64_t M, int64_t N, int64_t K)
 
 // f(m_lo, m_hi, n_lo, n_hi, plan) for every chunk of the problem, in launch order
 template <class F>
-static void for_each_chunk(int64_t M, int64_t N, int64_t K, bool big_only, F &&f)
+static void for_each_chunk(int64_t M, int64_t N, int64_t K, F &&f)
 {
     const int64_t step = max_operand_rows(K);
     for (int64_t m_lo = 0; m_lo < M; m_lo += step)
         for (int64_t n_lo = 0; n_lo < N; n_lo += step) {
             const int64_t m_hi = std::min(M, m_lo + step), n_hi = std::min(N, n_lo + step);
-            f(m_lo, m_hi, n_lo, n_hi, plan_gemm(m_hi - m_lo, n_hi - n_lo, K, big_only));
+            f(m_lo, m_hi, n_lo, n_hi, plan_gemm(m_hi - m_lo, n_hi - n_lo, K));
         }
 }
 

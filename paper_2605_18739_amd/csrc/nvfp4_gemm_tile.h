@@ -427,7 +427,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_regdq_kernel(GemmArgs g)
 
     if constexpr ((EPI & kEpiLora) != 0) {
         // ---- LoRA phase (Sec. 2.2 / 3.1: low-rank adapter beside the quantized weight).  The
-        // tile's 256 + BN rows of T and B (128 bf16 = 256 B each) are copied into LDS, multiplied
+        // tile's BM + BN rows of T and B (128 bf16 = 256 B each) are copied into LDS, multiplied
         // with v_mfma_f32_32x32x16_bf16 in eight 16-wide sub-steps, and the accumulators are
         // rescaled by lora_scale / (gsA gsW) so that the quantized product can be added on top
         // and the epilogue's single multiplication by gsA gsW leaves lora_scale * T B^T.
@@ -649,8 +649,7 @@ static hipError_t launch_regdq(const GemmArgs &g, int64_t tiles, hipStream_t s)
     return hipGetLastError();
 }
 
-// One tile shape with the epilogue variant chosen at run time (epi: kEpi* bits).  The LoRA phase
-// exists for the 256-row tiles only.
+// One tile shape with the epilogue variant chosen at run time (epi: kEpi* bits).
 template <int BM, int BN>
 static hipError_t launch_tile(int epi, const GemmArgs &g, int64_t tiles, hipStream_t s)
 {
@@ -660,12 +659,8 @@ static hipError_t launch_tile(int epi, const GemmArgs &g, int64_t tiles, hipStre
     case kEpiBF16 | kEpiGelu: return launch_regdq<BM, BN, kEpiBF16 | kEpiGelu>(g, tiles, s);
     case kEpiQuant: return launch_regdq<BM, BN, kEpiQuant>(g, tiles, s);
     case kEpiQuant | kEpiGelu: return launch_regdq<BM, BN, kEpiQuant | kEpiGelu>(g, tiles, s);
-    case kEpiF32 | kEpiLora:
-        if constexpr (BM >= 256) return launch_regdq<BM, BN, kEpiF32 | kEpiLora>(g, tiles, s);
-        else return hipErrorInvalidValue;
-    case kEpiBF16 | kEpiLora:
-        if constexpr (BM >= 256) return launch_regdq<BM, BN, kEpiBF16 | kEpiLora>(g, tiles, s);
-        else return hipErrorInvalidValue;
+    case kEpiF32 | kEpiLora: return launch_regdq<BM, BN, kEpiF32 | kEpiLora>(g, tiles, s);
+    case kEpiBF16 | kEpiLora: return launch_regdq<BM, BN, kEpiBF16 | kEpiLora>(g, tiles, s);
     default: return hipErrorInvalidValue;
     }
 }

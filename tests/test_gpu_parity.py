@@ -709,7 +709,7 @@ def _lora_case(oracle, M, N, K, scale, what, rows=None):
 def test_gemm_lora_small_and_ragged(oracle):
     _lora_case(oracle, 100, 136, 192, 1.0, "one ragged tile")
     _lora_case(oracle, 300, 520, 64, 0.5, "several tiles, one k step")
-    _lora_case(oracle, 520, 400, 320, 2.0, "256x192 tiles")
+    _lora_case(oracle, 520, 400, 320, 2.0, "several tiles, five k steps")
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 8, 64), (65, 72, 128), (40, 264, 448), (130, 200, 512),     # the phase on wave 1, 1, 4, 4 of eight
@@ -729,11 +729,34 @@ def test_lora_down_partial_steps(oracle, M, K):
     assert (np.abs(tv - wv) <= 2.0 ** -7 * np.abs(wv) + 2.0 ** -15 * bound).all()              # one bf16 step and the fp32 sums
 
 
-def test_gemm_lora_leftover_rectangle(oracle):
-    """18 x 17 tiles of 256x256: one whole wave, and a rectangle of leftover rows on 64x64 tiles; ragged both ways."""
-    M, N = 4500, 4104
-    rows = np.unique(np.concatenate([np.random.default_rng(3).integers(0, M, 60), [0, 3839, 3840, 4095, 4096, M - 1]])).astype(np.int64)
-    _lora_case(oracle, M, N, 64, 0.5, "lora leftover rectangle", rows=rows)
+@pytest.mark.parametrize("M,N,K,tiles", [
+    (911, 8248, 192, ["256x192"]), (911, 8248, 320, ["256x192"]), (1338, 8104, 64, ["256x256"]), (1338, 8104, 192, ["256x256"]),
+    (1100, 2048, 320, ["128x128"]), (2000, 1536, 64, ["128x128"]),
+    (4500, 4104, 64, ["256x192", "128x128"]), (3332, 7016, 192, ["256x256", "128x128"]), (5889, 8200, 64, ["256x256", "64x64"]),
+    (2321, 6728, 768, ["256x192", "64x64"])])
+def test_gemm_lora_on_every_tile_and_leftover_rectangle(oracle, M, N, K, tiles):
+    """The launch plan of the plain GEMM, each tile shape with its LoRA phase: single launches of few steps, and leftover
+    rectangles of both kinds; ragged both ways."""
+    assert [t for t, _ in nv.nvfp4_gemm_plan(M, N, K)] == tiles
+    rows = np.unique(np.concatenate([np.random.default_rng(3).integers(0, M, 60), np.arange(256, M, 256), np.arange(255, M, 256), [0, M - 1]])).astype(np.int64)
+    _lora_case(oracle, M, N, K, 0.5, f"lora {tiles}", rows=rows)
+
+
+@pytest.mark.parametrize("M,N,K", [(520, 400, 320), (1000, 3072, 3072), (2000, 1536, 1536), (3520, 1024, 3072), (2321, 6728, 768)])
+def test_gemm_lora_with_an_adapter_of_zeros_is_the_plain_gemm(M, N, K):
+    """Bit for bit, on values whose fp32 sums depend on their order (heavy tails)."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+
+    def heavy(rows):
+        x = torch.randn((rows, K), generator=g, device="cuda")
+        return nv.nvfp4_quantize((x * torch.exp(3.0 * torch.randn((rows, K), generator=g, device="cuda"))).to(torch.bfloat16))
+
+    a, w = heavy(M), heavy(N)
+    t = torch.randn((M, nv.LORA_RANK), generator=g, device="cuda").to(torch.bfloat16)
+    b = torch.zeros((N, nv.LORA_RANK), dtype=torch.bfloat16, device="cuda")
+    for dtype in (nv.OUT_F32, nv.OUT_BF16):
+        assert torch.equal(nv.nvfp4_gemm_lora(a, w, t, b, 0.5, dtype), nv.nvfp4_gemm(a, w, dtype))
 
 
 def test_gemm_lora_projection_shape(oracle):
