@@ -408,9 +408,9 @@ __device__ __forceinline__ void smooth_block16(uint32_t (&w)[8], float mu)
 
 // Mean of a row of d = 16 nb_row features (nb_row a power of two up to 64, one 16-element block per lane, the row's
 // lanes neighbours), rounded to bf16: RN_bf16(sum / d) of the exact sum.  Every lane of the wave calls this.
-// The sum is taken in fp32: 4 + log2(nb_row) <= 10 rounded levels, each off by at most 2^-24 of the sum of magnitudes, so
-// the mean lies within e = 10.1 * 2^-24 * (row maximum) of the exact one; where both ends of that interval round to the
-// same bf16 number, that is the mean.  Otherwise (one row in a few hundred, rows whose terms cancel, and rows that fp32
+// The sum is taken in fp32: 4 + log2(nb_row) <= 10 rounded levels, each off by at most 2^-24 of the sum of magnitudes, and
+// one more rounding for either end of the interval, so the exact mean lies between the ends at e = 11.1 * 2^-24 * (row
+// maximum) around the fp32 one; where both round to the same bf16 number, that is the mean.  Otherwise (one row in a few hundred, rows whose terms cancel, and rows that fp32
 // could overflow on) the wave takes the sum in fp64, which is exact for rows whose values span less than 2^40.
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float v) { return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, true)); }
@@ -433,7 +433,7 @@ __device__ __forceinline__ uint32_t row_mean_bits(const uint32_t (&w)[8], int nb
     if (nb_row > 8) { sum += dpp_f32<0x140>(sum); mx = fmaxf(mx, dpp_f32<0x140>(mx)); }
     for (int m = 16; m < nb_row; m <<= 1) { sum += __shfl_xor(sum, m, 64); mx = fmaxf(mx, __shfl_xor(mx, m, 64)); }
     const float mean = sum * (1.0f / (float)(16 * nb_row)) + 0.0f;           // (a power of two; a zero is +0)
-    const float e = 10.1f * 0x1p-24f * mx;
+    const float e = 11.1f * 0x1p-24f * mx;
     const uint32_t ends = pack_bf16x2(mean - e, mean + e);
     uint32_t bits = ends & 0xFFFFu;
     const bool sure = (bits == ends >> 16) & (mx < 0x1p110f);

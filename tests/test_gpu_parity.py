@@ -954,6 +954,34 @@ def test_kv_quant_k_smoothing(oracle, T, H, d):
     assert (nv.bits_from_bf16(back).reshape(T * H, d) == oracle.dequant_bf16(want_q, want_mean)).all()
 
 
+@pytest.mark.parametrize("d", [16, 32, 64, 128, 256, 512, 1024])
+def test_kv_quant_k_row_means_on_and_beside_bf16_midpoints(oracle, d):
+    """Rows whose exact mean is a midpoint between two bf16 numbers, or lies off it by t / d for t from far below what
+    an fp32 sum resolves (2^-40 of the mean) to far above, either way: the means are the exact ones rounded once, in both
+    forms of the call.  a, b: neighbouring bf16 numbers; a row is {2a, 2b, t, 0} and pairs {a, b}, in any order."""
+    g = np.random.default_rng(d)
+    rows = []
+    for k in range(-44, -4):
+        for sign in (-1.0, 0.0, 1.0):
+            lead, scale = float(g.integers(128, 255)), 2.0 ** float(g.integers(-20, 20)) * float(g.choice([-1.0, 1.0]))
+            t = sign * float(g.integers(128, 256)) * 2.0 ** k
+            x = np.array([2 * lead, 2 * lead + 2, t, 0.0] + [lead, lead + 1] * ((d - 4) // 2))
+            rows.append(g.permutation(x * scale))
+    x = np.array(rows)
+    kb = wl.to_bf16_bits(x.astype(np.float32))
+    assert (wl.bf16_bits_to_f32(kb).astype(np.float64) == x).all()                 # every value is a bf16 number
+    want_mean, want = _oracle_k_path(oracle, kb)
+    kv = dev_bf16(kb).reshape(len(rows), 1, d)
+    for mode in (nv.ONE_LAUNCH_ALWAYS, nv.ONE_LAUNCH_NEVER):
+        nv.nvfp4_set_one_launch(mode)
+        try:
+            gq, gm = nv.nvfp4_kv_quant_k(kv)
+        finally:
+            nv.nvfp4_set_one_launch()
+        assert (nv.bits_from_bf16(gm) == want_mean).all(), f"means, mode {mode}"
+        assert_q_equal(gq, want, f"mode {mode}")
+
+
 def test_kv_cache_random_sweep(oracle):
     """Seeded sweep over cache shapes and value distributions: plain values, the scale search, the
     smoothed keys and their reconstruction, all byte for byte against the oracle."""
