@@ -356,13 +356,15 @@ bool quantize_rows_resident_fits(int64_t rows, int64_t C, int64_t ld, bool smoot
 
 // Whether the one-launch form is taken for a tensor that fits.  It fetches the tensor once where the two passes
 // fetch it twice, but pays for the exchange across the grid, and its encoding runs at two waves per SIMD where the
-// streaming pass has six to eight.  Measured back to back (us, one launch / two passes, blocks of 16 elements):
-//   plain rule    1.5 k 5.3 / 6.1   19 k 6.6 / 6.2   192 k 9.6 / 6.6   676 k 13.2 / 12.6   887 k 14.2 / 14.7   1.7 M 21.3 / 23.0   3.5 M 34.6 / 42.7
-//   scale search                    19 k 9.1 / 8.1   192 k 13.1 / 9.2  676 k 22.1 / 18.6   1.7 M 34.1 / 32.0   2.6 M 41.6 / 43.7   3.5 M 54.5 / 56.7
-//   smoothed keys                   19 k 9.9 / 9.0   192 k 13.8 / 10.6 676 k 21.9 / 18.9   1.7 M 38.9 / 35.6   3.5 M 67.3 / 64.0
-// So: below 12 k blocks one launch where that saves the second launch, from there on two passes until the second
-// fetch costs more than the exchange, which is at 0.8 M blocks for the plain rule and 2.2 M with the search; smoothed
-// keys (whose first pass sums in fp64 either way) two passes throughout.  mode 1: whenever it fits; mode 2: never.
+// streaming pass has six to eight.  Measured in one session, calls back to back on inputs in turn that together exceed the
+// 256 MB Infinity Cache (us, one launch / two passes, blocks of 16 elements):
+//   plain rule    1.5 k 5.9 / 8.0   12 k 6.4 / 7.5    192 k 10.1 / 7.9   676 k 13.0 / 13.1   887 k 14.7 / 15.5   1.7 M 21.9 / 24.8   3.5 M 38.0 / 45.9
+//   scale search  1.5 k 6.8 / 8.0   12 k 7.8 / 7.4    192 k 11.8 / 8.7   676 k 17.4 / 15.1   1.7 M 30.2 / 28.9   2.2 M 35.8 / 35.0   2.6 M 41.2 / 42.7   3.5 M 55.1 / 56.8
+//   smoothed keys 1.5 k 7.2 / 8.1   12 k 8.3 / 7.8    192 k 12.6 / 9.8   676 k 19.7 / 17.3   1.7 M 36.8 / 33.3   2.2 M 44.9 / 40.0   3.5 M 64.5 / 59.6
+// So: below 12 k blocks one launch where that saves the second launch (host-bound; replayed from a graph the two passes
+// are ahead there by a microsecond), from there on two passes until the second fetch costs more than the exchange, which
+// is at 0.8 M blocks for the plain rule and between 2.2 M and 2.6 M with the search; smoothed keys two passes
+// throughout.  mode 1: whenever it fits; mode 2: never.
 static int g_one_launch_mode = 0;
 void set_one_launch_mode(int mode) { g_one_launch_mode = mode; }
 bool quantize_rows_resident_pays(int64_t nblk, bool search, bool smooth)
