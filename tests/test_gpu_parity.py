@@ -436,7 +436,7 @@ def test_gemm_config1(oracle):
 @pytest.mark.parametrize("M,N,K", [(1, 4, 64), (100, 136, 192), (130, 260, 128), (300, 520, 64),
                                    (513, 1028, 320),
                                    (1100, 2048, 320),      # 128x128 tiles, odd number of 64-k steps
-                                   # shapes of the fallback kernel: K not a multiple of 64 (16, 48, 80: one block,
+                                   # shapes that only the 64x64 tile takes: K not a multiple of 64 (16, 48, 80: one block,
                                    # a partial step, one step and a bit), N not a multiple of 8, several tiles each way
                                    (5, 12, 16), (130, 260, 48), (257, 132, 208), (64, 68, 1040), (300, 264, 80)])
 def test_gemm_ragged_tiles(oracle, M, N, K):
@@ -456,6 +456,25 @@ def test_gemm_tile_that_cuts_k_between_its_waves(oracle, M, N, K):
     ab = wl.to_bf16_bits(g.standard_normal((M, K)).astype(np.float32))
     wb = wl.to_bf16_bits((g.standard_normal((N, K)) * 0.02).astype(np.float32))
     _gemm_case(oracle, ab, wb, f"K cut between waves {M}x{N}x{K}")
+
+
+@pytest.mark.parametrize("M,N,K", [(40, 67, 80), (65, 129, 64), (70, 190, 208), (33, 5, 128), (3, 1, 16)])
+def test_gemm_widths_that_are_no_multiple_of_4(oracle, M, N, K):
+    """Odd widths in a padded Y, both output types: the last columns of a row are stored one by one and the padding is
+    left alone."""
+    g = np.random.default_rng(M * N + K)
+    ab = wl.to_bf16_bits(g.standard_normal((M, K)).astype(np.float32))
+    wb = wl.to_bf16_bits((g.standard_normal((N, K)) * 0.02).astype(np.float32))
+    ga, gw = nv.nvfp4_quantize(dev_bf16(ab)), nv.nvfp4_quantize(dev_bf16(wb))
+    Y, S = oracle.gemm(oracle.quantize(ab), oracle.quantize(wb))
+    for pad in (4, 8):
+        ldy = (N + 3) // 4 * 4 + pad
+        y32, y16 = (torch.full((M, ldy), -7.0, dtype=t, device="cuda") for t in (torch.float32, torch.bfloat16))
+        nv.nvfp4_gemm(ga, gw, nv.OUT_F32, Y=y32[:, :N])
+        nv.nvfp4_gemm(ga, gw, nv.OUT_BF16, Y=y16[:, :N])
+        assert_gemm_close(y32[:, :N].cpu().numpy(), Y, S, f"width {N}, ldy {ldy}")
+        assert (nv.bits_from_bf16(y16) == nv.bits_from_bf16(y32.to(torch.bfloat16))).all()
+        assert bool((y32[:, N:] == -7.0).all())
 
 
 def test_gemm_random_shapes(oracle):
@@ -528,7 +547,7 @@ def test_gemm_small_k_untiled(oracle, M, N, K):
     g = np.random.default_rng(M * N * K)
     ab = wl.to_bf16_bits(g.standard_normal((M, K)).astype(np.float32))
     wb = wl.to_bf16_bits(g.standard_normal((N, K)).astype(np.float32))
-    _gemm_case(oracle, ab, wb, f"untiled {M}x{N}x{K}", check_bf16=(N % 4 == 0))
+    _gemm_case(oracle, ab, wb, f"64x64 tile alone {M}x{N}x{K}", check_bf16=(N % 4 == 0))
 
 
 def test_gemm_unit_scales_is_bit_exact(oracle):
@@ -1138,12 +1157,10 @@ def _act_quant_case(oracle, M, N, K, given_scale, what, max_flips=0.001):
 
 @pytest.mark.parametrize("given_scale", [False, True])
 def test_gemm_act_quant(oracle, given_scale):
-    _act_quant_case(oracle, 200, 272, 256, given_scale, "small")
-    _act_quant_case(oracle, 520, 1040, 128, given_scale, "multi-tile")
-    _act_quant_case(oracle, 1100, 2048, 192, given_scale, "128x128 tiles")
-    _act_quant_case(oracle, 2100, 2064, 256, given_scale, "256x192 tiles")
-    _act_quant_case(oracle, 4200, 3072, 128, given_scale, "256x256 tiles")
-    _act_quant_case(oracle, 40, 48, 48, given_scale, "untiled K")
+    for M, N, K, tile in ((200, 272, 256, "64x64"), (520, 1040, 128, "64x64"), (1100, 2048, 192, "128x128"), (2100, 2064, 256, "128x128"),
+                          (1500, 6000, 192, "256x192"), (4200, 3072, 128, "256x256"), (40, 48, 48, "generic")):
+        assert [t for t, _ in nv.nvfp4_gemm_plan(M, N, K)] == [tile]
+        _act_quant_case(oracle, M, N, K, given_scale, f"{tile} tiles")
     # whole waves of 256x256 tiles, then the tail of a tile row on 64x64 tiles and the rows below on
     # 128x128 tiles: three launches share the output pitch and the table of partial maxima
     assert len(nv.nvfp4_gemm_plan(7040, 5296, 2368)) == 3
@@ -1157,7 +1174,7 @@ def test_gemm_scale_out_feeds_the_given_scale_quantizers(oracle, M, N, K):
     """nvfp4_gemm_scale_out: bf16 Y bit for bit what nvfp4_gemm gives, and the tensor scale of Y from the GEMM's
     epilogue equal to the oracle's amax / 2688 of those bits.  The calls that quantize Y afterwards take the scale as
     given (one read of Y each) and return the oracle's bytes along both axes and with the scale search.  Tiled
-    shapes with one and with several launches, and an odd shape that takes the fallback kernel."""
+    shapes of every size, and an odd shape that only the 64x64 tile takes."""
     say(f"[gemm+scale] {M}x{N}x{K}: {nv.nvfp4_gemm_plan(M, N, K)}")
     g = np.random.default_rng(M + N + K)
     ga = nv.nvfp4_quantize(dev_bf16(wl.to_bf16_bits(g.standard_normal((M, K)).astype(np.float32))))
@@ -1208,12 +1225,14 @@ def test_full_size_projection_config2(oracle):
     _gemm_case(oracle, cfg["A"], cfg["W"], "config2")
 
 
-@pytest.mark.parametrize("M,N,K", [(4100, 8200, 128),      # 256x192 tiles, ragged M and N tails
-                                   (8200, 8192, 192),      # 256x256 tiles, odd number of 64-k steps
-                                   (3520, 3072, 320),      # the projection shape, 5 steps
-                                   (700, 1544, 64)])       # single step
-def test_gemm_large_tile_paths(oracle, M, N, K):
-    """Shapes that take the register-dequantizing kernels (256-row tiles)."""
+@pytest.mark.parametrize("M,N,K,tile", [(4100, 8200, 128, "256x192"),      # ragged M and N tails
+                                        (8200, 8192, 192, "256x256"),      # odd number of 64-k steps
+                                        (3520, 3072, 320, "256x192"),      # the projection shape, 5 steps
+                                        (911, 8248, 64, "256x192"),        # single step
+                                        (700, 1544, 64, "128x128")])
+def test_gemm_large_tile_paths(oracle, M, N, K, tile):
+    """Shapes that take the larger tiles."""
+    assert nv.nvfp4_gemm_plan(M, N, K)[0][0] == tile
     g = np.random.default_rng(M + K)
     ab = wl.activation_with_outliers(M, K, 7, 0)
     wb = wl.normal((N, K), 0.02, 7, 1)
@@ -1224,8 +1243,7 @@ def test_gemm_large_tile_paths(oracle, M, N, K):
 
 @pytest.mark.parametrize("K", [128, 256, 384, 448, 640])
 def test_gemm_several_tiles_per_workgroup(oracle, K):
-    """More 256-row tiles than compute units, so a workgroup walks several tiles and starts
-    the copies of the next one while finishing the current one; the K values give every
+    """More 256-row tiles than compute units, several rounds of workgroups; the K values give every
     combination of even / odd counts of 64-k steps, 128-k copy steps and 256-k scale groups.
     One sampled row in every band of 256 rows, plus the band edges."""
     M, N = 4400, 8192
