@@ -280,8 +280,8 @@ int nvfp4_kv_quant_4over6(const void *kv_bf16, int64_t T, int64_t H, int64_t d, 
  * the scale search of Appendix Eq. 12-13): every row [t, h, :] first has its
  * mean over the d features removed,
  *   mean[t,h] = RN_bf16( (sum_u K[t,h,u]) / d ),  Kbar[t,h,u] = RN_bf16( K[t,h,u] - mean[t,h] )
- * (sum, quotient and difference in fp64: exact for rows whose values span less
- * than 2^40), and Kbar is quantized like nvfp4_kv_quant_4over6, its tensor scale
+ * (the sum and quotient of the mean as fp64 takes them, which is exactly for rows whose
+ * values span less than 2^40, rounded once; the difference rounded once), and Kbar is quantized like nvfp4_kv_quant_4over6, its tensor scale
  * taken from the amax of Kbar.  The means belong to the cache entry.
  * row_mean_bf16_out: device, bf16 [T*H].  d / 16 must be a power of two <= 64.
  * workspace: nvfp4_workspace_bytes(NVFP4_OP_KV_QUANT_K, T, H, d).

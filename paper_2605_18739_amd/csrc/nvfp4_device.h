@@ -7,7 +7,6 @@
 #include <stdint.h>
 
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-typedef _Float16 half4v __attribute__((ext_vector_type(4)));
 typedef _Float16 half8v __attribute__((ext_vector_type(8)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef float float16v __attribute__((ext_vector_type(16)));
@@ -68,14 +67,6 @@ __device__ __forceinline__ float e4m3_to_f32(uint32_t b)
 {
     float normal = __uint_as_float((b << 20) + (120u << 23));
     float sub = (float)(b & 7u) * 0.001953125f;    // m * 2^-9
-    return (b >> 3) ? normal : sub;
-}
-// value -> f16 bit pattern (every E4M3 value, subnormals included, is a normal f16)
-__device__ __forceinline__ _Float16 e4m3_to_f16(uint32_t b)
-{
-    uint16_t nb = (uint16_t)((b << 7) + 0x2000u);
-    _Float16 normal = __builtin_bit_cast(_Float16, nb);
-    _Float16 sub = (_Float16)((float)(b & 7u) * 0.001953125f);
     return (b >> 3) ? normal : sub;
 }
 
@@ -304,8 +295,8 @@ __device__ __forceinline__ void quantize_pair16(const uint32_t (&wa)[8], const u
 //     10^5 is still open;
 //  3. the fp64 definition.
 // Gains and errors below 2^-100, where fp32 may lose its relative accuracy, or that are no finite numbers are never sure.
-// Bound by VALU issue: about 230 slots per block (the bracketed search took about 450): 16 unpack, 8 maximum, 20 scales,
-// 32 multiplies, 32 conversions of up to three slots, 32 dot products.
+// Bound by VALU issue: 224 vector instructions per block in the compiled pass (the bracketed search took about 450), the
+// largest groups 16 unpack, 8 maximum, 20 scales, 32 multiplies, 32 conversions, 32 dot products.
 __device__ __forceinline__ float block_error_f32(const float (&f)[16], const uint32_t (&c)[2], float den)
 {
     typedef float float2v __attribute__((ext_vector_type(2)));

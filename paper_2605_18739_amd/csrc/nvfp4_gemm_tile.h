@@ -81,12 +81,6 @@ __device__ __forceinline__ float gelu_tanh_f32(float y)
     return (y * e) * __builtin_amdgcn_rcpf(e + 1.0f);
 }
 
-__device__ __forceinline__ uint32_t f32_to_bf16_rne(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-
 // 3-bit swizzle key of a row: distinct over every 8 consecutive rows and,
 // combined with the row parity, over every 16.  LDS reads are served 16 lanes at
 // a time out of 64 banks (256 B), writes 8 lanes at a time out of 128 B; with
