@@ -202,10 +202,8 @@ def _ptr(t):
     return ctypes.c_void_p(t.data_ptr()) if t is not None else None
 
 
-def _sizes(x, rank):
-    """The sizes that an output is allocated by; everything else about x is checked by the native call."""
-    assert x.dim() == rank, f"expected a tensor of {rank} dimensions, got {x.dim()}"
-    return x.shape
+def _wrong_rank(x, rank):
+    return AssertionError(f"expected a tensor of {rank} dimensions, got {x.dim()}")
 
 
 def nvfp4_quantize(x, block_axis=0, global_scale_in=None, out=None, workspace=None, stream=None):
@@ -213,7 +211,10 @@ def nvfp4_quantize(x, block_axis=0, global_scale_in=None, out=None, workspace=No
     if stream is not None and (out is None or workspace is None) and _elsewhere(stream):
         return _on(stream, nvfp4_quantize, x, block_axis, global_scale_in, out, workspace)
     if out is None:
-        R, C = _sizes(x, 2)
+        try:
+            R, C = x.shape
+        except ValueError:
+            raise _wrong_rank(x, 2) from None
         out = NVFP4Tensor(R, C, x.device) if block_axis == 0 else NVFP4Tensor(C, R, x.device)
     _check(_host().quantize(x, block_axis, global_scale_in, out, workspace, _stream(stream)))
     return out
@@ -245,7 +246,11 @@ def nvfp4_lora_down(x, a, out=None, workspace=None, stream=None):
     if stream is not None and (out is None or workspace is None) and _elsewhere(stream):
         return _on(stream, nvfp4_lora_down, x, a, out, workspace)
     if out is None:
-        out = _host().output(x, _sizes(x, 2)[0], LORA_RANK, True)
+        try:
+            M, _ = x.shape
+        except ValueError:
+            raise _wrong_rank(x, 2) from None
+        out = _host().output(x, M, LORA_RANK, True)
     _check(_host().lora_down(x, a, out, workspace, _stream(stream)))
     return out
 
@@ -271,7 +276,10 @@ def nvfp4_gemm_act_quant(A, W, act=ACT_GELU_TANH, global_scale_in=None, out=None
 
 
 def _heads_out(x):
-    T, H, d = _sizes(x, 3)
+    try:
+        T, H, d = x.shape
+    except ValueError:
+        raise _wrong_rank(x, 3) from None
     return NVFP4Tensor(T * H, d, x.device)
 
 
@@ -296,7 +304,10 @@ def nvfp4_quantize_4over6(x, global_scale_in=None, out=None, workspace=None, str
     if stream is not None and (out is None or workspace is None) and _elsewhere(stream):
         return _on(stream, nvfp4_quantize_4over6, x, global_scale_in, out, workspace)
     if out is None:
-        R, C = _sizes(x, 2)
+        try:
+            R, C = x.shape
+        except ValueError:
+            raise _wrong_rank(x, 2) from None
         out = NVFP4Tensor(R, C, x.device)
     _check(_host().quantize_4over6(x, global_scale_in, out, workspace, _stream(stream)))
     return out
@@ -328,7 +339,10 @@ def nvfp4_quantize_rht(x, sign_mask, global_scale_in=None, out=None, workspace=N
     if stream is not None and (out is None or workspace is None) and _elsewhere(stream):
         return _on(stream, nvfp4_quantize_rht, x, sign_mask, global_scale_in, out, workspace)
     if out is None:
-        R, C = _sizes(x, 2)
+        try:
+            R, C = x.shape
+        except ValueError:
+            raise _wrong_rank(x, 2) from None
         out = NVFP4Tensor(C, R, x.device)
     _check(_host().quantize_rht(x, int(sign_mask), global_scale_in, out, workspace, _stream(stream)))
     return out
@@ -339,7 +353,10 @@ def nvfp4_quantize_2d(w, global_scale_in=None, transposed=True, workspace=None, 
     Returns (NVFP4Tensor [R, C], NVFP4Tensor [C, R] or None)."""
     if stream is not None and _elsewhere(stream):
         return _on(stream, nvfp4_quantize_2d, w, global_scale_in, transposed, workspace)
-    R, C = _sizes(w, 2)
+    try:
+        R, C = w.shape
+    except ValueError:
+        raise _wrong_rank(w, 2) from None
     out = NVFP4Tensor(R, C, w.device)
     out_t = NVFP4Tensor(C, R, w.device) if transposed else None
     _check(_host().quantize_2d(w, global_scale_in, out, out_t, workspace, _stream(stream)))
@@ -353,7 +370,10 @@ def nvfp4_kv_quant_k(k, out=None, row_mean=None, workspace=None, stream=None):
     if out is None:
         out = _heads_out(k)
     if row_mean is None:
-        T, H, _ = _sizes(k, 3)
+        try:
+            T, H, _ = k.shape
+        except ValueError:
+            raise _wrong_rank(k, 3) from None
         row_mean = torch.empty(T * H, dtype=torch.bfloat16, device=k.device)
     _check(_host().kv_quant_k(k, out, row_mean, workspace, _stream(stream)))
     return out, row_mean
