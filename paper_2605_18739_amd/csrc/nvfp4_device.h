@@ -156,8 +156,9 @@ __device__ __forceinline__ void unpack16(const uint32_t (&w)[8], float (&f)[16])
 // be off by), anything else is further than 2^-17 from a midpoint and does not cross it.  Where s_g equals the
 // quotient exactly (an eighth of the bf16 maxima) the near-ties are ties, and the quotients are rounded to 17
 // significant bits, which puts them exactly on the midpoint; the conversions then round to the even code.
-// Bound by VALU issue: about 75 instruction slots per block against 190 for the bracket (16 unpack, 8 maximum, about
-// 10 scale, 16 multiplies, 8 conversions of up to three slots), and no data-dependent loop.
+// About 75 instruction slots per block against 190 for the bracket (16 unpack, 8 maximum, about 10 scale, 16 multiplies,
+// 8 conversions of up to three slots), and no data-dependent loop: the streaming pass of the plain rule issues vector
+// instructions in half of the SIMDs' cycles and is bound by memory.
 struct TensorScale {
     float sg;          // the tensor scale, shifted into the fp32-safe range
     float nudged;      // sg (1 -+ 2^-18), what quotients are formed with
@@ -295,8 +296,9 @@ __device__ __forceinline__ void quantize_pair16(const uint32_t (&wa)[8], const u
 //     10^5 is still open;
 //  3. the fp64 definition.
 // Gains and errors below 2^-100, where fp32 may lose its relative accuracy, or that are no finite numbers are never sure.
-// Bound by VALU issue: 224 vector instructions per block in the compiled pass (the bracketed search took about 450), the
-// largest groups 16 unpack, 8 maximum, 20 scales, 32 multiplies, 32 conversions, 32 dot products.
+// Bound by VALU issue (in 83 % of the SIMDs' cycles in the streaming pass of the smoothed keys): 224 vector instructions per
+// block in the compiled pass (the bracketed search took about 450), the largest groups 16 unpack, 8 maximum, 20 scales,
+// 32 multiplies, 32 conversions, 32 dot products.
 __device__ __forceinline__ float block_error_f32(const float (&f)[16], const uint32_t (&c)[2], float den)
 {
     typedef float float2v __attribute__((ext_vector_type(2)));
