@@ -26,7 +26,7 @@ constexpr int kAmaxThreads = 1024, kAmaxGrid = 256;
 template <bool CONTIG, bool STREAM>
 __global__ __launch_bounds__(kAmaxThreads) void amax_partial_kernel(const uint16_t *__restrict__ x, int64_t R,
                                                                     int64_t C, int64_t ld,
-                                                                    uint32_t *__restrict__ partial)
+                                                                    uint32_t *__restrict__ partial, Divisor by_row)
 {
     __shared__ uint32_t wave_max[kAmaxThreads / 64];
     const int64_t vec_per_row = C >> 3;
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kAmaxThreads) void amax_partial_kernel(const uint16
     const int64_t per = (nvec + gridDim.x - 1) / gridDim.x, begin = per * blockIdx.x, end = min(nvec, begin + per);
     auto offset_of = [&](int64_t i) {
         if (CONTIG) return i << 3;
-        const int64_t r = i / vec_per_row;
+        const int64_t r = divide(i, vec_per_row, by_row);
         return r * ld + ((i - r * vec_per_row) << 3);
     };
     uint32_t acc = 0;
@@ -151,11 +151,11 @@ __global__ __launch_bounds__(1024) void scale_from_partials_kernel(const uint32_
 // (two 128-bit loads, one 64-bit code store, one scale byte).
 // SEARCH: the Four-over-Six scale search of Eq. 12-13 instead of the plain max -> 6 rule.
 // SMOOTH: the row means of Eq. 6 (row_mean, one bf16 per row) are removed first.
-// slab_heads > 0: the rows are (token, head) pairs of a [T, H, d] tensor and the output is
+// SLABS (a variant of its own, so that the others carry neither its arguments nor its code): the rows are (token, head) pairs of a [T, H, d] tensor and the output is
 // regrouped into H / slab_heads slabs of slab_heads heads each, [slab][token][head in slab]
 // (what the pre-attention all-to-all of sequence-parallel inference sends to each peer).
 // --------------------------------------------------------------------------
-template <bool CONTIG, bool SEARCH = false, bool SMOOTH = false>
+template <bool CONTIG, bool SEARCH = false, bool SMOOTH = false, bool SLABS = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SEARCH ? 8 : 4)))   // at most 64 / 128 registers
 void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
                                                             int64_t C, int64_t ld,
@@ -165,7 +165,9 @@ void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
                                                             uint8_t *__restrict__ scales,
                                                             float *__restrict__ gs_out,
                                                             const uint16_t *__restrict__ row_mean = nullptr,
-                                                            int heads = 0, int slab_heads = 0, int row_shift = 0)
+                                                            int row_shift = 0, Divisor by_row = Divisor(),
+                                                            int64_t heads = 0, int64_t slab_heads = 0,
+                                                            Divisor by_heads = Divisor(), Divisor by_slab = Divisor())
 {
     __shared__ uint32_t lds4[4];
     const int64_t nb_row = C >> 4;
@@ -183,7 +185,7 @@ void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
                 int64_t off;
                 if (CONTIG) off = g << 4;
                 else {
-                    int64_t r = g / nb_row;
+                    int64_t r = divide(g, nb_row, by_row);
                     off = r * ld + ((g - r * nb_row) << 4);
                 }
                 const uint4v *p = (const uint4v *)(x + off);
@@ -200,6 +202,7 @@ void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
     const float sg = resolve_global_scale(gs_in, partial, n_partial, gs_out, lds4);
     if constexpr (SEARCH) fetch(first);
     const TensorScale ts = tensor_scale(sg);
+    const int64_t tokens = SLABS ? divide(R, heads, by_heads) : 0;
     for (int64_t g0 = first; g0 < nblk; g0 += stride * U) {
         if (g0 != first) fetch(g0);
 #pragma unroll
@@ -215,11 +218,11 @@ void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
                 else quantize_block16(w, ts, sbyte, c0, c1);
                 uint2v cc = {c0, c1};
                 int64_t go = g;                       // output block index
-                if (slab_heads > 0) {
-                    const int64_t row = g / nb_row, b = g - row * nb_row;
-                    const int64_t t = row / heads, h = row - t * heads;
-                    const int64_t slab = h / slab_heads, hl = h - slab * slab_heads;
-                    go = ((slab * (R / heads) + t) * slab_heads + hl) * nb_row + b;
+                if constexpr (SLABS) {
+                    const int64_t row = divide(g, nb_row, by_row), b = g - row * nb_row;
+                    const int64_t t = divide(row, heads, by_heads), h = row - t * heads;
+                    const int64_t slab = divide(h, slab_heads, by_slab), hl = h - slab * slab_heads;
+                    go = ((slab * tokens + t) * slab_heads + hl) * nb_row + b;
                 }
                 __builtin_nontemporal_store(cc, (uint2v *)(codes + (go << 3)));
                 scales[go] = (uint8_t)sbyte;
@@ -795,12 +798,13 @@ hipError_t launch_amax(const uint16_t *x, int64_t R, int64_t C, int64_t ld, uint
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(want, kAmaxGrid));
     *n_partial = grid;
     const bool stream = (uint64_t)R * (uint64_t)C * 2u > (256ull << 20);
+    const Divisor by_row(C >> 3, R * (C >> 3));
     if (ld == C) {
-        if (stream) amax_partial_kernel<true, true><<<grid, kAmaxThreads, 0, s>>>(x, R, C, ld, partial);
-        else amax_partial_kernel<true, false><<<grid, kAmaxThreads, 0, s>>>(x, R, C, ld, partial);
+        if (stream) amax_partial_kernel<true, true><<<grid, kAmaxThreads, 0, s>>>(x, R, C, ld, partial, by_row);
+        else amax_partial_kernel<true, false><<<grid, kAmaxThreads, 0, s>>>(x, R, C, ld, partial, by_row);
     } else {
-        if (stream) amax_partial_kernel<false, true><<<grid, kAmaxThreads, 0, s>>>(x, R, C, ld, partial);
-        else amax_partial_kernel<false, false><<<grid, kAmaxThreads, 0, s>>>(x, R, C, ld, partial);
+        if (stream) amax_partial_kernel<false, true><<<grid, kAmaxThreads, 0, s>>>(x, R, C, ld, partial, by_row);
+        else amax_partial_kernel<false, false><<<grid, kAmaxThreads, 0, s>>>(x, R, C, ld, partial, by_row);
     }
     return hipGetLastError();
 }
@@ -816,19 +820,20 @@ hipError_t launch_quantize_rows(const uint16_t *x, int64_t R, int64_t C, int64_t
                                 float *gs_out, hipStream_t s, bool scale_search)
 {
     int grid = grid_for(R * (C >> 4), kQuantMaxGrid);
+    const Divisor by_row(C >> 4, R * (C >> 4));
     if (scale_search) {
         if (ld == C)
             quantize_rows_kernel<true, true><<<grid, 256, 0, s>>>(x, R, C, ld, gs_in, partial, n_partial, codes,
                                                                   scales, gs_out);
         else
             quantize_rows_kernel<false, true><<<grid, 256, 0, s>>>(x, R, C, ld, gs_in, partial, n_partial, codes,
-                                                                   scales, gs_out);
+                                                                   scales, gs_out, nullptr, 0, by_row);
     } else if (ld == C)
         quantize_rows_kernel<true><<<grid, 256, 0, s>>>(x, R, C, ld, gs_in, partial, n_partial, codes,
                                                         scales, gs_out);
     else
         quantize_rows_kernel<false><<<grid, 256, 0, s>>>(x, R, C, ld, gs_in, partial, n_partial, codes,
-                                                         scales, gs_out);
+                                                         scales, gs_out, nullptr, 0, by_row);
     return hipGetLastError();
 }
 
@@ -889,8 +894,9 @@ hipError_t launch_quantize_rows_slabs(const uint16_t *x, int64_t T, int64_t H, i
                                       uint8_t *codes, uint8_t *scales, float *gs_out, hipStream_t s)
 {
     int grid = grid_for(T * H * (d >> 4), kQuantMaxGrid);
-    quantize_rows_kernel<true, false, false><<<grid, 256, 0, s>>>(x, T * H, d, d, gs_in, partial, n_partial, codes,
-                                                                  scales, gs_out, nullptr, (int)H, slab_heads);
+    quantize_rows_kernel<true, false, false, true><<<grid, 256, 0, s>>>(x, T * H, d, d, gs_in, partial, n_partial, codes,
+                                                                  scales, gs_out, nullptr, 0, Divisor(d >> 4, T * H * (d >> 4)),
+                                                                  H, slab_heads, Divisor(H, T * H + 1), Divisor(slab_heads, H));
     return hipGetLastError();
 }
 
@@ -910,7 +916,7 @@ hipError_t launch_quantize_rows_smooth(const uint16_t *x, int64_t rows, int d, c
 {
     int grid = grid_for(rows * (d >> 4), kQuantMaxGrid);
     quantize_rows_kernel<true, true, true><<<grid, 256, 0, s>>>(x, rows, d, d, nullptr, partial, n_partial, codes,
-                                                                scales, gs_out, row_mean, 0, 0,
+                                                                scales, gs_out, row_mean,
                                                                 __builtin_ctz((unsigned)(d >> 4)));
     return hipGetLastError();
 }

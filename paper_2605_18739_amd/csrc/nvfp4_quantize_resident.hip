@@ -63,15 +63,16 @@ struct ResidentArgs {
     // slab_heads > 0: the rows are (token, head) pairs of a [T, H, d] tensor and the output is regrouped into
     // H / slab_heads slabs of slab_heads heads each, [slab][token][head in slab] (the all-to-all send buffers)
     uint32_t nb_row, heads, slab_heads, tokens;
+    Divisor by_row, by_heads, by_slab;
 };
 
-// output block index of input block g (fewer than 2^32 blocks fit on the chip: 32-bit arithmetic)
+// output block index of input block g (fewer than 2^31 blocks fit on the chip: 32-bit arithmetic)
 __device__ __forceinline__ uint32_t output_block(uint32_t g, const ResidentArgs &a)
 {
     if (a.slab_heads == 0) return g;
-    const uint32_t row = g / a.nb_row, b = g - row * a.nb_row;
-    const uint32_t t = row / a.heads, h = row - t * a.heads;
-    const uint32_t slab = h / a.slab_heads, hl = h - slab * a.slab_heads;
+    const uint32_t row = a.by_row.small(g), b = g - row * a.nb_row;
+    const uint32_t t = a.by_heads.small(row), h = row - t * a.heads;
+    const uint32_t slab = a.by_slab.small(h), hl = h - slab * a.slab_heads;
     return ((slab * a.tokens + t) * a.slab_heads + hl) * a.nb_row + b;
 }
 
@@ -411,6 +412,11 @@ hipError_t launch_quantize_rows_resident(const uint16_t *x, int64_t rows, int64_
     a.heads = (uint32_t)heads;
     a.slab_heads = (uint32_t)slab_heads;
     a.tokens = heads > 0 ? (uint32_t)(rows / heads) : 0u;
+    if (slab_heads > 0) {
+        a.by_row = Divisor(C >> 4, a.nblk);
+        a.by_heads = Divisor(heads, rows);
+        a.by_slab = Divisor(slab_heads, heads);
+    }
     if (mean_out) return launch_resident<true, true>(a, grid, s);       // smoothed keys always take the scale search
     return scale_search ? launch_resident<true, false>(a, grid, s) : launch_resident<false, false>(a, grid, s);
 }

@@ -86,6 +86,16 @@ def test_quantize_given_scale_and_stride(oracle):
         assert_q_equal(nv.nvfp4_quantize(view, global_scale_in=gsd), oq, f"given scale {gs}")
 
 
+@pytest.mark.parametrize("R,C,ld", [(1, 16, 24), (700, 16, 24), (333, 48, 56), (129, 1008, 1016), (1000, 3088, 3104), (65, 4096, 4104)])
+@pytest.mark.parametrize("search", [False, True])
+def test_quantize_padded_rows_of_many_widths(oracle, R, C, ld, search):
+    """Rows cut out of a wider buffer: the kernels find a block's row by dividing by the width (one block, powers of two, odd)."""
+    xb = wl.to_bf16_bits(np.random.default_rng(R + C).standard_normal((R, ld)).astype(np.float32))
+    want = oracle.quantize(np.ascontiguousarray(xb[:, :C]), four_over_six=search)
+    view = dev_bf16(xb)[:, :C]
+    assert_q_equal(nv.nvfp4_quantize_4over6(view) if search else nv.nvfp4_quantize(view), want, f"{R}x{C} of {ld}")
+
+
 @pytest.mark.parametrize("offset", [0.0, 2.0 ** -23, -2.0 ** -23, 2.0 ** -19, -2.0 ** -19, -2.0 ** -17, 2.0 ** -16])
 def test_quantize_tensor_scales_on_and_beside_ties(oracle, offset):
     """Given scales (bf16 number) / (odd number below 128), and the same a little off: elements and block maxima of
@@ -806,6 +816,21 @@ def test_quantize_for_all_to_all(oracle, T, H, d, P):
     back = nv.bits_from_bf16(nv.nvfp4_kv_dequant(slab, T, Hp, d)).reshape(T, Hp, d)
     ref = oracle.dequant_bf16(want).reshape(T, H, d)[:, p * Hp:(p + 1) * Hp]
     assert (back == ref).all()
+
+
+@pytest.mark.parametrize("mode", [1, 2])            # one launch, two passes
+@pytest.mark.parametrize("T,H,d,P", [(1, 1, 16, 1), (9, 7, 48, 7), (31, 15, 80, 5), (100, 22, 96, 2), (64, 16, 64, 4)])
+def test_all_to_all_slabs_of_odd_widths_in_both_forms(oracle, T, H, d, P, mode):
+    """Widths and head counts that are no powers of two: the slab order divides by each of them."""
+    xb = wl.kv_tensor(T, H, d, 28, T).reshape(T * H, d)
+    want = oracle.quantize(xb)
+    nv.nvfp4_set_one_launch(mode)
+    try:
+        codes, scales, _ = host_q(nv.nvfp4_quantize_for_all_to_all(dev_bf16(xb).reshape(T, H, d), P))
+    finally:
+        nv.nvfp4_set_one_launch()
+    perm = lambda a: a.reshape(T, P, H // P, -1).transpose(1, 0, 2, 3).reshape(T * H, -1)
+    assert (codes == perm(want.codes)).all() and (scales == perm(want.scales)).all()
 
 
 # ----------------------------------------------------- random Hadamard transform

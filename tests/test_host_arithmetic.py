@@ -241,3 +241,21 @@ def test_one_nudge_of_the_tensor_scale_settles_every_near_tie():
                 assert (np.sign(y.astype(np.float64) - float(t)) == exact).all(), (s, t, step, ulp)
                 checked += y.size
     assert checked > 5_000_000
+
+
+def test_division_by_multiplication_is_exact_below_2_to_31():
+    """Divisor in csrc/nvfp4_kernels.h: n / d as (n m) >> (31 + l), l = ceil(log2 d), m = ceil(2^(31+l) / d).  Widths of every
+    size; n beside multiples of d, where a wrong factor shows first, and at both ends."""
+    rng = np.random.default_rng(31)
+    widths = list(range(1, 300)) + [1 << k for k in range(9, 31)] + [(1 << k) + e for k in range(9, 31) for e in (-1, 1)]
+    widths += [int(v) for v in rng.integers(1, 1 << 31, 300)] + [(1 << 31) - 1]
+    for d in widths:
+        l = (d - 1).bit_length()
+        m = -(-(1 << (31 + l)) // d)
+        assert 0 < m < 1 << 32
+        top = ((1 << 31) - 1) // d
+        for q in {0, 1, top, max(0, top - 1), *(int(v) for v in rng.integers(0, top + 1, 20))}:
+            for n in (q * d - 1, q * d, q * d + 1, q * d + d - 1, (1 << 31) - 1):
+                if 0 <= n < 1 << 31:
+                    assert (n * m) >> (31 + l) == n // d
+                    assert n * m < 1 << 64
