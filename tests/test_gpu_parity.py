@@ -371,6 +371,24 @@ def test_calls_on_another_stream_allocate_from_its_pool():
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("rows", [255, 256, 16383, 16384, 16385, 65537, 70000])
+def test_row_encoders_of_every_grid(oracle, rows):
+    """16 blocks a row: one block a lane below 1024 workgroups of 256 (16 384 rows), then up to four a lane, then more workgroups."""
+    say(f"[quantize] {rows} rows of 256")
+    xb = wl.normal((rows, 256), 1.0, 29, rows)
+    x = dev_bf16(xb)
+    nv.nvfp4_set_one_launch(nv.ONE_LAUNCH_NEVER)
+    try:
+        assert_q_equal(nv.nvfp4_quantize(x), oracle.quantize(xb), "plain")
+        assert_q_equal(nv.nvfp4_quantize_4over6(x), oracle.quantize(xb, four_over_six=True), "search")
+        want_mean, want = _oracle_k_path(oracle, xb)
+        got, mean = nv.nvfp4_kv_quant_k(x.reshape(rows, 1, 256))
+    finally:
+        nv.nvfp4_set_one_launch()
+    assert (nv.bits_from_bf16(mean) == want_mean).all()
+    assert_q_equal(got, want, "smoothed")
+
+
 def test_quantize_is_deterministic():
     xb = wl.activation_with_outliers(512, 3072, 1, 0)
     x = dev_bf16(xb)
