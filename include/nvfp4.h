@@ -374,8 +374,8 @@ void nvfp4_set_sync_spin_limit(uint32_t ticks_10ns);
 /* Which form the row quantizers (nvfp4_quantize with block_axis 0, the scale search, nvfp4_kv_quant*,
  * nvfp4_quantize_for_all_to_all; no scale given) take for a tensor that fits on the chip.  The one-launch form
  * fetches the tensor from HBM once, the two-pass form twice.  AUTO (the default) goes by what was measured: for the
- * plain rule one launch below 12 k blocks of 16 and from 0.8 M blocks on, with the scale search from 2.2 M blocks on,
- * two passes otherwise and for smoothed keys; ALWAYS takes the one-launch form whenever
+ * plain rule one launch below 12 k blocks of 16 and from 0.95 M blocks on,
+ * two passes otherwise, with the scale search and for smoothed keys; ALWAYS takes the one-launch form whenever
  * the tensor fits (least HBM traffic); NEVER always streams.
  * The bytes are the same either way.  Applies to calls made afterwards; NVFP4_ERR_SHAPE for another value. */
 enum { NVFP4_ONE_LAUNCH_AUTO = 0, NVFP4_ONE_LAUNCH_ALWAYS = 1, NVFP4_ONE_LAUNCH_NEVER = 2 };

@@ -359,22 +359,22 @@ bool quantize_rows_resident_fits(int64_t rows, int64_t C, int64_t ld, bool smoot
 // fetch it twice, but pays for the exchange across the grid, and its encoding runs at two waves per SIMD where the
 // streaming pass has six to eight.  Measured in one session, calls back to back on inputs in turn that together exceed the
 // 256 MB Infinity Cache (us, one launch / two passes, blocks of 16 elements):
-//   plain rule    1.5 k 5.9 / 8.0   12 k 6.4 / 7.5    192 k 10.1 / 7.9   676 k 13.0 / 13.1   887 k 14.7 / 15.5   1.7 M 21.9 / 24.8   3.5 M 38.0 / 45.9
-//   scale search  1.5 k 6.8 / 8.0   12 k 7.8 / 7.4    192 k 11.8 / 8.7   676 k 17.4 / 15.1   1.7 M 30.2 / 28.9   2.2 M 35.8 / 35.0   2.6 M 41.2 / 42.7   3.5 M 55.1 / 56.8
-//   smoothed keys 1.5 k 7.2 / 8.1   12 k 8.3 / 7.8    192 k 12.6 / 9.8   676 k 19.7 / 17.3   1.7 M 36.8 / 33.3   2.2 M 44.9 / 40.0   3.5 M 64.5 / 59.6
-// So: below 12 k blocks one launch where that saves the second launch (host-bound; replayed from a graph the two passes
-// are ahead there by a microsecond), from there on two passes until the second fetch costs more than the exchange, which
-// is at 0.8 M blocks for the plain rule and between 2.2 M and 2.6 M with the search; smoothed keys two passes
-// throughout.  mode 1: whenever it fits; mode 2: never.
+//   plain rule    12 k 6.5 / 9.3   192 k 10.1 / 9.6   384 k 11.0 / 10.6   676 k 13.1 / 12.5   887 k 14.8 / 14.0   998 k 15.3 / 15.8   1.7 M 21.0 / 23.3   3.5 M 34.6 / 42.7
+//   slabs         12 k 8.8 / 12.4  192 k 10.5 / 13.1  384 k 11.6 / 12.5   676 k 13.3 / 13.5   887 k 15.2 / 15.2   998 k 15.7 / 17.0   1.7 M 21.7 / 23.5   3.5 M 36.2 / 43.8
+//   scale search  12 k 7.6 / 9.1   192 k 11.6 / 9.5   676 k 17.0 / 14.1   1.7 M 29.6 / 26.4   2.2 M 35.1 / 33.0   2.6 M 39.1 / 38.1   3.0 M 44.2 / 41.1   3.5 M 50.6 / 47.8
+//   smoothed keys (with an earlier grid of the two passes) 192 k 12.6 / 9.8   676 k 19.7 / 17.3   3.5 M 64.5 / 59.6
+// So: below 12 k blocks one launch where that saves the second launch (host-bound), from there
+// on two passes until the second fetch costs more than the exchange, at 0.95 M blocks for the plain rule (the slabs, even from
+// 0.7 M to 0.9 M, follow it); with the search, whose encoding wants eight waves per SIMD, two passes throughout.  mode 1:
+// whenever it fits; mode 2: never.
 static int g_one_launch_mode = 0;
 void set_one_launch_mode(int mode) { g_one_launch_mode = mode; }
 bool quantize_rows_resident_pays(int64_t nblk, bool search, bool smooth)
 {
     if (g_one_launch_mode == 1) return true;
     if (g_one_launch_mode == 2) return false;
-    constexpr int64_t kSmall = 12000, kLarge = 800000, kLargeSearch = 2200000;
-    if (smooth) return false;
-    return search ? nblk >= kLargeSearch : nblk < kSmall || nblk >= kLarge;
+    constexpr int64_t kSmall = 12000, kLarge = 950000;
+    return !search && !smooth && (nblk < kSmall || nblk >= kLarge);
 }
 
 template <bool SEARCH, bool SMOOTH>
