@@ -6,11 +6,12 @@
 
 #include <algorithm>
 #include "nvfp4_kernels.h"
+#include "nvfp4_quantize_plan.h"
 
 namespace nvfp4 {
 
-// blocks in flight per lane and the largest grids of the streaming kernels (measured choices)
-constexpr int kQuantUnroll = 2, kDequantUnroll = 4, kQuantMaxGrid = 16384, kDequantMaxGrid = 8192;
+// blocks in flight per lane and the largest grid of the reconstruction (measured choices)
+constexpr int kQuantUnroll = 2, kDequantUnroll = 4, kDequantMaxGrid = 8192;
 
 // --------------------------------------------------------------------------
 // Pass 1: per-workgroup partial amax (largest |bf16| bit pattern).
@@ -791,19 +792,6 @@ static int grid_for(int64_t work_items, int max_grid)
     return (int)(g < max_grid ? g : max_grid);
 }
 
-// Workgroups of a pass that encodes rows: four blocks of 16 elements to a lane, so that what every workgroup does first (the
-// partial maxima again, the scale's tie tests: about as many vector instructions as a plain block) is paid once for four blocks,
-// but at least kQuantMinGrid workgroups (four to a compute unit), or one block a lane where there are fewer.  With one block a
-// lane up to the largest grid: 3520x24x128, smoothed keys and values with the search 31.0 us -> 30.0; 3520x3072 and 3520x14336
-// in front of their GEMMs 0.6 us and 4 us less.  Two blocks a lane changed nothing (31.0), at least 768 workgroups less
-// (30.5), 2048 as much (30.0); at most 1024 or 2048 for every size cost the 505 MB gradient 8 us.
-constexpr int kQuantMinGrid = 1024, kQuantBlocksPerLane = 4;
-static int grid_rows(int64_t nblk)
-{
-    const int64_t few = (nblk + 256 * kQuantBlocksPerLane - 1) / (256 * kQuantBlocksPerLane);
-    return grid_for(std::max<int64_t>(few * 256, std::min<int64_t>(nblk, 256 * kQuantMinGrid)), kQuantMaxGrid);
-}
-
 hipError_t launch_amax(const uint16_t *x, int64_t R, int64_t C, int64_t ld, uint32_t *partial,
                        int *n_partial, hipStream_t s)
 {
@@ -832,7 +820,7 @@ hipError_t launch_quantize_rows(const uint16_t *x, int64_t R, int64_t C, int64_t
                                 const uint32_t *partial, int n_partial, uint8_t *codes, uint8_t *scales,
                                 float *gs_out, hipStream_t s, bool scale_search)
 {
-    const int grid = grid_rows(R * (C >> 4));
+    const int grid = encode_rows_grid(R * (C >> 4), gs_in != nullptr);
     const Divisor by_row(C >> 4, R * (C >> 4));
     if (scale_search) {
         if (ld == C)
@@ -906,7 +894,7 @@ hipError_t launch_quantize_rows_slabs(const uint16_t *x, int64_t T, int64_t H, i
                                       const float *gs_in, const uint32_t *partial, int n_partial,
                                       uint8_t *codes, uint8_t *scales, float *gs_out, hipStream_t s)
 {
-    const int grid = grid_rows(T * H * (d >> 4));
+    const int grid = encode_rows_grid(T * H * (d >> 4), gs_in != nullptr);
     quantize_rows_kernel<true, false, false, true><<<grid, 256, 0, s>>>(x, T * H, d, d, gs_in, partial, n_partial, codes,
                                                                   scales, gs_out, nullptr, 0, Divisor(d >> 4, T * H * (d >> 4)),
                                                                   H, slab_heads, Divisor(H, T * H + 1), Divisor(slab_heads, H));
@@ -927,7 +915,7 @@ hipError_t launch_quantize_rows_smooth(const uint16_t *x, int64_t rows, int d, c
                                        const uint32_t *partial, int n_partial, uint8_t *codes,
                                        uint8_t *scales, float *gs_out, hipStream_t s)
 {
-    const int grid = grid_rows(rows * (d >> 4));
+    const int grid = encode_rows_grid(rows * (d >> 4), false);
     quantize_rows_kernel<true, true, true><<<grid, 256, 0, s>>>(x, rows, d, d, nullptr, partial, n_partial, codes,
                                                                 scales, gs_out, row_mean,
                                                                 __builtin_ctz((unsigned)(d >> 4)));

@@ -1,0 +1,32 @@
+// Launch rules of the row quantizers: plain C++ without HIP types, so that they can be compiled and exercised on their
+// own (tests build them with the address and undefined-behaviour sanitizers).
+#ifndef NVFP4_QUANTIZE_PLAN_H
+#define NVFP4_QUANTIZE_PLAN_H
+
+#include <algorithm>
+#include <cstdint>
+
+namespace nvfp4 {
+
+// Workgroups of 256 lanes of a pass that encodes rows of `nblk` blocks of 16 elements.
+// With partial maxima: four blocks to a lane, so that what every workgroup does first (the partial maxima again, the scale's tie
+// tests: about as many vector instructions as a plain block) is paid once for four blocks, but at least kQuantMinGrid
+// workgroups (four to a compute unit), or one block a lane where there are fewer.  With one block a lane up to the largest
+// grid: 3520x24x128, smoothed keys and values with the search 31.0 us -> 30.0; 3520x3072 and 3520x14336
+// in front of their GEMMs 0.6 us and 4 us less.  Two blocks a lane changed nothing (31.0), at least 768 workgroups less
+// (30.5), 2048 as much (30.0); at most 1024 or 2048 for every size cost the 505 MB gradient 8 us.
+// With a given scale there are no maxima to reduce, and one block a lane, up to the largest grid, has the most loads in
+// flight (us, one / four blocks a lane; replayed from a graph on inputs in turn that exceed the 256 MB
+// Infinity Cache): plain 0.7 M 7.0 / 7.0, 1.2 M 10.0 / 11.0, 1.7 M 13.6 / 14.8, 3.5 M 25.9 / 27.5, 5.0 M 36.3 / 39.0, 8.1 M
+// 58.7 / 60.5, 12 M 87.5 / 88.8; with the search 1.2 M 11.6 / 12.9, 3.5 M 28.7 / 29.1, 5.0 M 41.0 / 40.7, 8.1 M 63 / 63.
+constexpr int kQuantMaxGrid = 16384, kQuantMinGrid = 1024, kQuantBlocksPerLane = 4;
+
+inline int encode_rows_grid(int64_t nblk, bool given_scale)
+{
+    const int64_t per_lane = given_scale ? 1 : kQuantBlocksPerLane;
+    const int64_t all = (nblk + 255) / 256, few = (nblk + 256 * per_lane - 1) / (256 * per_lane);
+    return (int)std::min<int64_t>(kQuantMaxGrid, std::max<int64_t>(few, std::min<int64_t>(all, kQuantMinGrid)));
+}
+
+}  // namespace nvfp4
+#endif
