@@ -820,7 +820,7 @@ hipError_t launch_quantize_rows(const uint16_t *x, int64_t R, int64_t C, int64_t
                                 const uint32_t *partial, int n_partial, uint8_t *codes, uint8_t *scales,
                                 float *gs_out, hipStream_t s, bool scale_search)
 {
-    const int grid = encode_rows_grid(R * (C >> 4), gs_in != nullptr);
+    const int grid = encode_rows_grid(R * (C >> 4), gs_in != nullptr, scale_search);
     const Divisor by_row(C >> 4, R * (C >> 4));
     if (scale_search) {
         if (ld == C)
@@ -894,7 +894,7 @@ hipError_t launch_quantize_rows_slabs(const uint16_t *x, int64_t T, int64_t H, i
                                       const float *gs_in, const uint32_t *partial, int n_partial,
                                       uint8_t *codes, uint8_t *scales, float *gs_out, hipStream_t s)
 {
-    const int grid = encode_rows_grid(T * H * (d >> 4), gs_in != nullptr);
+    const int grid = encode_rows_grid(T * H * (d >> 4), gs_in != nullptr, false);
     quantize_rows_kernel<true, false, false, true><<<grid, 256, 0, s>>>(x, T * H, d, d, gs_in, partial, n_partial, codes,
                                                                   scales, gs_out, nullptr, 0, Divisor(d >> 4, T * H * (d >> 4)),
                                                                   H, slab_heads, Divisor(H, T * H + 1), Divisor(slab_heads, H));
@@ -915,7 +915,7 @@ hipError_t launch_quantize_rows_smooth(const uint16_t *x, int64_t rows, int d, c
                                        const uint32_t *partial, int n_partial, uint8_t *codes,
                                        uint8_t *scales, float *gs_out, hipStream_t s)
 {
-    const int grid = encode_rows_grid(rows * (d >> 4), false);
+    const int grid = encode_rows_grid(rows * (d >> 4), false, true);
     quantize_rows_kernel<true, true, true><<<grid, 256, 0, s>>>(x, rows, d, d, nullptr, partial, n_partial, codes,
                                                                 scales, gs_out, row_mean,
                                                                 __builtin_ctz((unsigned)(d >> 4)));

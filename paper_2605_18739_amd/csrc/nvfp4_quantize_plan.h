@@ -15,15 +15,21 @@ namespace nvfp4 {
 // grid: 3520x24x128, smoothed keys and values with the search 31.0 us -> 30.0; 3520x3072 and 3520x14336
 // in front of their GEMMs 0.6 us and 4 us less.  Two blocks a lane changed nothing (31.0), at least 768 workgroups less
 // (30.5), 2048 as much (30.0); at most 1024 or 2048 for every size cost the 505 MB gradient 8 us.
+// The plain rule keeps two blocks in flight a lane (the search one), and from kQuantLarge blocks on, where two blocks a lane
+// are at least 2930 workgroups, two are as good or better: one turn a lane, nothing waits for a second fetch.  Whole call
+// in two passes, us, one / two / four blocks a lane: 0.7 M 12.6 / 12.4 / 11.9, 0.9 M 15.2 / 14.7 / 14.2, 1.2 M 17.6 / 17.2 / 16.8,
+// 1.7 M 23.3 / 22.9 / 23.4, 3.5 M 43.1 / 42.0 / 42.6, 5.0 M 58.7 / 58.1 / 58.9, 8.1 M 93.6 / 92.3 / 94.3, 10 M 122.1 / 122.3 / 123.4,
+// 15.8 M 193.6 / 193.6 / 192.7; rows of a wider buffer the same within 0.3 us but for 1.7 M, 24.2 / 23.4 / 23.0.  With the
+// search four throughout: 1.7 M 28.2 / 26.9 / 26.6, 3.5 M 52.2 / 49.0 / 47.8, 8.1 M 106 / 106 / 102, from 12 M on even.
 // With a given scale there are no maxima to reduce, and one block a lane, up to the largest grid, has the most loads in
 // flight (us, one / four blocks a lane; replayed from a graph on inputs in turn that exceed the 256 MB
 // Infinity Cache): plain 0.7 M 7.0 / 7.0, 1.2 M 10.0 / 11.0, 1.7 M 13.6 / 14.8, 3.5 M 25.9 / 27.5, 5.0 M 36.3 / 39.0, 8.1 M
 // 58.7 / 60.5, 12 M 87.5 / 88.8; with the search 1.2 M 11.6 / 12.9, 3.5 M 28.7 / 29.1, 5.0 M 41.0 / 40.7, 8.1 M 63 / 63.
-constexpr int kQuantMaxGrid = 16384, kQuantMinGrid = 1024, kQuantBlocksPerLane = 4;
+constexpr int kQuantMaxGrid = 16384, kQuantMinGrid = 1024, kQuantBlocksPerLane = 4, kQuantLarge = 1500000;
 
-inline int encode_rows_grid(int64_t nblk, bool given_scale)
+inline int encode_rows_grid(int64_t nblk, bool given_scale, bool search)
 {
-    const int64_t per_lane = given_scale ? 1 : kQuantBlocksPerLane;
+    const int64_t per_lane = given_scale ? 1 : !search && nblk >= kQuantLarge ? 2 : kQuantBlocksPerLane;
     const int64_t all = (nblk + 255) / 256, few = (nblk + 256 * per_lane - 1) / (256 * per_lane);
     return (int)std::min<int64_t>(kQuantMaxGrid, std::max<int64_t>(few, std::min<int64_t>(all, kQuantMinGrid)));
 }

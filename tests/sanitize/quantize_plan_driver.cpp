@@ -15,15 +15,18 @@ static void require(bool ok, const char *what, long long n)
 }
 
 // Where nothing is reduced at a workgroup's head (a given scale) a lane takes one block, up to the largest grid; with partial
-// maxima at most four, and no fewer than 1024 workgroups while there are blocks for them.
+// maxima at most four (the plain rule two, as many as it holds in flight, from 1.5 M blocks on), and no fewer than 1024 workgroups while there are
+// blocks for them.
 static void check_grid(int64_t nblk)
 {
     const int64_t one_a_lane = std::min<int64_t>((nblk + 255) / 256, 16384);
-    require(encode_rows_grid(nblk, true) == one_a_lane, "given scale: one block a lane", nblk);
-    const int64_t g = encode_rows_grid(nblk, false);
-    require(g >= 1 && g <= one_a_lane, "a workgroup without a block", nblk);
-    require(g >= std::min<int64_t>(one_a_lane, 1024), "fewer workgroups than four to a compute unit", nblk);
-    require(g == 16384 || g * 256 * 4 >= nblk, "more than four blocks a lane below the largest grid", nblk);
+    for (bool search : {false, true}) {
+        require(encode_rows_grid(nblk, true, search) == one_a_lane, "given scale: one block a lane", nblk);
+        const int64_t g = encode_rows_grid(nblk, false, search), most = !search && nblk >= 1500000 ? 2 : 4;
+        require(g >= 1 && g <= one_a_lane, "a workgroup without a block", nblk);
+        require(g >= std::min<int64_t>(one_a_lane, 1024), "fewer workgroups than four to a compute unit", nblk);
+        require(g == 16384 || g * 256 * most >= nblk, "too many blocks a lane below the largest grid", nblk);
+    }
 }
 
 int main()
@@ -31,7 +34,7 @@ int main()
     for (int64_t b = 1; b <= (1ll << 40); b <<= 1)
         for (int64_t e : {-1, 0, 1, 255, 257})
             if (b + e > 0) check_grid(b + e);
-    for (int64_t b : {256 * 1024, 4 * 256 * 1024, 256 * 16384, 4 * 256 * 16384})
+    for (int64_t b : {256 * 1024, 4 * 256 * 1024, 1500000, 256 * 16384, 2 * 256 * 16384, 4 * 256 * 16384})
         for (int64_t e = -2; e <= 2; ++e) check_grid(b + e);
     std::printf("ok\n");
     return 0;
