@@ -253,9 +253,10 @@ int nvfp4_kv_quant(const void *kv_bf16, int64_t T, int64_t H, int64_t d, nvfp4_t
  * hipMalloc.  Same arguments and the same bytes as nvfp4_kv_quant, minus the workspace: the
  * partial maxima live in a fixed array inside the library's device image (4 KB on every GPU
  * the library runs on, held until the process ends; its address is looked up on the first
- * call on a device).  Windows for which the one-launch kernel is taken (see nvfp4_set_one_launch) need
- * no partial maxima and leave the array alone; the others take the two passes that use it.  The call allocates nothing, frees nothing and calls no allocating
- * routine; launch timing does not record it.
+ * call on a device).  Windows for which the one-launch kernel is taken (as nvfp4_set_one_launch says, by default
+ * from 0.8 M blocks on already) need no partial maxima and leave the array alone; the others take the two passes
+ * that use it.  The call allocates nothing, frees nothing and calls no allocating routine; launch timing does not
+ * record it.
  * Limit: T * H * d <= NVFP4_NOALLOC_MAX_ELEMENTS, NVFP4_ERR_SHAPE beyond it.
  * All calls on one GPU share that array, and it keeps the last call's contents (every slot a
  * call reads it has written before, so nothing needs clearing): calls that overlap on one GPU

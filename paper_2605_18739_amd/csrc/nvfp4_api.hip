@@ -74,7 +74,7 @@ size_t fused_partial_bytes(int64_t M, int64_t N)
 
 int quantize_impl(const void *x, int64_t R, int64_t C, int64_t ld, int block_axis,
                   const float *gs_in, nvfp4_tensor *out, void *ws, size_t ws_bytes, hipStream_t s,
-                  bool scale_search = false)
+                  bool scale_search = false, bool library_scratch = false)
 {
     if (!x || !out) return NVFP4_ERR_NULL;
     if (int rc = check_tensor(out)) return rc;
@@ -91,7 +91,7 @@ int quantize_impl(const void *x, int64_t R, int64_t C, int64_t ld, int block_axi
     uint32_t *partial = static_cast<uint32_t *>(ws);
     int n_partial = 0;
     if (!gs_in && block_axis == 0 && quantize_rows_resident_fits(R, C, ld, false) &&
-        quantize_rows_resident_pays(R * (C >> 4), scale_search, false)) {
+        quantize_rows_resident_pays(R * (C >> 4), scale_search, false, library_scratch)) {
         // the tensor fits on the chip (and is of a size at which that pays): one launch, one pass over the input
         hipError_t e = launch_quantize_rows_resident(xb, R, C, out->codes, out->scales, out->global_scale,
                                                      scale_search, nullptr, s);
@@ -167,7 +167,7 @@ int nvfp4_kv_quant_noalloc(const void *kv_bf16, int64_t T, int64_t H, int64_t d,
     uint32_t *ws = nullptr;
     if (int rc = scratch_on_current_device(&ws)) return rc;
     // no launch timing here: recording it would create events on first use
-    return quantize_impl(kv_bf16, T * H, d, d, 0, nullptr, out, ws, kPartialBytes, static_cast<hipStream_t>(stream));
+    return quantize_impl(kv_bf16, T * H, d, d, 0, nullptr, out, ws, kPartialBytes, static_cast<hipStream_t>(stream), false, true);
 }
 
 int nvfp4_quantize_4over6(const void *x_bf16, int64_t R, int64_t C, int64_t ld,

@@ -34,5 +34,16 @@ inline int encode_rows_grid(int64_t nblk, bool given_scale, bool search)
     return (int)std::min<int64_t>(kQuantMaxGrid, std::max<int64_t>(few, std::min<int64_t>(all, kQuantMinGrid)));
 }
 
+// Whether a tensor that fits on the chip takes the one-launch form (the figures stand in nvfp4_quantize_resident.hip).
+// library_scratch: the two passes would keep their partial maxima in the library's one array per GPU, where calls that overlap
+// race, while the exchange words of the one-launch form are one of 64 sets; such calls keep the lower bound, at which
+// the two forms are within a microsecond (0.8 M to 0.95 M blocks: one launch 14.5 to 15.2 us, two passes 13.4 to 15.2).
+constexpr int64_t kOneLaunchBelow = 12000, kOneLaunchFrom = 950000, kOneLaunchFromScratch = 800000;
+
+inline bool one_launch_pays(int64_t nblk, bool search, bool smooth, bool library_scratch)
+{
+    return !search && !smooth && (nblk < kOneLaunchBelow || nblk >= (library_scratch ? kOneLaunchFromScratch : kOneLaunchFrom));
+}
+
 }  // namespace nvfp4
 #endif

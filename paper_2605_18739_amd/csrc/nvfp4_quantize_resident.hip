@@ -16,6 +16,7 @@
 
 #include <algorithm>
 #include "nvfp4_kernels.h"
+#include "nvfp4_quantize_plan.h"
 
 #include <type_traits>
 
@@ -369,12 +370,11 @@ bool quantize_rows_resident_fits(int64_t rows, int64_t C, int64_t ld, bool smoot
 // whenever it fits; mode 2: never.
 static int g_one_launch_mode = 0;
 void set_one_launch_mode(int mode) { g_one_launch_mode = mode; }
-bool quantize_rows_resident_pays(int64_t nblk, bool search, bool smooth)
+bool quantize_rows_resident_pays(int64_t nblk, bool search, bool smooth, bool library_scratch)
 {
     if (g_one_launch_mode == 1) return true;
     if (g_one_launch_mode == 2) return false;
-    constexpr int64_t kSmall = 12000, kLarge = 950000;
-    return !search && !smooth && (nblk < kSmall || nblk >= kLarge);
+    return one_launch_pays(nblk, search, smooth, library_scratch);
 }
 
 template <bool SEARCH, bool SMOOTH>

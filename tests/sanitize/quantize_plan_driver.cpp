@@ -29,6 +29,18 @@ static void check_grid(int64_t nblk)
     }
 }
 
+// The search and the smoothed keys take two passes; the plain rule one launch below 12 k and from 0.95 M blocks on, and from 0.8 M on
+// where the two passes would share the library's scratch array.
+static void check_one_launch()
+{
+    for (int64_t n : {1, 11999, 12000, 799999, 800000, 887040, 949999, 950000, 3800000}) {
+        for (bool scratch : {false, true}) {
+            require(!one_launch_pays(n, true, false, scratch) && !one_launch_pays(n, true, true, scratch), "search in one launch", n);
+            require(one_launch_pays(n, false, false, scratch) == (n < 12000 || n >= (scratch ? 800000 : 950000)), "plain rule", n);
+        }
+    }
+}
+
 int main()
 {
     for (int64_t b = 1; b <= (1ll << 40); b <<= 1)
@@ -36,6 +48,7 @@ int main()
             if (b + e > 0) check_grid(b + e);
     for (int64_t b : {256 * 1024, 4 * 256 * 1024, 1500000, 256 * 16384, 2 * 256 * 16384, 4 * 256 * 16384})
         for (int64_t e = -2; e <= 2; ++e) check_grid(b + e);
+    check_one_launch();
     std::printf("ok\n");
     return 0;
 }
