@@ -5,6 +5,8 @@
 #include "nvfp4_device.h"
 
 #include <algorithm>
+#include <type_traits>
+
 #include "nvfp4_kernels.h"
 #include "nvfp4_quantize_plan.h"
 
@@ -152,10 +154,18 @@ __global__ __launch_bounds__(1024) void scale_from_partials_kernel(const uint32_
 // (two 128-bit loads, one 64-bit code store, one scale byte).
 // SEARCH: the Four-over-Six scale search of Eq. 12-13 instead of the plain max -> 6 rule.
 // SMOOTH: the row means of Eq. 6 (row_mean, one bf16 per row) are removed first.
-// SLABS (a variant of its own, so that the others carry neither its arguments nor its code): the rows are (token, head) pairs of a [T, H, d] tensor and the output is
+// SLABS: the rows are (token, head) pairs of a [T, H, d] tensor and the output is
 // regrouped into H / slab_heads slabs of slab_heads heads each, [slab][token][head in slab]
 // (what the pre-attention all-to-all of sequence-parallel inference sends to each peer).
+// The widths that strided rows and slabs divide by are an argument of those variants alone: the others neither carry
+// them nor pay for the host's computing them.
 // --------------------------------------------------------------------------
+struct NoWidths {};
+struct RowWidth { Divisor by_row; };                                            // strided: blocks of a row
+struct SlabWidths { int64_t heads, slab_heads; Divisor by_row, by_heads, by_slab; };
+template <bool CONTIG, bool SLABS>
+using Widths = std::conditional_t<SLABS, SlabWidths, std::conditional_t<CONTIG, NoWidths, RowWidth>>;
+
 template <bool CONTIG, bool SEARCH = false, bool SMOOTH = false, bool SLABS = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SEARCH ? 8 : 4)))   // at most 64 / 128 registers
 void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
@@ -166,9 +176,7 @@ void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
                                                             uint8_t *__restrict__ scales,
                                                             float *__restrict__ gs_out,
                                                             const uint16_t *__restrict__ row_mean = nullptr,
-                                                            int row_shift = 0, Divisor by_row = Divisor(),
-                                                            int64_t heads = 0, int64_t slab_heads = 0,
-                                                            Divisor by_heads = Divisor(), Divisor by_slab = Divisor())
+                                                            int row_shift = 0, Widths<CONTIG, SLABS> widths = {})
 {
     __shared__ uint32_t lds4[4];
     const int64_t nb_row = C >> 4;
@@ -184,9 +192,9 @@ void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
             const int64_t g = g0 + u * stride;
             if (g < nblk) {
                 int64_t off;
-                if (CONTIG) off = g << 4;
+                if constexpr (CONTIG) off = g << 4;
                 else {
-                    int64_t r = divide(g, nb_row, by_row);
+                    int64_t r = divide(g, nb_row, widths.by_row);
                     off = r * ld + ((g - r * nb_row) << 4);
                 }
                 const uint4v *p = (const uint4v *)(x + off);
@@ -203,7 +211,8 @@ void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
     const float sg = resolve_global_scale(gs_in, partial, n_partial, gs_out, lds4);
     if constexpr (SEARCH) fetch(first);
     const TensorScale ts = tensor_scale(sg);
-    const int64_t tokens = SLABS ? divide(R, heads, by_heads) : 0;
+    int64_t tokens = 0;
+    if constexpr (SLABS) tokens = divide(R, widths.heads, widths.by_heads);
     for (int64_t g0 = first; g0 < nblk; g0 += stride * U) {
         if (g0 != first) fetch(g0);
 #pragma unroll
@@ -220,10 +229,10 @@ void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t R,
                 uint2v cc = {c0, c1};
                 int64_t go = g;                       // output block index
                 if constexpr (SLABS) {
-                    const int64_t row = divide(g, nb_row, by_row), b = g - row * nb_row;
-                    const int64_t t = divide(row, heads, by_heads), h = row - t * heads;
-                    const int64_t slab = divide(h, slab_heads, by_slab), hl = h - slab * slab_heads;
-                    go = ((slab * tokens + t) * slab_heads + hl) * nb_row + b;
+                    const int64_t row = divide(g, nb_row, widths.by_row), b = g - row * nb_row;
+                    const int64_t t = divide(row, widths.heads, widths.by_heads), h = row - t * widths.heads;
+                    const int64_t slab = divide(h, widths.slab_heads, widths.by_slab), hl = h - slab * widths.slab_heads;
+                    go = ((slab * tokens + t) * widths.slab_heads + hl) * nb_row + b;
                 }
                 __builtin_nontemporal_store(cc, (uint2v *)(codes + (go << 3)));
                 scales[go] = (uint8_t)sbyte;
@@ -799,7 +808,7 @@ hipError_t launch_amax(const uint16_t *x, int64_t R, int64_t C, int64_t ld, uint
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(want, kAmaxGrid));
     *n_partial = grid;
     const bool stream = (uint64_t)R * (uint64_t)C * 2u > (256ull << 20);
-    const Divisor by_row(C >> 3, R * (C >> 3));
+    const Divisor by_row = ld == C ? Divisor() : Divisor(C >> 3, R * (C >> 3));     // (contiguous rows divide by nothing)
     if (ld == C) {
         if (stream) amax_partial_kernel<true, true><<<grid, kAmaxThreads, 0, s>>>(x, R, C, ld, partial, by_row);
         else amax_partial_kernel<true, false><<<grid, kAmaxThreads, 0, s>>>(x, R, C, ld, partial, by_row);
@@ -821,20 +830,20 @@ hipError_t launch_quantize_rows(const uint16_t *x, int64_t R, int64_t C, int64_t
                                 float *gs_out, hipStream_t s, bool scale_search)
 {
     const int grid = encode_rows_grid(R * (C >> 4), gs_in != nullptr, scale_search);
-    const Divisor by_row(C >> 4, R * (C >> 4));
+    const RowWidth width{ld == C ? Divisor() : Divisor(C >> 4, R * (C >> 4))};
     if (scale_search) {
         if (ld == C)
             quantize_rows_kernel<true, true><<<grid, 256, 0, s>>>(x, R, C, ld, gs_in, partial, n_partial, codes,
                                                                   scales, gs_out);
         else
             quantize_rows_kernel<false, true><<<grid, 256, 0, s>>>(x, R, C, ld, gs_in, partial, n_partial, codes,
-                                                                   scales, gs_out, nullptr, 0, by_row);
+                                                                   scales, gs_out, nullptr, 0, width);
     } else if (ld == C)
         quantize_rows_kernel<true><<<grid, 256, 0, s>>>(x, R, C, ld, gs_in, partial, n_partial, codes,
                                                         scales, gs_out);
     else
         quantize_rows_kernel<false><<<grid, 256, 0, s>>>(x, R, C, ld, gs_in, partial, n_partial, codes,
-                                                         scales, gs_out, nullptr, 0, by_row);
+                                                         scales, gs_out, nullptr, 0, width);
     return hipGetLastError();
 }
 
@@ -895,9 +904,9 @@ hipError_t launch_quantize_rows_slabs(const uint16_t *x, int64_t T, int64_t H, i
                                       uint8_t *codes, uint8_t *scales, float *gs_out, hipStream_t s)
 {
     const int grid = encode_rows_grid(T * H * (d >> 4), gs_in != nullptr, false);
+    const SlabWidths widths{H, slab_heads, Divisor(d >> 4, T * H * (d >> 4)), Divisor(H, T * H + 1), Divisor(slab_heads, H)};
     quantize_rows_kernel<true, false, false, true><<<grid, 256, 0, s>>>(x, T * H, d, d, gs_in, partial, n_partial, codes,
-                                                                  scales, gs_out, nullptr, 0, Divisor(d >> 4, T * H * (d >> 4)),
-                                                                  H, slab_heads, Divisor(H, T * H + 1), Divisor(slab_heads, H));
+                                                                  scales, gs_out, nullptr, 0, widths);
     return hipGetLastError();
 }
 
