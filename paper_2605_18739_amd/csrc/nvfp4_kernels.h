@@ -13,6 +13,7 @@ namespace nvfp4 {
 // GEMM 30.1 -> 29.8).  Exact for n < 2^31: with l = ceil(log2 d) and m = ceil(2^(31+l) / d) < 2^32, m d exceeds
 // 2^(31+l) by less than d, so n m / 2^(31+l) exceeds n / d by less than 1 / d (Granlund and Montgomery).
 // m = 0: indexes may be larger, plain division.
+__host__ __device__ __forceinline__ uint32_t quotient(uint32_t n, uint32_t m, int shift) { return (uint32_t)(((uint64_t)n * m) >> shift); }
 struct Divisor {
     uint32_t m = 0;
     int shift = 31;
@@ -25,7 +26,7 @@ struct Divisor {
         shift = 31 + l;
         m = (uint32_t)((((uint64_t)1 << shift) + (uint64_t)divisor - 1) / (uint64_t)divisor);
     }
-    __host__ __device__ __forceinline__ uint32_t small(uint32_t n) const { return (uint32_t)(((uint64_t)n * m) >> shift); }
+    __host__ __device__ __forceinline__ uint32_t small(uint32_t n) const { return quotient(n, m, shift); }
 };
 __host__ __device__ __forceinline__ int64_t divide(int64_t n, int64_t divisor, const Divisor &by)
 {

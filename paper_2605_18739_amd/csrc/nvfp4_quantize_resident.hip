@@ -52,28 +52,50 @@ __device__ __forceinline__ void static_for_slots(F &&f)
     }
 }
 
-struct ResidentArgs {
+// Kernel arguments.  What only the smoothed keys or the slabs read is part of their variants' arguments alone, and none has more than
+// 80 bytes: a call of a small tensor takes the host 4.4 us with 48 bytes, 4.5 with 80, 5.0 with 88 or 104.
+struct ResidentBase {
     const uint16_t *x;          // [rows, C] contiguous
     int64_t nblk;               // rows * C / 16
-    int row_shift;              // SMOOTH: log2(C / 16)
-    int sync_slot;
-    uint32_t spin_limit;        // bound of the grid-wide wait in 10 ns ticks
     uint8_t *codes, *scales;
     float *gs_out;
-    uint16_t *mean_out;         // SMOOTH: [rows] bf16 row means
-    // slab_heads > 0: the rows are (token, head) pairs of a [T, H, d] tensor and the output is regrouped into
-    // H / slab_heads slabs of slab_heads heads each, [slab][token][head in slab] (the all-to-all send buffers)
-    uint32_t nb_row, heads, slab_heads, tokens;
-    Divisor by_row, by_heads, by_slab;
+    int sync_slot;
+    uint32_t spin_limit;        // bound of the grid-wide wait in 10 ns ticks
 };
+struct RowMeans {
+    uint16_t *mean_out;         // [rows] bf16 row means
+    int row_shift;              // log2(C / 16)
+};
+// The rows are (token, head) pairs of a [T, H, d] tensor and the output is regrouped into
+// H / slab_heads slabs of slab_heads heads each, [slab][token][head in slab] (the all-to-all send buffers)
+struct Slabs {
+    uint32_t nb_row, heads, slab_heads, tokens;
+    uint32_t factor[3];         // Divisors by nb_row, heads and slab_heads (as three structs 8 bytes more)
+    uint8_t shift[3];
+    Slabs(int64_t nblk, int64_t nb_row_, int64_t heads_, int64_t slab_heads_)
+        : nb_row((uint32_t)nb_row_), heads((uint32_t)heads_), slab_heads((uint32_t)slab_heads_), tokens((uint32_t)(nblk / nb_row_ / heads_))
+    {
+        const Divisor by[3] = {Divisor(nb_row, nblk), Divisor(heads, nblk / nb_row), Divisor(slab_heads, heads)};
+        for (int i = 0; i < 3; ++i) {
+            factor[i] = by[i].m;
+            shift[i] = (uint8_t)by[i].shift;
+        }
+    }
+    __device__ __forceinline__ uint32_t divide(int i, uint32_t n) const { return quotient(n, factor[i], shift[i]); }
+};
+struct NoRowMeans {};
+struct NoSlabs {};
+template <bool SMOOTH, bool SLABS>
+struct ResidentArgs : ResidentBase, std::conditional_t<SMOOTH, RowMeans, NoRowMeans>, std::conditional_t<SLABS, Slabs, NoSlabs> {};
+static_assert(sizeof(ResidentArgs<false, false>) <= 80 && sizeof(ResidentArgs<true, false>) <= 80 && sizeof(ResidentArgs<false, true>) <= 80);
 
 // output block index of input block g (fewer than 2^31 blocks fit on the chip: 32-bit arithmetic)
-__device__ __forceinline__ uint32_t output_block(uint32_t g, const ResidentArgs &a)
+__device__ __forceinline__ uint32_t output_block(uint32_t g, const NoSlabs &) { return g; }
+__device__ __forceinline__ uint32_t output_block(uint32_t g, const Slabs &a)
 {
-    if (a.slab_heads == 0) return g;
-    const uint32_t row = a.by_row.small(g), b = g - row * a.nb_row;
-    const uint32_t t = a.by_heads.small(row), h = row - t * a.heads;
-    const uint32_t slab = a.by_slab.small(h), hl = h - slab * a.slab_heads;
+    const uint32_t row = a.divide(0, g), b = g - row * a.nb_row;
+    const uint32_t t = a.divide(1, row), h = row - t * a.heads;
+    const uint32_t slab = a.divide(2, h), hl = h - slab * a.slab_heads;
     return ((slab * a.tokens + t) * a.slab_heads + hl) * a.nb_row + b;
 }
 
@@ -85,8 +107,8 @@ __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b)
 
 // One block's share of pass 1: (SMOOTH: remove the row mean, in place;) largest |bf16| pattern.
 // live: the block exists (lanes past the end hold zeros and only take part in the shuffles).
-template <bool SMOOTH, bool WRITE_MEAN = true>
-__device__ __forceinline__ uint32_t block_pass1(uint32_t (&w)[8], bool live, int64_t g, const ResidentArgs &a)
+template <bool SMOOTH, bool WRITE_MEAN = true, class Args>
+__device__ __forceinline__ uint32_t block_pass1(uint32_t (&w)[8], bool live, int64_t g, const Args &a)
 {
     if constexpr (SMOOTH) {
         const int nb_row = 1 << a.row_shift;
@@ -110,9 +132,9 @@ struct Pass2Out {
 // Two blocks through one straight-line stretch of code.  The stores go through buffer descriptors sized to
 // the outputs: a block past the end of the tensor gets an offset outside the descriptor's range, which the
 // hardware drops, so no branch surrounds the stores and the compiler can schedule across them.
-template <bool SEARCH>
+template <bool SEARCH, class Args>
 __device__ __forceinline__ void pair_pass2(const uint32_t (&wa)[8], const uint32_t (&wb)[8], int64_t ga, int64_t gb, int64_t nblk,
-                                           const TensorScale &ts, const Pass2Out &out, const ResidentArgs &a)
+                                           const TensorScale &ts, const Pass2Out &out, const Args &a)
 {
     uint32_t sa, a0, a1, sb, b0, b1;
     if constexpr (SEARCH) {
@@ -130,8 +152,8 @@ __device__ __forceinline__ void pair_pass2(const uint32_t (&wa)[8], const uint32
     __builtin_amdgcn_raw_buffer_store_b8((uint8_t)sb, out.rscales, live_b ? ob : kDropped, 0, 0);
 }
 
-template <bool SEARCH, bool SMOOTH>
-__global__ __launch_bounds__(kResThreads) void quantize_rows_resident_kernel(ResidentArgs a)
+template <bool SEARCH, bool SMOOTH, bool SLABS>
+__global__ __launch_bounds__(kResThreads) void quantize_rows_resident_kernel(ResidentArgs<SMOOTH, SLABS> a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     uint4v *lds_blk = (uint4v *)lds;                                   // [slot][half][thread]
@@ -377,19 +399,19 @@ bool quantize_rows_resident_pays(int64_t nblk, bool search, bool smooth, bool li
     return one_launch_pays(nblk, search, smooth, library_scratch);
 }
 
-template <bool SEARCH, bool SMOOTH>
-static hipError_t launch_resident(const ResidentArgs &a, int grid, hipStream_t s)
+template <bool SEARCH, bool SMOOTH, bool SLABS>
+static hipError_t launch_resident(const ResidentArgs<SMOOTH, SLABS> &a, int grid, hipStream_t s)
 {
     static uint64_t attr_set = 0;              // the dynamic LDS limit is raised once per kernel variant and device
     int dev = 0;
     if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
     if (((attr_set >> (dev & 63)) & 1u) == 0) {
-        hipError_t e = hipFuncSetAttribute((const void *)quantize_rows_resident_kernel<SEARCH, SMOOTH>,
+        hipError_t e = hipFuncSetAttribute((const void *)quantize_rows_resident_kernel<SEARCH, SMOOTH, SLABS>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kResLdsBytes);
         if (e != hipSuccess) return e;
         attr_set |= 1ull << (dev & 63);
     }
-    quantize_rows_resident_kernel<SEARCH, SMOOTH><<<grid, kResThreads, kResLdsBytes, s>>>(a);
+    quantize_rows_resident_kernel<SEARCH, SMOOTH, SLABS><<<grid, kResThreads, kResLdsBytes, s>>>(a);
     return hipGetLastError();
 }
 
@@ -397,28 +419,14 @@ hipError_t launch_quantize_rows_resident(const uint16_t *x, int64_t rows, int64_
                                          uint8_t *scales, float *gs_out, bool scale_search, uint16_t *mean_out,
                                          hipStream_t s, int heads, int slab_heads)
 {
-    ResidentArgs a{};
-    a.x = x;
-    a.nblk = rows * (C >> 4);
-    const int grid = (int)std::min<int64_t>(kResMaxGrid, (a.nblk + kResThreads - 1) / kResThreads);
-    a.row_shift = mean_out ? __builtin_ctzll((unsigned long long)(C >> 4)) : 0;
-    a.sync_slot = (int)(g_next_sync_slot++ % kSyncSlots);
-    a.spin_limit = g_spin_limit;
-    a.codes = codes;
-    a.scales = scales;
-    a.gs_out = gs_out;
-    a.mean_out = mean_out;
-    a.nb_row = (uint32_t)(C >> 4);
-    a.heads = (uint32_t)heads;
-    a.slab_heads = (uint32_t)slab_heads;
-    a.tokens = heads > 0 ? (uint32_t)(rows / heads) : 0u;
-    if (slab_heads > 0) {
-        a.by_row = Divisor(C >> 4, a.nblk);
-        a.by_heads = Divisor(heads, rows);
-        a.by_slab = Divisor(slab_heads, heads);
-    }
-    if (mean_out) return launch_resident<true, true>(a, grid, s);       // smoothed keys always take the scale search
-    return scale_search ? launch_resident<true, false>(a, grid, s) : launch_resident<false, false>(a, grid, s);
+    const int64_t nblk = rows * (C >> 4);
+    const int grid = (int)std::min<int64_t>(kResMaxGrid, (nblk + kResThreads - 1) / kResThreads);
+    const ResidentBase base{x, nblk, codes, scales, gs_out, (int)(g_next_sync_slot++ % kSyncSlots), g_spin_limit};
+    if (mean_out)                                                       // smoothed keys always take the scale search
+        return launch_resident<true, true, false>({base, {mean_out, __builtin_ctzll((unsigned long long)(C >> 4))}, {}}, grid, s);
+    if (slab_heads > 0)                                                 // the slabs never do
+        return launch_resident<false, false, true>({base, {}, Slabs(nblk, C >> 4, heads, slab_heads)}, grid, s);
+    return scale_search ? launch_resident<true, false, false>({base, {}, {}}, grid, s) : launch_resident<false, false, false>({base, {}, {}}, grid, s);
 }
 
 }  // namespace nvfp4
