@@ -4,34 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-namespace nvfp4 {
+#include "nvfp4_quantize_plan.h"
 
-// Division of indexes by a width that a whole launch shares (blocks of a row, heads): one 32 x 32-bit multiplication and a
-// shift with a factor that the host computes, where a division by a run-time number is twenty to a hundred and more vector
-// instructions.  The all-to-all order takes three of them a block, beside the 75 of the encoding (us: 4620x24x128 15.7 -> 14.4
-// in one launch; in two passes 2000x16x128 11.5 -> 10.4, 300x24x128 11.8 -> 10.6); padded rows take one (3520x4096 with its
-// GEMM 30.1 -> 29.8).  Exact for n < 2^31: with l = ceil(log2 d) and m = ceil(2^(31+l) / d) < 2^32, m d exceeds
-// 2^(31+l) by less than d, so n m / 2^(31+l) exceeds n / d by less than 1 / d (Granlund and Montgomery).
-// m = 0: indexes may be larger, plain division.
-__host__ __device__ __forceinline__ uint32_t quotient(uint32_t n, uint32_t m, int shift) { return (uint32_t)(((uint64_t)n * m) >> shift); }
-struct Divisor {
-    uint32_t m = 0;
-    int shift = 31;
-    Divisor() = default;
-    Divisor(int64_t divisor, int64_t indexes)         // every n divided is below `indexes`
-    {
-        if (divisor < 1 || divisor >= (1ll << 31) || indexes > (1ll << 31)) return;
-        int l = 0;
-        while ((1ll << l) < divisor) ++l;
-        shift = 31 + l;
-        m = (uint32_t)((((uint64_t)1 << shift) + (uint64_t)divisor - 1) / (uint64_t)divisor);
-    }
-    __host__ __device__ __forceinline__ uint32_t small(uint32_t n) const { return quotient(n, m, shift); }
-};
-__host__ __device__ __forceinline__ int64_t divide(int64_t n, int64_t divisor, const Divisor &by)
-{
-    return by.m ? (int64_t)by.small((uint32_t)n) : n / divisor;
-}
+namespace nvfp4 {
 
 constexpr int kMaxPartials = 1024;   // workgroups of the amax pass = partial maxima in the workspace
 

@@ -8,7 +8,6 @@
 #include <type_traits>
 
 #include "nvfp4_kernels.h"
-#include "nvfp4_quantize_plan.h"
 
 namespace nvfp4 {
 

@@ -1,5 +1,5 @@
-// Launch rules of the row quantizers: plain C++ without HIP types, so that they can be compiled and exercised on their
-// own (tests build them with the address and undefined-behaviour sanitizers).
+// Index division and launch rules of the row quantizers: plain C++ without HIP types, so that they can be compiled and exercised
+// on their own (tests build them with the address and undefined-behaviour sanitizers).  Kernels call the constexpr functions.
 #ifndef NVFP4_QUANTIZE_PLAN_H
 #define NVFP4_QUANTIZE_PLAN_H
 
@@ -7,6 +7,34 @@
 #include <cstdint>
 
 namespace nvfp4 {
+
+// Division of indexes by a width that a whole launch shares (blocks of a row, heads): one 32 x 32-bit multiplication and a
+// shift with a factor that the host computes, where a division by a run-time number is twenty to a hundred and more vector
+// instructions.  The all-to-all order takes three of them a block, beside the 75 of the encoding, padded rows one (us, replayed
+// from a graph, the same grids, divided -> multiplied: all-to-all order of 4620x24x128 in one launch 16.5 -> 15.2, in two passes
+// 0.4 M blocks 11.0 -> 10.4, 0.7 M 14.2 -> 13.5, 3.5 M 48.5 -> 45.6; padded rows 3.5 M 45.5 -> 44.3, with the search 57.1 -> 55.8).
+// Exact for n < 2^31: with l = ceil(log2 d) and m = ceil(2^(31+l) / d) < 2^32, m d exceeds
+// 2^(31+l) by less than d, so n m / 2^(31+l) exceeds n / d by less than 1 / d (Granlund and Montgomery).
+// m = 0: indexes may be larger, plain division.
+constexpr uint32_t quotient(uint32_t n, uint32_t m, int shift) { return (uint32_t)(((uint64_t)n * m) >> shift); }
+struct Divisor {
+    uint32_t m = 0;
+    int shift = 31;
+    Divisor() = default;
+    constexpr Divisor(int64_t divisor, int64_t indexes)         // every n divided is below `indexes`
+    {
+        if (divisor < 1 || divisor >= (1ll << 31) || indexes > (1ll << 31)) return;
+        int l = 0;
+        while ((1ll << l) < divisor) ++l;
+        shift = 31 + l;
+        m = (uint32_t)((((uint64_t)1 << shift) + (uint64_t)divisor - 1) / (uint64_t)divisor);
+    }
+    constexpr uint32_t small(uint32_t n) const { return quotient(n, m, shift); }
+};
+constexpr int64_t divide(int64_t n, int64_t divisor, const Divisor &by)
+{
+    return by.m ? (int64_t)by.small((uint32_t)n) : n / divisor;
+}
 
 // Workgroups of 256 lanes of a pass that encodes rows of `nblk` blocks of 16 elements.
 // With partial maxima: four blocks to a lane, so that what every workgroup does first (the partial maxima again, the scale's tie

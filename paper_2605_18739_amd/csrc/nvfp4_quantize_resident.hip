@@ -16,7 +16,6 @@
 
 #include <algorithm>
 #include "nvfp4_kernels.h"
-#include "nvfp4_quantize_plan.h"
 
 #include <type_traits>
 

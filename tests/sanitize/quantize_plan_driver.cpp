@@ -1,5 +1,5 @@
-// Exercises the launch rules of the row quantizers (csrc/nvfp4_quantize_plan.h, host-only) under the address and
-// undefined-behaviour sanitizers.  Prints "ok" on success.
+// Exercises the index division and the launch rules of the row quantizers (csrc/nvfp4_quantize_plan.h, no HIP) under the
+// address and undefined-behaviour sanitizers.  Prints "ok" on success.
 #include "../../paper_2605_18739_amd/csrc/nvfp4_quantize_plan.h"
 
 #include <cstdio>
@@ -41,8 +41,35 @@ static void check_one_launch()
     }
 }
 
+// The division that the kernels run: numbers beside multiples of the width, where a wrong factor shows first, and at both ends
+// of the range; from 2^31 indexes on, and for widths that have no factor, the plain division.
+static void check_divisor(int64_t d, uint64_t &seed)
+{
+    const int64_t top = 1ll << 31;
+    const Divisor by(d, top), beyond(d, top + 1);
+    require(beyond.m == 0, "a factor beyond its range", d);
+    require((by.m != 0) == (d < top), "no factor inside its range", d);
+    for (int i = 0; i < 64; ++i) {
+        seed = seed * 6364136223846793005ull + 1442695040888963407ull;
+        const int64_t q = i == 0 ? 0 : i == 1 ? (top - 1) / d : (int64_t)((seed >> 16) % (uint64_t)((top - 1) / d + 1));
+        for (int64_t n : {q * d - 1, q * d, q * d + 1, q * d + d - 1, top - 1}) {
+            if (n >= 0 && n < top) require(divide(n, d, by) == n / d, "quotient", n);
+            const int64_t large = n + (1ll << 33);
+            if (n >= 0) require(divide(large, d, beyond) == large / d, "quotient of a large index", large);
+        }
+    }
+}
+
 int main()
 {
+    uint64_t seed = 31;
+    for (int64_t d = 1; d < 3000; ++d) check_divisor(d, seed);
+    for (int k = 9; k <= 31; ++k)
+        for (int64_t e : {-1, 0, 1}) check_divisor((1ll << k) + e, seed);
+    for (int i = 0; i < 3000; ++i) {
+        seed = seed * 6364136223846793005ull + 1442695040888963407ull;
+        check_divisor(1 + (int64_t)((seed >> 20) % ((1ull << 31) - 1)), seed);
+    }
     for (int64_t b = 1; b <= (1ll << 40); b <<= 1)
         for (int64_t e : {-1, 0, 1, 255, 257})
             if (b + e > 0) check_grid(b + e);

@@ -96,6 +96,21 @@ def test_quantize_padded_rows_of_many_widths(oracle, R, C, ld, search):
     assert_q_equal(nv.nvfp4_quantize_4over6(view) if search else nv.nvfp4_quantize(view), want, f"{R}x{C} of {ld}")
 
 
+@pytest.mark.parametrize("R,C,ld", [(1100, 4112, 4120), (2100, 4112, 4120), (5836, 4112, 4128), (5837, 4112, 4128)])
+def test_quantize_padded_rows_of_several_turns_a_lane(oracle, R, C, ld):
+    """Padded rows of 257 blocks each: with 1024 workgroups a lane of the search comes to its second turn at 262 144 blocks and one of the plain
+    rule at 524 288; 1.5 M blocks (between the last two) is where the plain rule goes from four blocks to a lane to two."""
+    say(f"[quantize] {R}x{C} of {ld}")
+    xb = wl.to_bf16_bits(np.random.default_rng(R).standard_normal((R, ld)).astype(np.float32))
+    xc = np.ascontiguousarray(xb[:, :C])
+    view = dev_bf16(xb)[:, :C]
+    want = oracle.quantize(xc)
+    plain = nv.nvfp4_quantize(view)
+    assert_q_equal(plain, want, "plain")
+    assert_q_equal(nv.nvfp4_quantize(view, global_scale_in=plain.global_scale), want, "given scale")
+    assert_q_equal(nv.nvfp4_quantize_4over6(view), oracle.quantize(xc, four_over_six=True), "search")
+
+
 @pytest.mark.parametrize("offset", [0.0, 2.0 ** -23, -2.0 ** -23, 2.0 ** -19, -2.0 ** -19, -2.0 ** -17, 2.0 ** -16])
 def test_quantize_tensor_scales_on_and_beside_ties(oracle, offset):
     """Given scales (bf16 number) / (odd number below 128), and the same a little off: elements and block maxima of

@@ -244,7 +244,7 @@ def test_one_nudge_of_the_tensor_scale_settles_every_near_tie():
 
 
 def test_division_by_multiplication_is_exact_below_2_to_31():
-    """Divisor in csrc/nvfp4_kernels.h: n / d as (n m) >> (31 + l), l = ceil(log2 d), m = ceil(2^(31+l) / d).  Widths of every
+    """The bound of Divisor in csrc/nvfp4_quantize_plan.h, on unlimited integers (the compiled struct itself runs in test_sanitizers): n / d as (n m) >> (31 + l), l = ceil(log2 d), m = ceil(2^(31+l) / d).  Widths of every
     size; n beside multiples of d, where a wrong factor shows first, and at both ends."""
     rng = np.random.default_rng(31)
     widths = list(range(1, 300)) + [1 << k for k in range(9, 31)] + [(1 << k) + e for k in range(9, 31) for e in (-1, 1)]

@@ -1,5 +1,5 @@
 """CPU builds with -fsanitize=address,undefined: the whole oracle on small exact-size buffers, and the
-host-side GEMM launch planner over a sweep of shapes (coverage invariant) and the row quantizers' launch rules.  No GPU, no HIP."""
+host-side GEMM launch planner over a sweep of shapes (coverage invariant) and the row quantizers' index division and launch rules.  No GPU, no HIP."""
 import os
 import subprocess
 
@@ -30,5 +30,5 @@ def test_gemm_launch_planner_under_sanitizers(tmp_path):
     _build_and_run(tmp_path, "g++", ["-std=c++17", os.path.join(HERE, "sanitize", "plan_driver.cpp")], [])
 
 
-def test_row_quantizer_launch_rules_under_sanitizers(tmp_path):
+def test_row_quantizer_index_division_and_launch_rules_under_sanitizers(tmp_path):
     _build_and_run(tmp_path, "g++", ["-std=c++17", os.path.join(HERE, "sanitize", "quantize_plan_driver.cpp")], [])
