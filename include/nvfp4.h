@@ -87,9 +87,10 @@ enum { NVFP4_OP_QUANTIZE = 0, NVFP4_OP_KV_QUANT = 1, NVFP4_OP_GEMM_ACT_QUANT = 2
  *               the backward GEMMs need it).
  * global_scale_in: device pointer to one float, or NULL.  NULL: the scale is
  *               derived from the tensor's amax: contiguous row-block tensors of up
- *               to ~120 MB are held on the chip between the two steps (one launch,
+ *               to ~120 MB can be held on the chip between the two steps (one launch,
  *               one pass over x; the launch occupies every compute unit while it
- *               runs), larger or strided ones take one extra pass over x.  A
+ *               runs; nvfp4_set_one_launch says which are), others take one extra
+ *               pass over x.  A
  *               tensor that is needed along both axes (every training operand
  *               is) has one amax: pass the first call's out->global_scale to
  *               the second call and its extra pass is saved.

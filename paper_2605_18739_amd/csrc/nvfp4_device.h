@@ -296,9 +296,9 @@ __device__ __forceinline__ void quantize_pair16(const uint32_t (&wa)[8], const u
 //     10^5 is still open;
 //  3. the fp64 definition.
 // Gains and errors below 2^-100, where fp32 may lose its relative accuracy, or that are no finite numbers are never sure.
-// Bound by VALU issue (in 83 % of the SIMDs' cycles in the streaming pass of the smoothed keys): 224 vector instructions per
-// block in the compiled pass (the bracketed search took about 450), the largest groups 16 unpack, 8 maximum, 20 scales,
-// 32 multiplies, 32 conversions, 32 dot products.
+// Bound by VALU issue (in 69 % of the SIMDs' cycles in the streaming passes of the search and of the smoothed keys) and by the latency
+// of the one block in flight: 224 vector instructions per block in the compiled pass (the bracketed search took about 450), the
+// largest groups 16 unpack, 8 maximum, 20 scales, 32 multiplies, 32 conversions, 32 dot products.
 __device__ __forceinline__ float block_error_f32(const float (&f)[16], const uint32_t (&c)[2], float den)
 {
     typedef float float2v __attribute__((ext_vector_type(2)));

@@ -65,7 +65,7 @@ inline int encode_rows_grid(int64_t nblk, bool given_scale, bool search)
 // Whether a tensor that fits on the chip takes the one-launch form (the figures stand in nvfp4_quantize_resident.hip).
 // library_scratch: the two passes would keep their partial maxima in the library's one array per GPU, where calls that overlap
 // race, while the exchange words of the one-launch form are one of 64 sets; such calls keep the lower bound, at which
-// the two forms are within a microsecond (0.8 M to 0.95 M blocks: one launch 14.5 to 15.2 us, two passes 13.4 to 15.2).
+// the two forms are within a microsecond (on the device 0.80 M 14.2 us and 13.3, 0.89 M 14.7 and 13.9).
 constexpr int64_t kOneLaunchBelow = 12000, kOneLaunchFrom = 950000, kOneLaunchFromScratch = 800000;
 
 inline bool one_launch_pays(int64_t nblk, bool search, bool smooth, bool library_scratch)

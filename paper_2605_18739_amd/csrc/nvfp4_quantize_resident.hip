@@ -52,7 +52,8 @@ __device__ __forceinline__ void static_for_slots(F &&f)
 }
 
 // Kernel arguments.  What only the smoothed keys or the slabs read is part of their variants' arguments alone, and none has more than
-// 80 bytes: a call of a small tensor takes the host 4.4 us with 48 bytes, 4.5 with 80, 5.0 with 88 or 104.
+// 80 bytes: a call of a small tensor takes the host 4.4 us with 48 bytes, 4.5 with 80, 5.0 with 88 or 104 (in sessions where two launches
+// take it 8 us; where they take 6.5, all sizes are within 0.05 of 3.9).
 struct ResidentBase {
     const uint16_t *x;          // [rows, C] contiguous
     int64_t nblk;               // rows * C / 16
@@ -379,16 +380,22 @@ bool quantize_rows_resident_fits(int64_t rows, int64_t C, int64_t ld, bool smoot
 
 // Whether the one-launch form is taken for a tensor that fits.  It fetches the tensor once where the two passes
 // fetch it twice, but pays for the exchange across the grid, and its encoding runs at two waves per SIMD where the
-// streaming pass has six to eight.  Measured in one session, calls back to back on inputs in turn that together exceed the
-// 256 MB Infinity Cache (us, one launch / two passes, blocks of 16 elements):
-//   plain rule    12 k 6.5 / 9.3   192 k 10.1 / 9.6   384 k 11.0 / 10.6   676 k 13.1 / 12.5   887 k 14.8 / 14.0   998 k 15.3 / 15.8   1.7 M 21.0 / 23.3   3.5 M 34.6 / 42.7
-//   slabs         12 k 8.8 / 12.4  192 k 10.5 / 13.1  384 k 11.6 / 12.5   676 k 13.3 / 13.5   887 k 15.2 / 15.2   998 k 15.7 / 17.0   1.7 M 21.7 / 23.5   3.5 M 36.2 / 43.8
-//   scale search  12 k 7.6 / 9.1   192 k 11.6 / 9.5   676 k 17.0 / 14.1   1.7 M 29.6 / 26.4   2.2 M 35.1 / 33.0   2.6 M 39.1 / 38.1   3.0 M 44.2 / 41.1   3.5 M 50.6 / 47.8
-//   smoothed keys (with an earlier grid of the two passes) 192 k 12.6 / 9.8   676 k 19.7 / 17.3   3.5 M 64.5 / 59.6
-// So: below 12 k blocks one launch where that saves the second launch (host-bound), from there
-// on two passes until the second fetch costs more than the exchange, at 0.95 M blocks for the plain rule (the slabs, even from
-// 0.7 M to 0.9 M, follow it); with the search, whose encoding wants eight waves per SIMD, two passes throughout.  mode 1:
-// whenever it fits; mode 2: never.
+// streaming pass has six to eight.  Both forms in one session, on inputs in turn that together exceed the 256 MB Infinity Cache
+// from 0.4 M blocks on (us, one launch / two passes, by blocks of 16 elements).  On the device, replayed from a graph:
+//                  1.5 k        12 k        48 k       0.19 M       0.38 M       0.68 M       0.80 M       0.89 M       1.0 M        1.7 M        2.2 M        2.6 M        3.5 M
+//   plain rule     5.3 / 5.0   6.4 / 5.3   8.0 / 6.0  10.2 /  7.5  11.2 /  9.8  13.1 / 12.1  14.2 / 13.3  14.7 / 13.9  15.4 / 16.3  21.4 / 23.1  24.4 / 28.2  27.1 / 33.0  34.8 / 42.2
+//   slabs          5.5 / 5.2   6.5 / 5.5   8.2 / 6.4  10.4 /  7.9  11.5 / 10.2  13.3 / 12.9  14.6 / 14.4  15.0 / 14.9  15.8 / 17.1  21.8 / 23.8  25.0 / 28.6  27.7 / 33.9  35.9 / 43.6
+//   scale search   6.5 / 5.3   7.9 / 5.9   9.5 / 6.9  11.8 /  8.5  14.1 / 11.0  17.2 / 14.2  19.3 / 16.1  19.7 / 16.9  20.7 / 19.4  30.3 / 27.7  34.8 / 33.5  38.7 / 38.5  50.3 / 48.6
+//   smoothed keys  7.2 / 6.5   8.3 / 6.9  10.1 / 8.1  12.6 /  9.9  15.4 / 13.1  19.8 / 16.7  22.8 / 19.6  23.5 / 20.2  24.5 / 21.3  35.9 / 31.0  43.6 / 37.8  48.3 / 41.5  62.2 / 54.4
+// Called from Python one after another, outputs given (a second launch takes the host 2.8 us; from 0.2 M blocks on as above):
+//   plain rule     5.4 / 8.3   6.2 / 8.3   7.8 / 8.3   9.9 /  8.1      slabs  5.6 / 8.3   6.3 / 8.4   8.0 / 8.3  10.0 /  8.3
+//   scale search   6.5 / 8.3   7.5 / 8.2   9.2 / 8.3  11.6 /  8.7      keys   7.1 / 8.5   8.1 / 8.4   9.7 / 8.4  12.4 /  9.7
+// and with outputs allocated by the call (8 us on the host with one launch, 11.3 with two) one launch is ahead up to 0.2 M blocks, even at 0.4 M.
+// So: by the device's time, on which the two passes are ahead from the smallest size up to 0.95 M blocks with the plain rule
+// (the slabs cross at the same place) and throughout with the search and for smoothed keys, whose encoding wants the waves;
+// except that below 12 k blocks the plain rule and the slabs take one launch, which saves a host-bound caller 2 to 3 us and costs
+// a graph at most one.  (Above 12 k blocks a graph's loss grows to 2.7 us at 0.1 M while the host-bound caller's gain goes.)
+// mode 1: whenever it fits; mode 2: never.
 static int g_one_launch_mode = 0;
 void set_one_launch_mode(int mode) { g_one_launch_mode = mode; }
 bool quantize_rows_resident_pays(int64_t nblk, bool search, bool smooth, bool library_scratch)
